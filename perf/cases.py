@@ -203,14 +203,20 @@ class _Handles:
         B.tl_pool_destroy(self.pool)
 
 
-def _pool(case, seed, ids, fills, extra):
-    """Pool tensors with N(0, 1) everywhere and the segments `ids` at random slots; `extra` slots stay free."""
+def _pool_tensors(case, seed, ids, extra):
+    """Pool tensors with N(0, 1) everywhere, the slots of the segments `ids` at random and the generator of what
+    follows; `extra` slots stay free."""
     C, hkv = case["seg_len"], case["kv_heads"]
     n_slots = max(8, len(ids) + len(ids) // 16 + extra)
     gen = torch.Generator(device="cuda").manual_seed(seed)
     kv = [torch.empty((n_slots, C, hkv, D), dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(2)]
-    pool = B.tl_pool_create(n_slots, C, hkv, D, kv[0], kv[1])
-    slots = np.random.Generator(np.random.PCG64(seed)).permutation(n_slots)[:len(ids)]
+    return kv, np.random.Generator(np.random.PCG64(seed)).permutation(n_slots)[:len(ids)], gen
+
+
+def _pool(case, seed, ids, fills, extra):
+    kv, slots, gen = _pool_tensors(case, seed, ids, extra)
+    C, n_slots = case["seg_len"], kv[0].shape[0]
+    pool = B.tl_pool_create(n_slots, C, case["kv_heads"], D, kv[0], kv[1])
     B.tl_pool_adopt(pool, ids, slots, [fills.get(i, C) for i in ids])
     return pool, kv, gen
 
@@ -314,3 +320,76 @@ def _run_serve(s):
     for plan in plans:
         B.tl_plan_destroy(plan)
     return [t for o in s["outputs"] for t in o] + s["kv"] + [slots]
+
+
+# ---- the same numbers in 64 bits ---------------------------------------------------------------------------
+def exact(case, seed):
+    return _exact_step(case, seed) if case["kind"] == "step" else _exact_serve(case, seed)
+
+
+def _exact_attend(q, k_pre, v_pre, mult, k_new, v_new):
+    """Softmax attention of one request's new tokens q [n, hq, D] over prefix keys [L, hkv, D], key j counted
+    mult[j] times (None: once), and over the new tokens up to the row's own; returns (O [n, hq, D], LSE [n, hq])."""
+    n, hq, _ = q.shape
+    hkv, L = k_new.shape[1], k_pre.shape[0]
+    out = torch.empty((n, hq, D), dtype=torch.float64, device="cuda")
+    lse = torch.empty((n, hq), dtype=torch.float64, device="cuda")
+    extra = None if mult is None else torch.log(mult.double())
+    step = max(1, (1 << 27) // ((L + n) * (hq // hkv)))          # tokens at a time: 1 GiB of scores
+    for g in range(hkv):
+        heads = slice(g * (hq // hkv), (g + 1) * (hq // hkv))
+        k = torch.cat([k_pre[:, g], k_new[:, g]]).double()
+        v = torch.cat([v_pre[:, g], v_new[:, g]]).double()
+        for t in range(0, n, step):
+            e = min(n, t + step)
+            s = (q[t:e, heads].double().reshape(-1, D) @ k.t() * SCALE).view(e - t, -1, L + n)
+            if extra is not None:
+                s[:, :, :L] += extra
+            later = torch.arange(n, device="cuda")[None, :] > torch.arange(t, e, device="cuda")[:, None]
+            s[:, :, L:].masked_fill_(later[:, None, :], -math.inf)
+            top = torch.logsumexp(s, dim=-1)
+            lse[t:e, heads] = top
+            s.sub_(top[..., None]).exp_()
+            out[t:e, heads] = (s.view(-1, L + n) @ v).view(e - t, -1, D)
+    return out, lse
+
+
+def _exact_step(case, seed):
+    new, lists, fills = _step_layout(case)
+    C, hq, hkv = case["seg_len"], case["q_heads"], case["kv_heads"]
+    ids = list(dict.fromkeys(i for l in lists for i in l))
+    kv, slots, gen = _pool_tensors(case, seed, ids, 0)
+    slot_of = dict(zip(ids, slots.tolist()))
+    T = int(new.sum())
+    q, k, v = _rows(gen, T, hq), _rows(gen, T, hkv), _rows(gen, T, hkv)
+    outs, at = [], 0
+    for lq, ids_r in zip(new.tolist(), lists):
+        times = {}
+        for i in ids_r:
+            times[i] = times.get(i, 0) + 1
+        token = [slot_of[i] * C + np.arange(fills.get(i, C)) for i in times]
+        mult = [np.full(fills.get(i, C), m) for i, m in times.items()]
+        index = torch.from_numpy(np.concatenate(token) if token else np.zeros(0, np.int64)).cuda()
+        mult = torch.from_numpy(np.concatenate(mult)).cuda() if case["zipf"] else None
+        pre = [x.view(-1, hkv, D)[index] for x in kv]
+        outs.append(_exact_attend(q[at:at + lq], *pre, mult, k[at:at + lq], v[at:at + lq]))
+        at += lq
+    return torch.cat([o for o, _ in outs]), torch.cat([l for _, l in outs])
+
+
+def _exact_serve(case, seed):
+    S, hq, hkv, C = case["n_req"], case["q_heads"], case["kv_heads"], case["seg_len"]
+    steps = _serve_steps(case)
+    kv, slots, gen = _pool_tensors(case, seed, list(range(case["shared"])), S * (-(-sum(steps) // C)))
+    inputs = [(_rows(gen, S * lq, hq), _rows(gen, S * lq, hkv), _rows(gen, S * lq, hkv)) for lq in steps]
+    index = torch.from_numpy(slots.astype(np.int64)).cuda()
+    seen = [[x[index].view(-1, hkv, D) for x in kv] for _ in range(S)]
+    outs = []
+    for lq, (q, k, v) in zip(steps, inputs):
+        per = []
+        for r in range(S):
+            rows = slice(r * lq, (r + 1) * lq)
+            per.append(_exact_attend(q[rows], *seen[r], None, k[rows], v[rows]))
+            seen[r] = [torch.cat([x, y[rows]]) for x, y in zip(seen[r], (k, v))]
+        outs += [torch.cat([o for o, _ in per]), torch.cat([l for _, l in per])]
+    return outs + [None, None, None]           # the pool's rows are copies and the slots whole numbers
