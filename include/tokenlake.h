@@ -18,9 +18,8 @@
  *    default stream) and return without synchronising.
  *    tl_segment_attn, tl_causal_block, tl_merge and tl_fused_attn enqueue nothing but
  *    kernels, except that the first call that uses a plan makes the plan's device copy (one
- *    hipMalloc, one asynchronous copy on `stream`) and the first tl_segment_attn after an
- *    adopt or evict uploads the pool's fill table (one asynchronous copy): run one step
- *    eagerly before capturing a step into a HIP graph.
+ *    hipMalloc, one asynchronous copy on `stream`): run one step eagerly before capturing a
+ *    step into a HIP graph.
  *  - A pool, and the plans made from it, belong to one host thread at a time: calls on the
  *    same pool or plan from several threads need the caller's own lock (the id table, the
  *    use stamps and the lazily made device copies are plain host state).  Different pools
@@ -72,8 +71,8 @@ const char* tl_last_error(void);
  * Slot s holds K and V as [seg_len, kv_heads, head_dim] bf16 each, at
  *   k_dev + s * seg_len * kv_heads * head_dim   (same for v_dev).
  * A slot has `fill` valid tokens (1..seg_len); tokens at or beyond fill do not exist for
- * attention.  The pool object lives on the host; it owns the id->slot table, the per-slot
- * fill / reference count / last-use stamp, and a device mirror of fill[].
+ * attention.  The pool object lives on the host; it owns the id->slot table and the per-slot
+ * fill / reference count / last-use stamp.
  * ------------------------------------------------------------------------------------ */
 typedef struct tl_pool tl_pool;
 

@@ -31,11 +31,10 @@ struct AttnArgs {
   void* final_out;        // fused rows only: [n_tokens, q_heads, 128] fp32 or bf16
   float* final_lse;       // fused rows only: [n_tokens, q_heads] or null
   int32_t final_is_bf16;
-  const int32_t* fill;    // per-slot valid tokens (pool work)
   const Work* work;
   const int32_t* tok;     // token index lists
-  const int32_t* slots;   // slot lists of the split-K units
-  const float* slot_lm;   // log2(times the unit's run lists the slot), parallel to slots; null = all once
+  const int32_t* unit_slots;  // slot lists of the split-K units: pairs (first kv row, valid tokens)
+  const float* slot_lm;   // log2(times the unit's run lists the slot), one per pair; null = all once
   const int32_t* tile_base;  // first kv row of each full 64-token tile (pool row tiles)
   const int32_t* part_tile;  // (first kv row, valid tokens) of each cut-short tile
   const float* tile_lm;      // log2(times the tile's slot is listed), parallel to tile_base
@@ -45,7 +44,8 @@ struct AttnArgs {
   const float* prior_lse;     // [rows, q_heads]
   float* out;             // [rows, q_heads, 128]
   float* lse;             // [rows, q_heads]
-  int32_t q_heads, kv_heads, group, seg_len, n_work;   // group = q_heads / kv_heads
+  int32_t q_heads, kv_heads, group, n_work;   // group = q_heads / kv_heads
+  int32_t unit_heads_log2;  // split-K units: log2 of the kv heads per workgroup
   float scale;            // softmax scale
   float scale_log2e;      // scale * log2(e)
 };

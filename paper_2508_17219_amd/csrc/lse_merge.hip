@@ -190,7 +190,8 @@ __global__ __launch_bounds__(256) void single_token_self_kernel(const uint16_t* 
 void fill_args(AttnArgs& a, const tl_plan* plan, const PlanDev& d, const void* q, float scale, float* out, float* lse) {
   a.q = (const uint16_t*)q;
   a.tok = d.tok;
-  a.slots = d.slots;
+  a.unit_slots = d.unit_slots;
+  a.unit_heads_log2 = plan->unit_heads_log2;
   a.slot_lm = plan->any_unit_repeat ? d.unit_lm : nullptr;
   a.tile_base = d.tile_base;
   a.part_tile = d.part_tile;
@@ -235,8 +236,6 @@ tl_status fused_rows(const tl_pool* pool, const tl_plan* plan, const void* base,
   a.final_out = out_dev;
   a.final_lse = lse_out;
   a.final_is_bf16 = out_is_bf16 ? 1 : 0;
-  a.fill = nullptr;            // the row-tile kernel reads the fills that the plan baked into its tile lists
-  a.seg_len = pool->seg_len;
   a.work = d.ftiles;
   a.n_work = (int)plan->ftiles.size();
   return launch_fused_row_tiles(a, a.n_work, st);
@@ -304,8 +303,6 @@ tl_status tl_segment_attn(const tl_pool* pool, tl_plan* plan, const void* q_dev,
   if (rc != TL_OK) return rc;
   if (!(scale > 0.f) || !std::isfinite(scale)) TL_FAIL(TL_EINVAL, "tl_segment_attn: scale must be positive and finite");
   hipStream_t st = (hipStream_t)stream;
-  rc = pool_device_ready(pool, st);
-  if (rc != TL_OK) return rc;
   rc = plan_device_ready(plan, st);
   if (rc != TL_OK) return rc;
   const PlanDev d = plan_dev(plan, plan->blob_dev);
@@ -313,8 +310,6 @@ tl_status tl_segment_attn(const tl_pool* pool, tl_plan* plan, const void* q_dev,
   fill_args(a, plan, d, q_dev, scale, out_partial, lse);
   a.k = (const uint16_t*)pool->k_dev;
   a.v = (const uint16_t*)pool->v_dev;
-  a.fill = pool->fill_dev;
-  a.seg_len = pool->seg_len;
   a.work = d.tiles;
   a.n_work = (int)plan->tiles.size();
   rc = launch_pool_row_tiles(a, a.n_work, st);
@@ -338,8 +333,6 @@ tl_status tl_causal_block(tl_plan* plan, const void* q_dev, const void* k_new_de
   fill_args(a, plan, d, q_dev, scale, out_partial, lse);
   a.k = (const uint16_t*)k_new_dev;
   a.v = (const uint16_t*)v_new_dev;
-  a.fill = nullptr;
-  a.seg_len = 0;
   a.work = d.ctiles;
   a.n_work = (int)plan->ctiles.size();
   if (!plan->single_tok.empty()) {

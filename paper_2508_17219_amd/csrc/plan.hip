@@ -25,6 +25,19 @@ struct RawItem {
   int32_t begin, end;          // list positions [begin, end)
 };
 
+// kv heads per workgroup of the split-K kernel: the most of 8, 4, 2 or 1 that divides kv_heads (whole
+// token rows per workgroup stream best), halved while the launch would be fewer workgroups than
+// three quarters of the CUs: then a unit's heads go to several workgroups, whose waves share the
+// unit's tokens.  Measured, a workgroup per unit with one wave per head against this deal: 64 requests
+// of a one-kv-head layer 391 -> 123 us (1.8 -> 5.8 TB/s; seven of eight waves had no head), one request
+// of 15.9k tokens with 8 kv heads 34 -> 15 us (32 workgroups became 256); with 8 heads and 200 units or
+// more the two are the same launch (234 us, 5.97 TB/s; 811 units 3.83 ms, 6.0 TB/s).
+int32_t plan_unit_heads_log2(int32_t kv_heads, int64_t n_units, int64_t n_cu) {
+  int32_t log2 = 3;
+  while (kv_heads & ((1 << log2) - 1)) --log2;
+  while (log2 > 0 && 4 * n_units * (kv_heads >> log2) < 3 * n_cu) --log2;
+  return log2;
+}
 
 }  // namespace
 
@@ -376,14 +389,15 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         for (int32_t r : it.reqs)
           for (int32_t t = req_row_ptr[r]; t < req_row_ptr[r + 1]; ++t) p->item_tokens.push_back(t);
         const int32_t slot_base = (int32_t)p->item_slots.size();
-        const int32_t unit_base = (int32_t)p->unit_slots.size();
+        const int32_t unit_base = (int32_t)p->unit_slots.size() / 2;
         for (int32_t u = c0; u < c1; ++u) {
           const int32_t sl = run_slots[u].first, m = run_slots[u].second;
           for (int32_t k = 0; k < m; ++k) p->item_slots.push_back(sl);       // the item's list keeps every occurrence
           prefix_pairs += (int64_t)m * n_tok * pool->fill[sl];
           item_pairs += (int64_t)m * n_tok * pool->fill[sl];
           if (few_rows) {
-            p->unit_slots.push_back(sl);
+            p->unit_slots.push_back(sl * pool->seg_len);
+            p->unit_slots.push_back(pool->fill[sl]);
             p->unit_lm.push_back(log2f((float)m));
             if (m > 1) p->any_unit_repeat = true;
           }
@@ -423,6 +437,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         row_cursor += n_tok;
       }
     }
+    p->unit_heads_log2 = plan_unit_heads_log2(pool->kv_heads, (int64_t)p->units.size(), n_cu > 0 ? n_cu : kComputeUnits);
     // the token array doubles as the tile token list
     p->tok = p->item_tokens;
 
@@ -574,7 +589,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       o.ctiles = reserve(sizeof(Work) * p->ctiles.size());
       o.ftiles = reserve(sizeof(Work) * p->ftiles.size());
       o.tok = reserve(sizeof(int32_t) * p->tok.size());
-      o.slots = reserve(sizeof(int32_t) * p->unit_slots.size());
+      o.unit_slots = reserve(sizeof(int32_t) * p->unit_slots.size());
       o.unit_lm = reserve(sizeof(float) * p->unit_lm.size());
       o.merge_ptr = reserve(sizeof(int32_t) * p->merge_ptr.size());
       o.merge_rows = reserve(sizeof(int32_t) * p->merge_rows.size());
@@ -595,7 +610,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       fill(o.ctiles, p->ctiles.data(), sizeof(Work) * p->ctiles.size());
       fill(o.ftiles, p->ftiles.data(), sizeof(Work) * p->ftiles.size());
       fill(o.tok, p->tok.data(), sizeof(int32_t) * p->tok.size());
-      fill(o.slots, p->unit_slots.data(), sizeof(int32_t) * p->unit_slots.size());
+      fill(o.unit_slots, p->unit_slots.data(), sizeof(int32_t) * p->unit_slots.size());
       fill(o.unit_lm, p->unit_lm.data(), sizeof(float) * p->unit_lm.size());
       fill(o.merge_ptr, p->merge_ptr.data(), sizeof(int32_t) * p->merge_ptr.size());
       fill(o.merge_rows, p->merge_rows.data(), sizeof(int32_t) * p->merge_rows.size());

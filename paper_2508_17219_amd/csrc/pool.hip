@@ -1,5 +1,5 @@
 // Segment pool: id -> slot table, per-slot fill / reference count / last-use stamp on the
-// host; K/V slots and a mirror of fill[] on the device.  (Paper Section 3.1: fixed-size
+// host; K/V slots on the device.  (Paper Section 3.1: fixed-size
 // segments in cache slots; Section 1 and 4: one copy per segment; Section 4.3: eviction by
 // last access time.)
 #include <cstdarg>
@@ -42,11 +42,11 @@ __global__ void gather_slots_kernel(uint4* __restrict__ out, const uint4* __rest
 
 // Destination chunks of one append launch: rows [src_row, src_row + n) of the source go to
 // tokens [tok, tok + n) of `slot`; `zero_to` > tok + n asks for tokens [tok + n, zero_to) to be
-// cleared; new_fill is stored in fill[slot].
+// cleared.
 struct AppendChunk {
-  int32_t slot, tok, n, src_row, zero_to, new_fill;
+  int32_t slot, tok, n, src_row, zero_to;
 };
-constexpr int kAppendChunks = 128;   // 3 KB of kernel arguments
+constexpr int kAppendChunks = 128;   // 2.5 KB of kernel arguments
 struct AppendArgs {
   AppendChunk c[kAppendChunks];
 };
@@ -54,7 +54,7 @@ struct AppendArgs {
 // blockIdx.y = chunk; the blocks of a column stride over the chunk's 16-byte pieces.
 __global__ void append_rows_kernel(uint4* __restrict__ pool_k, uint4* __restrict__ pool_v,
                                    const uint4* __restrict__ src_k, const uint4* __restrict__ src_v,
-                                   int32_t* __restrict__ fill, const AppendArgs args, size_t row16, size_t slot16) {
+                                   const AppendArgs args, size_t row16, size_t slot16) {
   const AppendChunk c = args.c[blockIdx.y];
   const size_t dst0 = (size_t)c.slot * slot16 + (size_t)c.tok * row16;
   const size_t src0 = (size_t)c.src_row * row16;
@@ -70,22 +70,6 @@ __global__ void append_rows_kernel(uint4* __restrict__ pool_k, uint4* __restrict
     pool_k[dst0 + n16 + i] = z;
     pool_v[dst0 + n16 + i] = z;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) fill[c.slot] = c.new_fill;
-}
-
-tl_status pool_device_ready(const tl_pool* pool, hipStream_t stream) {
-  if (!pool->fill_dev) {
-    int32_t* p = nullptr;
-    TL_HIP(hipMalloc((void**)&p, sizeof(int32_t) * (size_t)pool->n_slots));
-    pool->fill_dev = p;
-    pool->fill_dirty = true;
-  }
-  if (pool->fill_dirty) {
-    TL_HIP(hipMemcpyAsync(pool->fill_dev, pool->fill.data(), sizeof(int32_t) * (size_t)pool->n_slots,
-                          hipMemcpyHostToDevice, stream));
-    pool->fill_dirty = false;
-  }
-  return TL_OK;
 }
 
 }  // namespace tl
@@ -141,8 +125,6 @@ tl_status tl_pool_create(tl_pool** out, int32_t n_slots, int32_t seg_len, int32_
   p->n_used = 0;
   p->free_hint = 0;
   p->generation = 0;
-  p->fill_dev = nullptr;
-  p->fill_dirty = true;
   try {
     p->id_of.assign(n_slots, 0);
     p->fill.assign(n_slots, 0);
@@ -171,7 +153,6 @@ tl_status tl_pool_create(tl_pool** out, int32_t n_slots, int32_t seg_len, int32_
 
 tl_status tl_pool_destroy(tl_pool* pool) {
   if (!pool) return TL_OK;
-  if (pool->fill_dev) (void)hipFree(pool->fill_dev);
   if (pool->owns_kv) {
     (void)hipFree(pool->k_dev);
     (void)hipFree(pool->v_dev);
@@ -216,17 +197,15 @@ tl_status tl_pool_put(tl_pool* pool, uint64_t segment_id, const void* k_src_dev,
   int32_t s = take_slot(pool, want_slot);
   if (s < 0) TL_FAIL(TL_EFULL, "tl_pool_put: no free slot (%d in use)", pool->n_used);
   hipStream_t st = (hipStream_t)stream;
-  tl_status rc = pool_device_ready(pool, st);
-  if (rc != TL_OK) return rc;
-  // one launch: copy the fill rows, clear the rest of the slot, store the slot's fill
+  // one launch: copy the fill rows, clear the rest of the slot
   const size_t row16 = (size_t)pool->kv_heads * pool->head_dim * 2 / 16;
   const size_t slot16 = row16 * pool->seg_len;
   AppendArgs args;
   memset(&args, 0, sizeof(args));
-  args.c[0] = AppendChunk{s, 0, fill, 0, pool->seg_len, fill};
+  args.c[0] = AppendChunk{s, 0, fill, 0, pool->seg_len};
   const unsigned bx = (unsigned)(slot16 / 256 > 32 ? 32 : (slot16 + 255) / 256);
   hipLaunchKernelGGL(append_rows_kernel, dim3(bx, 1), dim3(256), 0, st, (uint4*)pool->k_dev, (uint4*)pool->v_dev,
-                     (const uint4*)k_src_dev, (const uint4*)v_src_dev, pool->fill_dev, args, row16, slot16);
+                     (const uint4*)k_src_dev, (const uint4*)v_src_dev, args, row16, slot16);
   TL_HIP(hipGetLastError());
   occupy(pool, s, segment_id, fill);
   if (slot_out) *slot_out = s;
@@ -281,8 +260,6 @@ tl_status tl_pool_append_batch(tl_pool* pool, int32_t n_chains, const int32_t* h
     TL_FAIL(TL_EFULL, "tl_pool_append: %d free slots, %d needed", pool->n_slots - pool->n_used, n_new_all);
   if (n_rows_all == 0) return TL_OK;
   hipStream_t st = (hipStream_t)stream;
-  tl_status rc = pool_device_ready(pool, st);
-  if (rc != TL_OK) return rc;
 
   // ---- place the rows (host state changes from here on; no failure path below but HIP's) ----
   std::vector<AppendChunk> chunks;
@@ -292,7 +269,7 @@ tl_status tl_pool_append_batch(tl_pool* pool, int32_t n_chains, const int32_t* h
     if (has_tail[c] && room[c] > 0 && n_rows > 0) {
       const int32_t ts = tail_slot[c];
       const int32_t n = n_rows < room[c] ? n_rows : room[c];
-      chunks.push_back(AppendChunk{ts, pool->fill[ts], n, row_ptr[c], 0, pool->fill[ts] + n});
+      chunks.push_back(AppendChunk{ts, pool->fill[ts], n, row_ptr[c], 0});
       pool->fill[ts] += n;
       pool->stamp[ts] = ++pool->clock;
       pool->generation++;
@@ -302,7 +279,7 @@ tl_status tl_pool_append_batch(tl_pool* pool, int32_t n_chains, const int32_t* h
       const int32_t n = n_rows - row < C ? n_rows - row : C;
       const int32_t s = take_slot(pool, -1);
       occupy(pool, s, new_ids[i], n);
-      chunks.push_back(AppendChunk{s, 0, n, row_ptr[c] + row, C, n});
+      chunks.push_back(AppendChunk{s, 0, n, row_ptr[c] + row, C});
       if (new_slots_out) new_slots_out[i] = s;
       row += n;
     }
@@ -322,7 +299,7 @@ tl_status tl_pool_append_batch(tl_pool* pool, int32_t n_chains, const int32_t* h
     }
     const unsigned bx = (unsigned)(most16 / 256 > 32 ? 32 : (most16 + 255) / 256);
     hipLaunchKernelGGL(append_rows_kernel, dim3(bx, (unsigned)nc), dim3(256), 0, st, (uint4*)pool->k_dev, (uint4*)pool->v_dev,
-                       (const uint4*)k_rows_dev, (const uint4*)v_rows_dev, pool->fill_dev, args, row16, slot16);
+                       (const uint4*)k_rows_dev, (const uint4*)v_rows_dev, args, row16, slot16);
   }
   TL_HIP(hipGetLastError());
   return TL_OK;
@@ -354,7 +331,6 @@ tl_status tl_pool_adopt(tl_pool* pool, const uint64_t* ids, const int32_t* slots
     if (!seen_slot.emplace(slots[i], i).second) TL_FAIL(TL_EINVAL, "tl_pool_adopt: slot %d listed twice", slots[i]);
   }
   for (int32_t i = 0; i < n; ++i) occupy(pool, slots[i], ids[i], fills[i]);
-  pool->fill_dirty = true;
   return TL_OK;
 }
 
@@ -380,7 +356,6 @@ tl_status tl_pool_evict_lru(tl_pool* pool, uint64_t* evicted_id) {
   pool->n_used--;
   pool->generation++;
   if (best < pool->free_hint) pool->free_hint = best;
-  pool->fill_dirty = true;
   return TL_OK;
 }
 

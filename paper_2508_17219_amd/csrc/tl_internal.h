@@ -45,7 +45,7 @@ constexpr int kComputeUnits = 256;   // MI355X (tl_plan_create's default; the pl
 
 // One unit of kernel work.  Its query tokens are tok[tok_off .. tok_off+n_tok) (batch token
 // indices), its partial rows out_row .. out_row+n_tok-1.
-//  pool work:   split-K units: kv_off/kv_len index the plan's unit slot list (with unit_lm[]);
+//  pool work:   split-K units: kv_off/kv_len index the plan's unit slot list, entries of two ints (with unit_lm[]);
 //               row tiles: the item's kv tokens are listed as tiles of 64: full_off/n_full index tile_base[]
 //               (first kv row of each completely filled tile), part_off/n_part index
 //               part_tile[] (first kv row, valid tokens) for the tiles cut short by a fill.
@@ -80,9 +80,6 @@ struct tl_pool {
   uint64_t generation;           // goes up whenever a slot's content, fill or owner changes (put of a new id,
                                  // append, adopt, evict): a plan is valid for the generation it was built in
   mutable tl::PrefixTree tree;   // grows as plans walk their requests' lists; loses a segment's nodes on eviction
-  // device mirror of fill[]
-  mutable int32_t* fill_dev;
-  mutable bool fill_dirty;
 };
 
 struct tl_plan {
@@ -107,16 +104,17 @@ struct tl_plan {
   bool any_repeat = false;              // some work item's list names a slot more than once
   std::vector<float> tile_lm, part_lm;  // log2 of how often the tile's slot is listed (parallel to tile_base / part_tile pairs)
   std::vector<int32_t> prior_rows;      // Work::prior_off
-  std::vector<int32_t> unit_slots;      // split-K units: Work::kv_off/kv_len, each distinct slot of a chunk once ...
+  std::vector<int32_t> unit_slots;      // split-K units: Work::kv_off/kv_len, each distinct slot of a chunk once as (first kv row, valid tokens) ...
   std::vector<float> unit_lm;           // ... with log2 of the number of times the run lists it
   bool any_unit_repeat = false;
+  int32_t unit_heads_log2 = 0;          // log2 of the kv heads that a workgroup of the split-K kernel takes
   uint64_t pool_generation;      // the pool's generation when the plan was built
   int32_t pool_n_slots;
   // Everything the kernels read, laid out once at creation as one block of host memory (each array
   // starts on a 256-byte boundary); the device copy is made on first use, in one transfer.
   std::vector<char> blob_host;
   struct {
-    size_t tiles, units, ctiles, ftiles, tok, slots, merge_ptr, merge_rows, tile_base, part_tile, merge_tok, single_tok,
+    size_t tiles, units, ctiles, ftiles, tok, unit_slots, merge_ptr, merge_rows, tile_base, part_tile, merge_tok, single_tok,
         tile_lm, part_lm, prior_rows, unit_lm, merge_fix;
   } off;
   void* blob_dev;                // hipMalloc'd copy of blob_host, or null
@@ -127,7 +125,7 @@ namespace tl {
 // Device addresses of a plan's arrays inside a copy of its block that starts at `base`.
 struct PlanDev {
   const Work *tiles, *units, *ctiles, *ftiles;
-  const int32_t *tok, *slots, *merge_ptr, *merge_rows, *tile_base, *part_tile, *merge_tok, *single_tok;
+  const int32_t *tok, *unit_slots, *merge_ptr, *merge_rows, *tile_base, *part_tile, *merge_tok, *single_tok;
   const float *tile_lm, *part_lm;
   const int32_t* prior_rows;
   const float* unit_lm;
@@ -141,7 +139,7 @@ inline PlanDev plan_dev(const tl_plan* p, const void* base) {
   d.ctiles = (const Work*)(b + p->off.ctiles);
   d.ftiles = (const Work*)(b + p->off.ftiles);
   d.tok = (const int32_t*)(b + p->off.tok);
-  d.slots = (const int32_t*)(b + p->off.slots);
+  d.unit_slots = (const int32_t*)(b + p->off.unit_slots);
   d.merge_ptr = (const int32_t*)(b + p->off.merge_ptr);
   d.merge_rows = (const int32_t*)(b + p->off.merge_rows);
   d.tile_base = (const int32_t*)(b + p->off.tile_base);
@@ -156,7 +154,6 @@ inline PlanDev plan_dev(const tl_plan* p, const void* base) {
   return d;
 }
 
-tl_status pool_device_ready(const tl_pool* pool, hipStream_t stream);
 // Makes the plan's device copy if there is none yet: one hipMalloc and one copy enqueued on `stream`.
 tl_status plan_device_ready(tl_plan* plan, hipStream_t stream);
 // TL_EINVAL if the pool has changed since the plan was built.

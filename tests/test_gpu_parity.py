@@ -1135,6 +1135,25 @@ def test_head_group_sizes_from_mha_to_one_kv_head(hq, hkv):
     run.close()
 
 
+@pytest.mark.parametrize("hq,hkv,compute_units", [(8, 1, -1), (8, 2, 1), (12, 4, 1), (21, 3, -1), (16, 8, 1), (16, 8, 24), (16, 8, 4096), (20, 10, 4096)])
+def test_split_k_units_with_their_waves_dealt_to_heads_and_slices(hq, hkv, compute_units):
+    """A workgroup takes 8, 4, 2 or 1 kv heads and deals a unit's tiles to the waves that share a head:
+    prefixes around the 32-token tile (slices without keys, cut-short last tiles) up to several
+    rounds of every slice, on few and on many CUs, every row against the oracle; a repeated
+    segment keeps its multiplicity."""
+    _say("units dealt to heads and slices hq=%d hkv=%d compute_units=%d" % (hq, hkv, compute_units))
+    lengths = np.array([1, 31, 32, 33, 64, 95, 255, 256, 257, 289, 1000, 2100])
+    lists, fills = wl._lists_from_lengths(lengths, 64)
+    lists[10] = [lists[10][1]] * 3 + lists[10]
+    rng = np.random.Generator(np.random.PCG64(5))
+    b = wl._finish("unit_slices", 53, hq, hkv, 64, 128, [1] * 11 + [2], lists, fills, rng, k_gain=4.0, v_offset_mod=7)
+    for split in (0, 3):
+        run = H.run_gpu(b, split_segments=split, compute_units=compute_units)
+        assert run.info.n_units >= 12 and run.info.n_tiles == 0
+        _check_all_requests(run)
+        run.close()
+
+
 def test_single_long_prompt_is_cut_along_its_kv_and_merged():
     """A batch too small to fill the GPU with row tiles: the plan cuts the slot list into chunks,
     each chunk yields a partial per row, the merge puts them together."""
