@@ -113,12 +113,21 @@ def _host(a, dtype) -> np.ndarray:
     return np.ascontiguousarray(np.asarray(a), dtype=dtype)
 
 
+_raw_stream = None      # (device index) -> handle of torch's current stream there, once torch can use a GPU
+
+
 def _stream(stream) -> Optional[int]:
+    """torch's current stream as a handle: asked of torch directly, because a `torch.cuda.Stream` object and the
+    availability check in front of it cost 4 us a call, as much as a launch."""
+    global _raw_stream
     if stream is None:
         import torch
-        if torch.cuda.is_available():
-            return torch.cuda.current_stream().cuda_stream or None
-        return None
+        if _raw_stream is None:
+            if not torch.cuda.is_available():
+                return None
+            torch.cuda.init()
+            _raw_stream = torch._C._cuda_getCurrentRawStream
+        return _raw_stream(torch._C._cuda_getDevice()) or None
     return int(stream) or None
 
 
@@ -246,35 +255,41 @@ def tl_plan_create(pool: int, q_heads: int, req_row_ptr, req_seg_ptr, seg_ids, f
 
 
 def tl_plan_destroy(plan: int):
-    _plan_shapes.pop(plan, None)
+    _plan_sizes.pop(plan, None)
     _check(load_library().tl_plan_destroy(plan))
 
 
-# (n_tokens, n_partial_rows, q_heads, kv_heads) of every live plan: the compute wrappers check the
-# tensors they are handed against it -- the C ABI sees only pointers and cannot
-_plan_shapes = {}
+# What the tensors of a compute call need at least, for every live plan: elements of (q and the output, new K or V,
+# the output's LSE, the partials, the partials' LSE).  The compute wrappers check the tensors they are handed
+# against it -- the C ABI sees only pointers and cannot.
+_plan_sizes = {}
 
 
-def _shape_of(plan: int):
-    sh = _plan_shapes.get(plan)
-    if sh is None:
+def _sizes_of(plan: int):
+    sz = _plan_sizes.get(plan)
+    if sz is None:
         i = tl_plan_get_info(plan)
-        sh = _plan_shapes[plan] = (i.n_tokens, i.n_partial_rows, i.q_heads, i.kv_heads)
-    return sh
+        T, R, hq, hkv = i.n_tokens, i.n_partial_rows, i.q_heads, i.kv_heads
+        sz = _plan_sizes[plan] = (T * hq * 128, T * hkv * 128, T * hq, R * hq * 128, R * hq)
+    return sz
 
 
-def _need(t, name: str, rows: int, heads: int, dim, kind: str):
-    """t must be a device tensor of the given element kind with at least rows x heads (x dim) elements."""
-    if t is None or rows == 0 or isinstance(t, int):
-        return
-    if not _kinds:
-        import torch
-        _kinds.update(bf16=torch.bfloat16, f32=torch.float32)
-    if t.dtype != _kinds[kind]:
-        raise TypeError("%s must be %s, is %s" % (name, kind, t.dtype))
-    n = rows * heads * (dim or 1)
-    if t.numel() < n:
-        raise ValueError("%s has %d elements, the plan needs %d" % (name, t.numel(), n))
+def _need(t, name: str, n: int, kind: str) -> Optional[int]:
+    """The address of t, a dense device tensor of the given element kind with at least n elements (or an address,
+    or None); a tensor that the plan has no rows for may be anything dense."""
+    if t is None or isinstance(t, int):
+        return t
+    if n:
+        if not _kinds:
+            import torch
+            _kinds.update(bf16=torch.bfloat16, f32=torch.float32)
+        if t.dtype != _kinds[kind]:
+            raise TypeError("%s must be %s, is %s" % (name, kind, t.dtype))
+        if t.numel() < n:
+            raise ValueError("%s has %d elements, the plan needs %d" % (name, t.numel(), n))
+    if not t.is_contiguous():
+        raise ValueError("device tensor must be contiguous")
+    return t.data_ptr()
 
 
 _kinds = {}
@@ -314,48 +329,45 @@ def tl_plan_export(plan: int) -> dict:
 
 # ---- compute ----------------------------------------------------------------------------
 def tl_segment_attn(pool: int, plan: int, q, scale: float, out_partial, lse, stream=None):
-    T, R, hq, _ = _shape_of(plan)
-    _need(q, "q", T, hq, 128, "bf16"); _need(out_partial, "out_partial", R, hq, 128, "f32"); _need(lse, "lse", R, hq, None, "f32")
-    _check(load_library().tl_segment_attn(pool, plan, _dev(q), scale, _dev(out_partial), _dev(lse), _stream(stream)))
+    n_q, _, _, n_part, n_plse = _sizes_of(plan)
+    _check(load_library().tl_segment_attn(pool, plan, _need(q, "q", n_q, "bf16"), scale, _need(out_partial, "out_partial", n_part, "f32"),
+                                          _need(lse, "lse", n_plse, "f32"), _stream(stream)))
 
 
 def tl_causal_block(plan: int, q, k_new, v_new, scale: float, out_partial, lse, stream=None):
-    T, R, hq, hkv = _shape_of(plan)
-    _need(q, "q", T, hq, 128, "bf16"); _need(k_new, "k_new", T, hkv, 128, "bf16"); _need(v_new, "v_new", T, hkv, 128, "bf16")
-    _need(out_partial, "out_partial", R, hq, 128, "f32"); _need(lse, "lse", R, hq, None, "f32")
-    _check(load_library().tl_causal_block(plan, _dev(q), _dev(k_new), _dev(v_new), scale, _dev(out_partial), _dev(lse),
-                                          _stream(stream)))
+    n_q, n_kv, _, n_part, n_plse = _sizes_of(plan)
+    _check(load_library().tl_causal_block(plan, _need(q, "q", n_q, "bf16"), _need(k_new, "k_new", n_kv, "bf16"),
+                                          _need(v_new, "v_new", n_kv, "bf16"), scale, _need(out_partial, "out_partial", n_part, "f32"),
+                                          _need(lse, "lse", n_plse, "f32"), _stream(stream)))
+
+
+def _fused_args(pool, plan, q, k_new, v_new, scale, out, out_is_bf16, lse_out, stream, prior_partial, prior_lse):
+    n_q, n_kv, n_lse, n_part, n_plse = _sizes_of(plan)
+    return (pool, plan, _need(q, "q", n_q, "bf16"), _need(k_new, "k_new", n_kv, "bf16"), _need(v_new, "v_new", n_kv, "bf16"), scale,
+            _need(prior_partial, "prior_partial", n_part, "f32"), _need(prior_lse, "prior_lse", n_plse, "f32"),
+            _need(out, "out", n_q, "bf16" if out_is_bf16 else "f32"), int(bool(out_is_bf16)), _need(lse_out, "lse_out", n_lse, "f32"),
+            _stream(stream))
 
 
 def tl_fused_attn(pool: int, plan: int, q, k_new, v_new, scale: float, out, out_is_bf16: bool, lse_out=None, stream=None,
                   prior_partial=None, prior_lse=None):
     """prior_partial / prior_lse: the partial buffers tl_segment_attn wrote (needed by TL_PLAN_FUSE_TAILS plans)."""
-    T, R, hq, hkv = _shape_of(plan)
-    _need(q, "q", T, hq, 128, "bf16"); _need(k_new, "k_new", T, hkv, 128, "bf16"); _need(v_new, "v_new", T, hkv, 128, "bf16")
-    _need(out, "out", T, hq, 128, "bf16" if out_is_bf16 else "f32"); _need(lse_out, "lse_out", T, hq, None, "f32")
-    _need(prior_partial, "prior_partial", R, hq, 128, "f32"); _need(prior_lse, "prior_lse", R, hq, None, "f32")
-    _check(load_library().tl_fused_attn(pool, plan, _dev(q), _dev(k_new), _dev(v_new), scale, _dev(prior_partial),
-                                        _dev(prior_lse), _dev(out), int(bool(out_is_bf16)), _dev(lse_out), _stream(stream)))
+    _check(load_library().tl_fused_attn(*_fused_args(pool, plan, q, k_new, v_new, scale, out, out_is_bf16, lse_out, stream,
+                                                     prior_partial, prior_lse)))
 
 
 def tl_fused_attn_static(pool: int, plan: int, q, k_new, v_new, scale: float, out, out_is_bf16: bool, lse_out=None,
                          stream=None, prior_partial=None, prior_lse=None):
     """tl_fused_attn without any device allocation (the plan's work lists go to a static device buffer)."""
-    T, R, hq, hkv = _shape_of(plan)
-    _need(q, "q", T, hq, 128, "bf16"); _need(k_new, "k_new", T, hkv, 128, "bf16"); _need(v_new, "v_new", T, hkv, 128, "bf16")
-    _need(out, "out", T, hq, 128, "bf16" if out_is_bf16 else "f32"); _need(lse_out, "lse_out", T, hq, None, "f32")
-    _need(prior_partial, "prior_partial", R, hq, 128, "f32"); _need(prior_lse, "prior_lse", R, hq, None, "f32")
-    _check(load_library().tl_fused_attn_static(pool, plan, _dev(q), _dev(k_new), _dev(v_new), scale, _dev(prior_partial),
-                                               _dev(prior_lse), _dev(out), int(bool(out_is_bf16)), _dev(lse_out),
-                                               _stream(stream)))
+    _check(load_library().tl_fused_attn_static(*_fused_args(pool, plan, q, k_new, v_new, scale, out, out_is_bf16, lse_out, stream,
+                                                            prior_partial, prior_lse)))
 
 
 def tl_merge(plan: int, out_partial, lse, out, out_is_bf16: bool, lse_out=None, stream=None):
-    T, R, hq, _ = _shape_of(plan)
-    _need(out_partial, "out_partial", R, hq, 128, "f32"); _need(lse, "lse", R, hq, None, "f32")
-    _need(out, "out", T, hq, 128, "bf16" if out_is_bf16 else "f32"); _need(lse_out, "lse_out", T, hq, None, "f32")
-    _check(load_library().tl_merge(plan, _dev(out_partial), _dev(lse), _dev(out), int(bool(out_is_bf16)), _dev(lse_out),
-                                   _stream(stream)))
+    n_q, _, n_lse, n_part, n_plse = _sizes_of(plan)
+    _check(load_library().tl_merge(plan, _need(out_partial, "out_partial", n_part, "f32"), _need(lse, "lse", n_plse, "f32"),
+                                   _need(out, "out", n_q, "bf16" if out_is_bf16 else "f32"), int(bool(out_is_bf16)),
+                                   _need(lse_out, "lse_out", n_lse, "f32"), _stream(stream)))
 
 
 def tl_set_option(knob: str, value: int):

@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+
 #include "tl_internal.h"
 
 namespace tl {
@@ -49,6 +51,18 @@ struct AttnArgs {
   float scale;            // softmax scale
   float scale_log2e;      // scale * log2(e)
 };
+
+// Allows `kernel` its dynamic LDS on the current device; the runtime is asked once per kernel and device
+// (`done`, a static of the launcher: one bit per device), not at every launch.
+inline tl_status allow_lds(const void* kernel, size_t bytes, std::atomic<uint64_t>& done) {
+  int dev = 0;
+  TL_HIP(hipGetDevice(&dev));
+  const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+  if (done.load(std::memory_order_acquire) & bit) return TL_OK;
+  TL_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+  done.fetch_or(bit, std::memory_order_release);
+  return TL_OK;
+}
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 

@@ -284,15 +284,12 @@ tl_status launch_splitk_units(const AttnArgs& a, int n_work, hipStream_t st) {
   if (a.unit_heads_log2 < 0 || a.unit_heads_log2 > 3 || a.kv_heads & ((1 << a.unit_heads_log2) - 1))
     TL_FAIL(TL_EINVAL, "launch_splitk_units: %d kv heads cannot be dealt %d to a workgroup", a.kv_heads, 1 << a.unit_heads_log2);
   const dim3 grid((unsigned)n_work, (unsigned)(a.kv_heads >> a.unit_heads_log2)), block(kThreads);
-  if (get_option_vread() == 0) {
-    auto kern = splitk_unit_attn_kernel<0>;
-    TL_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
-    hipLaunchKernelGGL(kern, grid, block, kLdsBytes, st, a);
-  } else {
-    auto kern = splitk_unit_attn_kernel<1>;
-    TL_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
-    hipLaunchKernelGGL(kern, grid, block, kLdsBytes, st, a);
-  }
+  static std::atomic<uint64_t> allowed[2];
+  const bool scalar_v = get_option_vread() != 0;
+  auto kern = scalar_v ? splitk_unit_attn_kernel<1> : splitk_unit_attn_kernel<0>;
+  const tl_status rc = allow_lds((const void*)kern, kLdsBytes, allowed[scalar_v]);
+  if (rc != TL_OK) return rc;
+  hipLaunchKernelGGL(kern, grid, block, kLdsBytes, st, a);
   TL_HIP(hipGetLastError());
   return TL_OK;
 }

@@ -738,15 +738,12 @@ template <int MODE>
 tl_status launch_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) {
   if (n_work == 0) return TL_OK;
   const dim3 grid((unsigned)n_work * a.kv_heads), block(kThreads);
-  if (get_option_vread() == 0) {
-    auto kern = row_tile_attn_kernel<MODE, 0>;
-    TL_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
-    hipLaunchKernelGGL(kern, grid, block, kLdsBytes, st, a);
-  } else {
-    auto kern = row_tile_attn_kernel<MODE, 1>;
-    TL_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
-    hipLaunchKernelGGL(kern, grid, block, kLdsBytes, st, a);
-  }
+  static std::atomic<uint64_t> allowed[2];
+  const bool scalar_v = get_option_vread() != 0;
+  auto kern = scalar_v ? row_tile_attn_kernel<MODE, 1> : row_tile_attn_kernel<MODE, 0>;
+  const tl_status rc = allow_lds((const void*)kern, kLdsBytes, allowed[scalar_v]);
+  if (rc != TL_OK) return rc;
+  hipLaunchKernelGGL(kern, grid, block, kLdsBytes, st, a);
   TL_HIP(hipGetLastError());
   return TL_OK;
 }
