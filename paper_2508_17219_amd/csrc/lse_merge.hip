@@ -19,21 +19,31 @@ namespace {
 // blockIdx.x = position in the list of tokens to merge, blockIdx.y = chunk of 256 (head, channel-quad) positions; a thread owns
 // 4 consecutive channels of one head.
 //   M = max_j LSE_j;  w_j = exp(LSE_j - M);  O = sum w_j O_j / sum w_j;  LSE = M + ln sum w_j
-template <bool OUT_BF16>
+// MID false: lists of up to 7 partials, which the plan has laid out as fixed records (mfix).  MID true: lists of up
+// to 15, read through the list bounds -- three dependent loads in front, which the many workgroups of such a
+// launch hide.  Bound by HBM; the partials' loads are all in flight at once either way.
+template <bool OUT_BF16, bool MID>
 __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict__ part, const float* __restrict__ lse,
-                                                        const int32_t* __restrict__ mfix, void* __restrict__ out,
-                                                        float* __restrict__ lse_out, int q_heads) {
-  // the token's record: {token, partial rows..., -1 ...}; the same for every lane, one load
-  int32_t rec[kMergeFixInts];
+                                                        const int32_t* __restrict__ mfix, const int32_t* __restrict__ mptr,
+                                                        const int32_t* __restrict__ mrows, const int32_t* __restrict__ mtok,
+                                                        void* __restrict__ out, float* __restrict__ lse_out, int q_heads) {
+  // token, partial rows, -1 for the places behind the list's end; the same for every lane
+  constexpr int kList = (MID ? kLongMergeList : kMidMergeList) - 1;
+  int32_t rec[1 + kList];
+  if (MID) {
+    rec[0] = mtok[blockIdx.x];
+    const int b = mptr[rec[0]], n = mptr[rec[0] + 1] - b;
 #pragma unroll
-  for (int u = 0; u < kMergeFixInts; ++u) rec[u] = mfix[(size_t)blockIdx.x * kMergeFixInts + u];
+    for (int u = 0; u < kList; ++u) rec[1 + u] = u < n ? mrows[b + u] : -1;
+  } else {
+#pragma unroll
+    for (int u = 0; u <= kList; ++u) rec[u] = mfix[(size_t)blockIdx.x * kMergeFixInts + u];
+  }
   const int t = rec[0];
   const int idx = blockIdx.y * blockDim.x + threadIdx.x;
   if (idx < q_heads * 32) {
     const int hd = idx >> 5, c4 = idx & 31;
-    // LSEs and partial rows of the whole list are fetched at once, neither waiting for the other:
-    // one memory latency after the record's
-    constexpr int kList = kMergeFixInts - 1;
+    // LSEs and partial rows of the whole list are fetched at once, neither waiting for the other
     float l[kList];
     float4 v[kList];
 #pragma unroll
@@ -82,6 +92,7 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict_
 // accumulates with the same weights w_j = exp(LSE_j - M) as the kernel above, and slice 0 adds
 // the slices up in a fixed order.
 constexpr int kMergeSlices = 8;
+constexpr int64_t kMidMergePairs = 4096;    // (token, head) pairs from which lists of 8 to 15 partials are worth a launch
 template <bool OUT_BF16>
 __global__ __launch_bounds__(32 * kMergeSlices) void lse_merge_sliced_kernel(
     const float* __restrict__ part, const float* __restrict__ lse, const int32_t* __restrict__ mptr,
@@ -372,25 +383,32 @@ tl_status tl_merge(tl_plan* plan, const float* out_partial, const float* lse, vo
   if (rc != TL_OK) return rc;
   if (plan->merge_tok.empty()) return TL_OK;
   const PlanDev d = plan_dev(plan, plan->blob_dev);
-  const int n_short = plan->n_merge_short, n_long = (int)plan->merge_tok.size() - n_short;
-  if (n_short > 0) {
-    const dim3 grid((unsigned)n_short, (unsigned)((plan->q_heads * 32 + 255) / 256)), block(256);
-    if (out_is_bf16)
-      hipLaunchKernelGGL(lse_merge_kernel<true>, grid, block, 0, st, out_partial, lse, d.merge_fix, out_dev, lse_out,
-                         plan->q_heads);
-    else
-      hipLaunchKernelGGL(lse_merge_kernel<false>, grid, block, 0, st, out_partial, lse, d.merge_fix, out_dev, lse_out,
-                         plan->q_heads);
+  // Lists of 8 to 15 partials (a prompt's list cut into pieces) take a launch of the plain kernel: 9 partials for
+  // each of 512 tokens x 32 heads, 75 MB, 15 us there against 27 us from the slices.  A few such tokens beside long
+  // lists (a decode batch) go with those: below some 4096 (token, head) pairs a launch of their own costs more.
+  const int n_short = plan->n_merge_short;
+  int n_mid = plan->n_merge_mid, n_long = (int)plan->merge_tok.size() - n_short - n_mid;
+  if (n_long > 0 && (int64_t)n_mid * plan->q_heads < kMidMergePairs) {
+    n_long += n_mid;
+    n_mid = 0;
   }
+  const unsigned chunks = (unsigned)((plan->q_heads * 32 + 255) / 256);
+  auto plain = [&](auto kern, int n, const int32_t* tokens) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)n, chunks), dim3(256), 0, st, out_partial, lse, d.merge_fix, d.merge_ptr,
+                       d.merge_rows, tokens, out_dev, lse_out, plan->q_heads);
+  };
+  if (n_short > 0) plain(out_is_bf16 ? lse_merge_kernel<true, false> : lse_merge_kernel<false, false>, n_short, d.merge_tok);
+  if (n_mid > 0) plain(out_is_bf16 ? lse_merge_kernel<true, true> : lse_merge_kernel<false, true>, n_mid, d.merge_tok + n_short);
   if (n_long > 0) {
     // long merge lists (split-K): the sliced kernel, one workgroup per (token, head)
     const dim3 grid((unsigned)n_long, (unsigned)plan->q_heads), block(32 * kMergeSlices);
+    const int32_t* tokens = d.merge_tok + n_short + n_mid;
     if (out_is_bf16)
       hipLaunchKernelGGL(lse_merge_sliced_kernel<true>, grid, block, 0, st, out_partial, lse, d.merge_ptr, d.merge_rows,
-                         d.merge_tok + n_short, out_dev, lse_out, plan->q_heads);
+                         tokens, out_dev, lse_out, plan->q_heads);
     else
       hipLaunchKernelGGL(lse_merge_sliced_kernel<false>, grid, block, 0, st, out_partial, lse, d.merge_ptr, d.merge_rows,
-                         d.merge_tok + n_short, out_dev, lse_out, plan->q_heads);
+                         tokens, out_dev, lse_out, plan->q_heads);
   }
   TL_HIP(hipGetLastError());
   return TL_OK;

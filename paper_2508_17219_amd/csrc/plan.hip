@@ -514,11 +514,15 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       for (int32_t t = 0; t < T; ++t)
         if (!tok_fused[t]) p->merge_ptr[t + 1]++;
     for (int32_t t = 0; t < T; ++t) p->merge_ptr[t + 1] += p->merge_ptr[t];
-    // tokens with long lists (split-K) last: tl_merge gives them the sliced kernel
+    // tokens with longer lists (pieces of one list, split-K) last: tl_merge gives them kernels of their own
     {
-      auto is_short = [&](int32_t t) { return p->merge_ptr[t + 1] - p->merge_ptr[t] < kLongMergeList; };
-      auto mid = std::stable_partition(p->merge_tok.begin(), p->merge_tok.end(), is_short);
+      auto shorter = [&](int32_t n) {
+        return [&, n](int32_t t) { return p->merge_ptr[t + 1] - p->merge_ptr[t] < n; };
+      };
+      auto mid = std::stable_partition(p->merge_tok.begin(), p->merge_tok.end(), shorter(kMidMergeList));
+      auto end = std::stable_partition(mid, p->merge_tok.end(), shorter(kLongMergeList));
       p->n_merge_short = (int32_t)(mid - p->merge_tok.begin());
+      p->n_merge_mid = (int32_t)(end - mid);
     }
     p->merge_rows.assign(p->merge_ptr[T], 0);
     {
@@ -532,7 +536,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     }
     // the short lists once more as fixed records, so that the merge kernel gets a token's whole list with
     // one load instead of three dependent ones
-    static_assert(kLongMergeList <= kMergeFixInts, "a short list and its token fit one record");
+    static_assert(kMidMergeList <= kMergeFixInts, "a short list and its token fit one record");
     p->merge_fix.assign((size_t)p->n_merge_short * kMergeFixInts, -1);
     for (int32_t i = 0; i < p->n_merge_short; ++i) {
       const int32_t t = p->merge_tok[i];

@@ -33,7 +33,8 @@ constexpr int kHeadDim = 128;
 constexpr int kKvTile = 64;      // kv tokens per LDS tile of the row-tile kernel
 constexpr int kTreeNodesPerSlot = 16;   // the pool's prefix tree is cleared when it outgrows this many nodes per slot
 constexpr int kMergeFixInts = 8;   // ints of a short merge list's fixed record: the token, then up to 7 partial rows
-constexpr int kLongMergeList = 8;  // partials per token from which the merge deals the list to slices
+constexpr int kMidMergeList = 8;   // partials per token from which a list has no fixed record
+constexpr int kLongMergeList = 16; // partials per token from which the merge deals the list to slices
 constexpr int kRowTile = 256;    // query rows (token x head-in-group) per workgroup
 constexpr int kUnitRows = 16;    // max rows per kv head of a split-K unit
 // A request is planned for the one-pass kernel from this many query rows per kv head: it then
@@ -91,8 +92,9 @@ struct tl_plan {
   std::vector<tl::Work> tiles, units, ctiles, ftiles;   // ftiles: fused rows (pool tiles + causal block in one pass)
   std::vector<int32_t> merge_fix;  // the short lists again, one fixed record of 8 ints per token: {token, rows..., -1 padding}
   std::vector<int32_t> merge_tok;  // tokens that tl_merge writes (all but the fused ones): n_merge_short with short
-                                   // lists first, then those with kLongMergeList or more partials
-  int32_t n_merge_short = 0;
+                                   // lists first, then n_merge_mid with kMidMergeList or more partials, then
+                                   // those with kLongMergeList or more
+  int32_t n_merge_short = 0, n_merge_mid = 0;
   std::vector<int32_t> single_tok; // the new token of every request that has exactly one (not fused): self block = one key
   // the part of the pool's prefix tree that this batch walked, nodes in order of first visit (a node's
   // parent comes before it): what tl_plan_hot_slots searches, from the root side, without the pool

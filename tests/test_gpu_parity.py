@@ -1254,6 +1254,27 @@ def test_random_batches_with_peaked_scores_and_offset_values():
             run.close()
 
 
+@pytest.mark.parametrize("segs,q_heads,out_bf16", [
+    ([6, 7, 14], 8, False),                          # lists of 7, 8 and 15 partials: fixed records, plain kernel; no long list
+    ([6, 7, 14], 8, True),
+    ([6, 7, 14, 15, 16], 8, True),                   # a few lists of 8 and 15 beside long ones go with those
+    ([7] * 60 + [14] * 6 + [15, 3], 64, False),      # 66 tokens x 64 heads of 8 and 15 beside long ones: a launch of their own
+])
+def test_merge_lists_at_the_edges_of_their_kernels(segs, q_heads, out_bf16):
+    """Decode tokens with one partial per segment and one for themselves: every row against the oracle."""
+    _say("merge lists %s" % (sorted(set(segs)),))
+    n, total = len(segs), sum(segs)
+    rng = np.random.default_rng(17)
+    b = wl.Batch(name="merge_lists", seed=31, q_heads=q_heads, kv_heads=q_heads // 4, seg_len=64, n_slots=total,
+                 req_row_ptr=np.arange(n + 1, dtype=np.int32), req_seg_ptr=np.concatenate([[0], np.cumsum(segs)]).astype(np.int32),
+                 seg_ids=np.arange(total, dtype=np.uint64), pool_ids=np.arange(total, dtype=np.uint64),
+                 pool_slots=rng.permutation(total).astype(np.int32), pool_fills=rng.integers(1, 65, size=total).astype(np.int32))
+    run = H.run_gpu(b, split_segments=1, out_bf16=out_bf16)
+    assert run.info.n_merge_entries == total + n
+    _check_all_requests(run)
+    run.close()
+
+
 # ---- the step as a HIP graph ----------------------------------------------------------------------
 @pytest.mark.parametrize("fuse", [False, True])
 def test_step_replays_from_a_hip_graph(fuse):
