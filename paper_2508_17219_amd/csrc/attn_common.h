@@ -47,6 +47,8 @@ struct AttnArgs {
   float* out;             // [rows, q_heads, 128]
   float* lse;             // [rows, q_heads]
   int32_t q_heads, kv_heads, group, n_work;   // group = q_heads / kv_heads
+  const Work* units;      // row tiles and split-K units in one launch: the units (work: the row tiles)
+  int32_t n_units;
   int32_t unit_heads_log2;  // split-K units: log2 of the kv heads per workgroup
   float scale;            // softmax scale
   float scale_log2e;      // scale * log2(e)

@@ -12,6 +12,7 @@ namespace tl {
 tl_status launch_pool_row_tiles(const AttnArgs& a, int n_work, hipStream_t st);
 tl_status launch_causal_row_tiles(const AttnArgs& a, int n_work, hipStream_t st);
 tl_status launch_splitk_units(const AttnArgs& a, int n_work, hipStream_t st);
+tl_status launch_tiles_and_units(const AttnArgs& a, hipStream_t st);
 tl_status launch_fused_row_tiles(const AttnArgs& a, int n_work, hipStream_t st);
 
 namespace {
@@ -208,6 +209,8 @@ void fill_args(AttnArgs& a, const tl_plan* plan, const PlanDev& d, const void* q
   a.part_tile = d.part_tile;
   a.tile_lm = plan->any_repeat ? d.tile_lm : nullptr;   // null: every tile has multiplicity 1
   a.part_lm = plan->any_repeat ? d.part_lm : nullptr;
+  a.units = nullptr;
+  a.n_units = 0;
   a.out = out;
   a.lse = lse;
   a.q_heads = plan->q_heads;
@@ -323,10 +326,14 @@ tl_status tl_segment_attn(const tl_pool* pool, tl_plan* plan, const void* q_dev,
   a.v = (const uint16_t*)pool->v_dev;
   a.work = d.tiles;
   a.n_work = (int)plan->tiles.size();
+  a.units = d.units;
+  a.n_units = (int)plan->units.size();
+  // (a grid beyond 2^30 blocks would not fit the joint launch's block numbers)
+  if (a.n_work > 0 && a.n_units > 0 && ((int64_t)a.n_work + a.n_units) * a.kv_heads < (1 << 30)) return launch_tiles_and_units(a, st);
   rc = launch_pool_row_tiles(a, a.n_work, st);
   if (rc != TL_OK) return rc;
   a.work = d.units;
-  a.n_work = (int)plan->units.size();
+  a.n_work = a.n_units;
   return launch_splitk_units(a, a.n_work, st);
 }
 

@@ -51,6 +51,7 @@
 #include <type_traits>
 
 #include "attn_common.h"
+#include "splitk_unit.h"
 
 namespace tl {
 
@@ -123,16 +124,15 @@ __device__ __forceinline__ float max16(const f32x16& s) {
 // new tokens up to its own rows -- and writes the final, normalised output: such rows have one
 // partial, so they need no merge.
 template <int MODE, int VREAD>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void row_tile_attn_kernel(const AttnArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+__device__ __forceinline__ void row_tile(const AttnArgs& a, const int block, uint16_t* lds) {
   uint16_t* lds_k = lds;                 // [kBufs][64][kKS]
   uint16_t* lds_v = lds + kBufs * kKTile;    // [kBufs][64][kVS]
   int32_t* lds_idx = (int32_t*)(lds + kBufs * (kKTile + kVTile));   // [kIdxRing]
   float* lds_lm = (float*)(lds_idx + kIdxRing);   // [kIdxRing] log2(multiplicity) of the same tiles
   int32_t* lds_flag = lds_idx + 2 * kIdxRing;
 
-  const int g = blockIdx.x % a.kv_heads;
-  const Work wk = a.work[blockIdx.x / a.kv_heads];
+  const int g = block % a.kv_heads;
+  const Work wk = a.work[block / a.kv_heads];
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int G = a.group;
@@ -734,6 +734,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   }
 }
 
+template <int MODE, int VREAD>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void row_tile_attn_kernel(const AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  row_tile<MODE, VREAD>(a, blockIdx.x, lds);
+}
+
+// Row tiles of the pool and split-K units in one launch: units first, which are bound by HBM and by their own
+// chain, then row tiles, which find the CUs that the units leave and finish evenly on all of them.  The first
+// row tile's block is a multiple of eight, so that a kv head stays on its XCD.  One launch after the other, the
+// first leaves CUs idle at its end and HBM idles through the row tiles: 5 chunks of up to 941 tokens beside 67 decoded
+// ones 407 us a step, together 372; 3 chunks of 64 to 438 beside 12, 266 and 239 us.  (Groups of eight blocks of each
+// kind in turn: a unit takes a whole round whatever runs beside it, so the units' second round ends late, 574 us
+// where units first are 510.)
+__host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) {
+  return ((unsigned)a.n_units * (unsigned)(a.kv_heads >> a.unit_heads_log2) + 7u) & ~7u;
+}
+template <int VREAD>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void tiles_and_units_attn_kernel(const AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  const unsigned n_unit_blocks = unit_blocks(a);
+  if (blockIdx.x >= n_unit_blocks) {
+    row_tile<0, VREAD>(a, blockIdx.x - n_unit_blocks, lds);
+  } else if (blockIdx.x < (unsigned)a.n_units * (unsigned)(a.kv_heads >> a.unit_heads_log2)) {
+    unit::splitk_unit<VREAD>(a, a.units[blockIdx.x % a.n_units], blockIdx.x / a.n_units, lds);
+  }
+}
+static_assert(kThreads == unit::kThreads, "one block size for both kinds");
+
 template <int MODE>
 tl_status launch_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) {
   if (n_work == 0) return TL_OK;
@@ -751,6 +779,20 @@ tl_status launch_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) {
 }  // namespace
 
 tl_status launch_pool_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) { return launch_row_tiles<0>(a, n_work, st); }
+tl_status launch_tiles_and_units(const AttnArgs& a, hipStream_t st) {
+  if (a.unit_heads_log2 < 0 || a.unit_heads_log2 > 3 || a.kv_heads & ((1 << a.unit_heads_log2) - 1))
+    TL_FAIL(TL_EINVAL, "launch_tiles_and_units: %d kv heads cannot be dealt %d to a workgroup", a.kv_heads, 1 << a.unit_heads_log2);
+  const dim3 grid(unit_blocks(a) + (unsigned)a.n_work * a.kv_heads), block(kThreads);
+  static std::atomic<uint64_t> allowed[2];
+  const bool scalar_v = get_option_vread() != 0;
+  auto kern = scalar_v ? tiles_and_units_attn_kernel<1> : tiles_and_units_attn_kernel<0>;
+  constexpr size_t lds_bytes = kLdsBytes > unit::kLdsBytes ? kLdsBytes : unit::kLdsBytes;
+  const tl_status rc = allow_lds((const void*)kern, lds_bytes, allowed[scalar_v]);
+  if (rc != TL_OK) return rc;
+  hipLaunchKernelGGL(kern, grid, block, lds_bytes, st, a);
+  TL_HIP(hipGetLastError());
+  return TL_OK;
+}
 tl_status launch_causal_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) { return launch_row_tiles<1>(a, n_work, st); }
 tl_status launch_fused_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) { return launch_row_tiles<2>(a, n_work, st); }
 
