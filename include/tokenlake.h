@@ -206,7 +206,10 @@ enum {
                              another request of the batch, or at least 512 such rows -- except,
                              in a batch of fewer row-tile workgroups than the GPU has CUs, those
                              whose lists are long enough (> 2048 tokens) to be cut along the
-                             KV instead.  Such rows have a single partial, so nothing is
+                             KV instead, and except, in a batch that also has requests of at
+                             most 16 rows (decode) with a list, where cutting the lists and
+                             sharing a launch with those is estimated to be faster by a tenth
+                             or more (lists of uneven lengths).  Such rows have a single partial, so nothing is
                              written to out_partial for them and tl_segment_attn /
                              tl_causal_block / tl_merge skip them.  Needs TL_PLAN_SELF_BLOCK. */
   TL_PLAN_FUSE_TAILS = 16 /* every request with more than 16 query rows per kv head (that

@@ -9,6 +9,7 @@
 // split-K chunks.
 #include <algorithm>
 #include <cstring>
+#include <functional>
 #include <new>
 #include <queue>
 #include <unordered_set>
@@ -37,6 +38,48 @@ int32_t plan_unit_heads_log2(int32_t kv_heads, int64_t n_units, int64_t n_cu) {
   while (kv_heads & ((1 << log2) - 1)) --log2;
   while (log2 > 0 && 4 * n_units * (kv_heads >> log2) < 3 * n_cu) --log2;
   return log2;
+}
+
+// What the row tiles of a batch cost, in KV tiles of a workgroup (1.5 us): a workgroup's start, first
+// loads and epilogue, and a step's causal launch and merge where the one-pass kernel needs neither.
+constexpr int64_t kTileStart = 5, kThreeStepLaunches = 10;
+constexpr double kBytesPerTile = 7.8e6;      // what HBM moves in the time of one KV tile (5.2 TB/s)
+
+struct RowWork {
+  int64_t kv_tiles, row_tiles;
+};
+
+// KV tiles until the last of `lanes` CUs is done when they take `work` (kv_tiles + kTileStart for each row
+// tile) longest first; with many more row tiles than CUs, which leave no gaps, the mean.
+int64_t makespan(std::vector<RowWork> work, int64_t lanes) {
+  int64_t total = 0, longest = 0, n = 0;
+  for (const RowWork& w : work) {
+    total += (w.kv_tiles + kTileStart) * w.row_tiles;
+    longest = std::max(longest, w.kv_tiles + kTileStart);
+    n += w.row_tiles;
+  }
+  if (n > 16 * lanes) return std::max(longest, total / lanes);
+  std::sort(work.begin(), work.end(), [](const RowWork& a, const RowWork& b) { return a.kv_tiles > b.kv_tiles; });
+  std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> busy;
+  int64_t end = 0;
+  for (const RowWork& w : work)
+    for (int64_t i = 0; i < w.row_tiles; ++i) {
+      int64_t at = 0;
+      if ((int64_t)busy.size() >= lanes) {
+        at = busy.top();
+        busy.pop();
+      }
+      busy.push(at + w.kv_tiles + kTileStart);
+      end = std::max(end, at + w.kv_tiles + kTileStart);
+    }
+  return end;
+}
+
+// Pieces that a list of `kv_tiles` is cut into where the mean load of a CU is `mean`: pieces of at most half the
+// mean let a launch end evenly; shorter ones (never under 2048 tokens) would only add partials to merge.
+int64_t pieces_of(int64_t kv_tiles, int64_t mean) {
+  const int64_t longest = std::max<int64_t>(2048 / kKvTile, mean / 2);
+  return std::max<int64_t>(1, (kv_tiles + longest - 1) / longest);
 }
 
 }  // namespace
@@ -109,6 +152,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     const int64_t n_cu = compute_units < 0 ? kComputeUnits : compute_units;
     const int32_t min_chunk_slots = std::max(1, 2048 / pool->seg_len);
     std::vector<char> fused(n_req, 0);
+    std::vector<char> alone(n_req, 0);             // on the three steps, but in no run shared with others
     // A one-pass row tile cannot be cut along its KV: when the whole batch is fewer row-tile
     // workgroups than the GPU has CUs (one long prompt, say), requests whose slot lists are long
     // enough to be cut (see below) stay on the three-step path
@@ -139,6 +183,62 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         for (int32_t pos = 0; pos < len_of(r) && !shares; ++pos) shares = users[slot_at(r, pos)] > 1;
         fused[r] = rows >= kFuseRows || !shares;
       }
+      // In a batch that also has split-K units (one that is all one-pass rows stays so: its caller may make the
+      // one-pass call alone): one-pass rows whose lists differ much in length leave CUs idle behind the longest, which cannot be
+      // cut; and they run after the batch's split-K units, in a launch of their own.  On the three steps long
+      // lists are cut, and row tiles and units share a launch, in which the units cost the CUs they need to
+      // saturate HBM (about three fifths of them) rather than all.  The cheaper of the two by this estimate, the
+      // one-pass rows unless the three steps are a tenth cheaper.  (4 prefill chunks of 300 to 600 tokens on
+      // 1.5k to 15k beside 48 decoded tokens: 582 us as one-pass rows, 541 us in three steps; of random mixes
+      // 8 chunks of 64 to 124 beside 67 decoded tokens on 2.9k to 23k 1061 and 833 us, 4 chunks of up to 231 beside
+      // 79 of a 28-on-4-head layer 975 and 577 us; 16 chunks of 512 on 8k to 32k stay one-pass.)
+      if (n_cu > 0 && !(flags & TL_PLAN_FUSE_TAILS)) {
+        const int64_t lanes = std::max<int64_t>(1, n_cu / pool->kv_heads);
+        std::vector<RowWork> one_pass, causal, pool_part;
+        int64_t n_fused = 0, load = 0;
+        for (int32_t r = 0; r < n_req; ++r) {
+          if (!fused[r]) continue;
+          int64_t kv = 0;
+          for (int32_t pos = 0; pos < len_of(r); ++pos) kv += (pool->fill[slot_at(r, pos)] + kKvTile - 1) / kKvTile;
+          const int64_t n_row = (ntok_of(r) + tok_tile - 1) / tok_tile;
+          ++n_fused;
+          load += kv * n_row;
+          for (int64_t i = 0; i < n_row; ++i) {
+            const int64_t self = (std::min<int64_t>((i + 1) * tok_tile, ntok_of(r)) + kKvTile - 1) / kKvTile;
+            one_pass.push_back(RowWork{kv + self, 1});
+            causal.push_back(RowWork{self, 1});
+          }
+          if (kv > 0) pool_part.push_back(RowWork{kv, n_row});
+        }
+        if (n_fused > 0 && !pool_part.empty()) {
+          int64_t unit_tokens = 0;          // of the split-K units, each slot once
+          for (int32_t r = 0; r < n_req; ++r)
+            if (ntok_of(r) > 0 && (int64_t)ntok_of(r) * G <= kUnitRows)
+              for (int32_t pos = 0; pos < len_of(r); ++pos)
+                if (int32_t& u = users[slot_at(r, pos)]; u > 0) {
+                  unit_tokens += pool->fill[slot_at(r, pos)];
+                  u = 0;
+                }
+          const double units = (double)unit_tokens * pool->kv_heads * (4 * kHeadDim) / kBytesPerTile;
+          double partial_rows = 0;
+          const int64_t mean = load / lanes;
+          for (RowWork& w : pool_part) {
+            const int64_t n = pieces_of(w.kv_tiles, mean);
+            partial_rows += (double)(n + 1) * w.row_tiles * kRowTile;
+            w.kv_tiles = (w.kv_tiles + n - 1) / n;
+            w.row_tiles *= n;
+          }
+          const double merge = partial_rows * pool->kv_heads * (2 * 4 * kHeadDim) / kBytesPerTile;     // written and read
+          const double as_one_pass = makespan(one_pass, lanes) + units;
+          const double as_three = makespan(pool_part, lanes) + 0.6 * units + makespan(causal, lanes) + merge + kThreeStepLaunches;
+          if (unit_tokens > 0 && as_three < 0.9 * as_one_pass)
+            for (int32_t r = 0; r < n_req; ++r)
+              if (fused[r] && len_of(r) > 0) {
+                fused[r] = 0;
+                alone[r] = 1;
+              }
+        }
+      }
     }
     // ---- walk the prefix tree ---------------------------------------------------------------------
     // every request with a list, in order, front to back; `grouped` requests are those the planner
@@ -149,7 +249,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     if ((int64_t)tree.size() > (int64_t)kTreeNodesPerSlot * pool->n_slots) tree.reset(pool->n_slots);
     tree.begin_batch();
     std::vector<int32_t> path(n_entries);          // tree node of every list entry
-    auto is_live = [&](int32_t r) { return ntok_of(r) > 0 && len_of(r) > 0 && !fused[r]; };
+    auto is_live = [&](int32_t r) { return ntok_of(r) > 0 && len_of(r) > 0 && !fused[r] && !alone[r]; };
     for (int32_t r = 0; r < n_req; ++r) {
       const bool grouped = is_live(r);
       int32_t node = 0;
@@ -223,6 +323,10 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
           if (it >= 0) raw[it].reqs.push_back(r);
         }
     }
+
+    // (their rows are many enough: sharing a run would cut their lists at every fork and add partials)
+    for (int32_t r = 0; r < n_req; ++r)
+      if (alone[r]) raw.push_back(RawItem{{r}, r, 0, len_of(r)});
 
     // The kv tokens of a slot list as tiles of kKvTile rows.  A slot listed several times (lists are
     // multisets: Section 3.1 has no order or uniqueness among the segments a request attends to) is
@@ -334,19 +438,45 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     // Row-tile items of a small batch: when all row tiles together are fewer workgroups than the
     // GPU has CUs, long slot lists are cut into chunks (each a work item with partial rows of its
     // own, merged like any other) until there are about two workgroups per CU; a chunk keeps at
-    // least 2048 tokens so that its start-up stays small against its work.
+    // least 2048 tokens so that its start-up stays small against its work.  With more row tiles than that,
+    // lists longer than half the mean load of a CU are cut if that ends the launch earlier by more than the
+    // partials cost (lists of unequal length, or a little more than a whole number of rounds).
     int tile_chunks = 1;
+    int64_t longest_piece = 0;           // in KV tiles; 0: not cut
     {
-      int64_t wgs = 0;
+      int64_t wgs = 0, load = 0;
+      double cut_rows = 0;
+      std::vector<RowWork> whole, cut;
       for (size_t i = 0; i < raw.size(); ++i) {
         const RawItem& it = raw[i];
         if (is_tail_item[i]) continue;
         int64_t n_tok = 0;
         for (int32_t r : it.reqs) n_tok += ntok_of(r);
-        if (!unit_item(it, n_tok)) wgs += ((n_tok + tok_tile - 1) / tok_tile) * pool->kv_heads;
+        if (unit_item(it, n_tok)) continue;
+        const int64_t n_row = (n_tok + tok_tile - 1) / tok_tile;
+        wgs += n_row * pool->kv_heads;
+        whole.push_back(RowWork{((int64_t)(it.end - it.begin) * pool->seg_len + kKvTile - 1) / kKvTile, n_row});
+        load += whole.back().kv_tiles * n_row;
       }
       if (wgs > 0 && wgs < n_cu) tile_chunks = (int)std::min<int64_t>(16, (2 * n_cu + wgs - 1) / wgs);
+      if (n_cu > 0 && wgs >= n_cu) {
+        const int64_t lanes = std::max<int64_t>(1, n_cu / pool->kv_heads), mean = load / lanes;
+        for (const RowWork& w : whole) {
+          const int64_t n = pieces_of(w.kv_tiles, mean);
+          cut_rows += (double)(n - 1) * w.row_tiles * kRowTile;
+          cut.push_back(RowWork{(w.kv_tiles + n - 1) / n, w.row_tiles * n});
+        }
+        const double merge = cut_rows * pool->kv_heads * (2 * 4 * kHeadDim) / kBytesPerTile;
+        if (cut_rows > 0 && 1.05 * makespan(cut, lanes) + merge < makespan(whole, lanes))
+          longest_piece = std::max<int64_t>(2048 / kKvTile, mean / 2);
+      }
     }
+    auto even_step = [&](int32_t run) -> int32_t {       // slots per piece of a run of that many
+      if (longest_piece == 0) return run;
+      const int64_t tiles = ((int64_t)run * pool->seg_len + kKvTile - 1) / kKvTile;
+      const int64_t n = (tiles + longest_piece - 1) / longest_piece;
+      return (int32_t)((run + n - 1) / std::max<int64_t>(1, n));
+    };
     int32_t row_cursor = 0;
     p->item_tok_ptr.push_back(0);
     p->item_slot_ptr.push_back(0);
@@ -382,7 +512,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       const int32_t run = (int32_t)run_slots.size();
       const int32_t step = few_rows ? split
                            : tile_chunks > 1 ? std::max(min_chunk_slots, (run + tile_chunks - 1) / tile_chunks)
-                                             : run;
+                                             : even_step(run);
       for (int32_t c0 = 0; c0 < run; c0 += step) {
         const int32_t c1 = std::min(run, c0 + step);
         const int32_t tok_base = (int32_t)p->item_tokens.size();

@@ -316,6 +316,37 @@ def test_small_batch_of_row_tiles_is_cut_along_its_kv():
     B.tl_pool_destroy(plan_pool[0])
 
 
+@pytest.mark.parametrize("heads", [(32, 8, 5), (8, 1, 16)])
+def test_uneven_chunks_beside_decode_leave_the_one_pass_kernel(heads):
+    """Prefill chunks on prefixes of very different lengths beside decoded tokens: the longest list would
+    keep its CUs busy long after the others, so the chunks go to the three steps, uncut by what they share
+    and in pieces of their own.  The same chunks without decode, on even prefixes, or with the CU count
+    switched off stay one-pass rows."""
+    hq, hkv, n_chunk = heads
+
+    def plan_of(lo, hi, n_decode, compute_units=-1):
+        b = wl.prefill(seed=5, n_req=n_chunk + n_decode, new_tokens=600, lo=lo, hi=hi, seg_len=256, n_slots=8192, n_shared=3, hq=hq, hkv=hkv)
+        lens = [600] * (n_chunk) + [1] * n_decode
+        b.req_row_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        plan_pool[0] = _pool_for(b)
+        flags = B.TL_PLAN_SELF_BLOCK | B.TL_PLAN_FUSE_ROWS
+        plan = B.tl_plan_create(plan_pool[0], b.q_heads, b.req_row_ptr, b.req_seg_ptr, b.seg_ids, flags, 0, compute_units)
+        info = B.tl_plan_get_info(plan)
+        _check_plan_covers(b, plan, flags, fused_req=tuple(range(n_chunk)) if info.n_fused_tokens else ())
+        ex = B.tl_plan_export(plan)
+        pieces = np.diff(ex["item_slot_ptr"])[np.diff(ex["item_tok_ptr"]) == 600]
+        B.tl_plan_destroy(plan)
+        B.tl_pool_destroy(plan_pool[0])
+        return info, pieces
+
+    info, pieces = plan_of(900, 30000, 40)
+    assert info.n_fused_tokens == 0 and info.n_tiles > 0 and info.n_units > 0
+    assert len(pieces) > n_chunk                                # some list was cut
+    assert plan_of(900, 30000, 0)[0].n_fused_tokens == 600 * n_chunk
+    assert plan_of(900, 1000, 1)[0].n_fused_tokens == 600 * n_chunk
+    assert plan_of(900, 30000, 40, 0)[0].n_fused_tokens == 600 * n_chunk
+
+
 def test_one_pass_tails_keep_shared_runs_as_work_items():
     """TL_PLAN_FUSE_TAILS: the shared system prompt stays one work item read once for every session's
     rows; each session's private history and its new tokens are one-pass rows that merge the session's

@@ -1254,6 +1254,36 @@ def test_random_batches_with_peaked_scores_and_offset_values():
             run.close()
 
 
+@pytest.mark.parametrize("q_heads,kv_heads,n_decode,vread", [(8, 1, 1, 0), (8, 2, 9, 0), (28, 4, 3, 0), (64, 8, 8, 0), (16, 16, 5, 0), (8, 2, 3, 1)])
+def test_row_tiles_and_units_in_one_launch(q_heads, kv_heads, n_decode, vread):
+    """Prefill chunks on the three steps and decode tokens share the launch of tl_segment_attn: unit counts
+    that are and are not multiples of eight (where the row tiles' blocks begin), every way the units' heads
+    are dealt, both LDS read variants; every decode row and sampled chunk rows against the oracle."""
+    _say("row tiles and units %d/%d %d vread=%d" % (q_heads, kv_heads, n_decode, vread))
+    b = wl.prefill(seed=77, n_req=2 + n_decode, new_tokens=130, lo=200, hi=2900, seg_len=128, n_slots=512, n_shared=1, hq=q_heads, hkv=kv_heads)
+    b.req_row_ptr = np.concatenate([[0], np.cumsum([130, 70] + [1] * n_decode)]).astype(np.int32)
+    B.tl_set_option("vread", vread)
+    try:
+        for compute_units in (-1, 0):
+            run = H.run_gpu(b, compute_units=compute_units)
+            assert run.info.n_tiles > 0 and run.info.n_units > 0
+            _check_all_requests(run, rows_per_req=24, seed=3)
+            run.close()
+    finally:
+        B.tl_set_option("vread", 0)
+
+
+def test_uneven_chunks_beside_decode_against_the_oracle():
+    """The batch of uneven chunks and decoded tokens that the plan takes off the one-pass kernel."""
+    _say("uneven chunks beside decode")
+    b = wl.prefill(seed=5, n_req=45, new_tokens=600, lo=900, hi=30000, seg_len=256, n_slots=8192, n_shared=3, hq=32, hkv=8)
+    b.req_row_ptr = np.concatenate([[0], np.cumsum([600] * 5 + [1] * 40)]).astype(np.int32)
+    run = H.run_gpu(b, fuse=True, compute_units=256)
+    assert run.info.n_fused_tokens == 0 and run.info.n_tiles > 0 and run.info.n_units > 0
+    _check_all_requests(run, rows_per_req=6, seed=4, reqs=range(10))
+    run.close()
+
+
 @pytest.mark.parametrize("segs,q_heads,out_bf16", [
     ([6, 7, 14], 8, False),                          # lists of 7, 8 and 15 partials: fixed records, plain kernel; no long list
     ([6, 7, 14], 8, True),
