@@ -338,8 +338,8 @@ tl_status tl_fused_attn(const tl_pool* pool, tl_plan* plan, const void* q_dev, c
  * device code (4 MiB per GPU, held until the process ends).  The call makes no hipMalloc, hipFree
  * or other allocating call: it looks up the buffer's address (once per device, on the first call
  * with that device current), enqueues one host-to-device copy of the work lists and the kernel on
- * `stream`.  TL_EINVAL if the plan's work lists exceed 4 MiB (the named workloads take 20-400 KB)
- * or the device index is 64 or more.  All calls on one GPU share the buffer, which keeps the last
+ * `stream`.  TL_EINVAL if the work lists of the one-pass rows, with the tile lists of the plan's row-tile
+ * items, exceed 4 MiB (the named workloads take 20-400 KB) or the device index is 64 or more.  All calls on one GPU share the buffer, which keeps the last
  * call's contents: calls on one stream are ordered and safe; calls that overlap on one GPU (two
  * streams, two threads) race and must be serialised by the caller. */
 tl_status tl_fused_attn_static(const tl_pool* pool, tl_plan* plan, const void* q_dev, const void* k_new_dev,

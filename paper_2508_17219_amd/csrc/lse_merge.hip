@@ -296,16 +296,16 @@ tl_status tl_fused_attn_static(const tl_pool* pool, tl_plan* plan, const void* q
   if (plan->ftiles.empty()) return TL_OK;
   if (!plan->prior_rows.empty() && (!prior_partial || !prior_lse))
     TL_FAIL(TL_EINVAL, "tl_fused_attn_static: the plan has one-pass tails: the partials of tl_segment_attn are needed");
-  if (plan->blob_host.size() > kStaticScratchBytes)
+  if (plan->one_pass_bytes > kStaticScratchBytes)
     TL_FAIL(TL_EINVAL, "tl_fused_attn_static: the plan's work lists take %zu bytes, the static buffer holds %zu",
-            plan->blob_host.size(), kStaticScratchBytes);
+            plan->one_pass_bytes, kStaticScratchBytes);
   void* base = nullptr;
   rc = static_scratch(&base);
   if (rc != TL_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   // the buffer keeps the last call's lists: this call's are copied over them, in stream order
   // (nothing in the buffer has to start at zero)
-  TL_HIP(hipMemcpyAsync(base, plan->blob_host.data(), plan->blob_host.size(), hipMemcpyHostToDevice, st));
+  TL_HIP(hipMemcpyAsync(base, plan->blob_host.data(), plan->one_pass_bytes, hipMemcpyHostToDevice, st));
   return fused_rows(pool, plan, base, q_dev, k_new_dev, v_new_dev, scale, prior_partial, prior_lse, out_dev, out_is_bf16, lse_out, st);
 }
 

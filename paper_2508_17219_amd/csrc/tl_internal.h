@@ -100,7 +100,8 @@ struct tl_plan {
   // parent comes before it): what tl_plan_hot_slots searches, from the root side, without the pool
   std::vector<int32_t> bt_slot, bt_first_child, bt_next_sib, bt_roots;
   std::vector<int64_t> bt_load;
-  std::vector<int32_t> tok;      // token index array referenced by Work::tok_off
+  std::vector<int32_t> tok;      // token index array referenced by Work::tok_off: with a self block every token in
+                                 // order first, then the items' tokens
   std::vector<int32_t> tile_base;  // Work::full_off
   std::vector<int32_t> part_tile;  // Work::part_off, pairs (first kv row, valid tokens)
   bool any_repeat = false;              // some work item's list names a slot more than once
@@ -119,6 +120,7 @@ struct tl_plan {
     size_t tiles, units, ctiles, ftiles, tok, unit_slots, merge_ptr, merge_rows, tile_base, part_tile, merge_tok, single_tok,
         tile_lm, part_lm, prior_rows, unit_lm, merge_fix;
   } off;
+  size_t one_pass_bytes = 0;     // length of the block's head that the one-pass kernel reads
   void* blob_dev;                // hipMalloc'd copy of blob_host, or null
 };
 

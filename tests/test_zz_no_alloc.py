@@ -45,6 +45,30 @@ def test_static_buffer_variant_equals_fused_attn_on_two_calls_in_a_row():
         run.close()
 
 
+@pytest.mark.gpu
+def test_static_buffer_variant_beside_a_large_decode_batch():
+    """Only what the one-pass kernel reads has to fit the static buffer: 100 decode requests with 4096 list
+    entries each have 3.3 MB of slot lists, 4.9 MB with their repeat counts, beside a short prompt."""
+    print("[case] tl_fused_attn_static beside 409600 list entries of decode", flush=True)
+    n_dec, n_seg, C = 100, 4096, 64
+    ids = np.arange(n_seg, dtype=np.uint64) + 10
+    b = wl.Batch(name="static_decode", seed=47, q_heads=8, kv_heads=1, seg_len=C, n_slots=n_seg,
+                 req_row_ptr=np.concatenate([np.arange(n_dec + 1), [n_dec + 64]]).astype(np.int32),
+                 req_seg_ptr=np.concatenate([np.arange(n_dec + 1) * n_seg, [n_dec * n_seg + 2]]).astype(np.int32),
+                 seg_ids=np.concatenate([np.tile(ids, n_dec), ids[:2]]), pool_ids=ids,
+                 pool_slots=np.arange(n_seg, dtype=np.int32), pool_fills=np.full(n_seg, C, np.int32))
+    run = H.run_gpu(b, flags=B.TL_PLAN_SELF_BLOCK | B.TL_PLAN_NO_SHARING, fuse=True)
+    assert run.info.n_fused_tokens == 64 and run.info.n_units > 100
+    out = torch.full_like(run.out, float("nan"))
+    lse = torch.full_like(run.lse, float("nan"))
+    B.tl_fused_attn_static(run.pool, run.plan, run.q, run.k_new, run.v_new, b.scale, out, False, lse)
+    torch.cuda.synchronize()
+    assert torch.equal(out[n_dec:], run.out[n_dec:]) and torch.equal(lse[n_dec:], run.lse[n_dec:])
+    res = H.compare_rows_device(run, n_dec, np.array([0, 31, 32, 63]))
+    assert res["ok"], res
+    run.close()
+
+
 def test_static_buffer_variant_refuses_lists_beyond_its_buffer():
     """Checked before any device call, so fake pointers do: 1500 requests x 700 segments of one tile
     each give 4.2 MB of tile lists, more than the 4 MiB buffer."""
