@@ -11,6 +11,7 @@
 #include <cstring>
 #include <functional>
 #include <new>
+#include <numeric>
 #include <queue>
 #include <unordered_set>
 
@@ -478,6 +479,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       return (int32_t)((run + n - 1) / std::max<int64_t>(1, n));
     };
     int32_t row_cursor = 0;
+    const int32_t own_toks = (flags & TL_PLAN_SELF_BLOCK) ? T : 0;      // the token array: every token in order, then the items' tokens
     p->item_tok_ptr.push_back(0);
     p->item_slot_ptr.push_back(0);
     int64_t prefix_pairs = 0, tile_pairs = 0;
@@ -515,7 +517,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
                                              : even_step(run);
       for (int32_t c0 = 0; c0 < run; c0 += step) {
         const int32_t c1 = std::min(run, c0 + step);
-        const int32_t tok_base = (int32_t)p->item_tokens.size();
+        const int32_t tok_base = own_toks + (int32_t)p->item_tokens.size();
         for (int32_t r : it.reqs)
           for (int32_t t = req_row_ptr[r]; t < req_row_ptr[r + 1]; ++t) p->item_tokens.push_back(t);
         const int32_t slot_base = (int32_t)p->item_slots.size();
@@ -568,16 +570,15 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       }
     }
     p->unit_heads_log2 = plan_unit_heads_log2(pool->kv_heads, (int64_t)p->units.size(), n_cu > 0 ? n_cu : kComputeUnits);
-    // the token array doubles as the tile token list
-    p->tok = p->item_tokens;
+    p->tok.resize(own_toks);
+    std::iota(p->tok.begin(), p->tok.end(), 0);
+    p->tok.insert(p->tok.end(), p->item_tokens.begin(), p->item_tokens.end());
 
     const int32_t n_items = (int32_t)p->item_row_base.size();
     int32_t self_base = -1;
     int64_t self_pairs = 0;
     if (flags & TL_PLAN_SELF_BLOCK) {
       self_base = row_cursor;
-      const int32_t ident_base = (int32_t)p->tok.size();
-      for (int32_t t = 0; t < T; ++t) p->tok.push_back(t);
       for (int32_t r = 0; r < n_req; ++r) {
         const int32_t a = req_row_ptr[r], b = req_row_ptr[r + 1];
         const int64_t lq = b - a;
@@ -607,9 +608,9 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         for (int32_t t0 = a; t0 < b; t0 += tok_tile) {
           const int32_t n = std::min(tok_tile, b - t0);
           if (fused[r])
-            p->ftiles.push_back(Work{ident_base + t0, n, t0, a, t0 + n - a, full_off, n_full, part_off, n_part, prior_off, n_prior});
+            p->ftiles.push_back(Work{t0, n, t0, a, t0 + n - a, full_off, n_full, part_off, n_part, prior_off, n_prior});
           else
-            p->ctiles.push_back(Work{ident_base + t0, n, self_base + t0, a, t0 + n - a, 0, 0, 0, 0, 0, 0});
+            p->ctiles.push_back(Work{t0, n, self_base + t0, a, t0 + n - a, 0, 0, 0, 0, 0, 0});
         }
       }
       row_cursor += T;
@@ -717,23 +718,26 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         total += (bytes + 255) & ~(size_t)255;
         return at;
       };
+      // first what the one-pass kernel reads (of the token array, each token's own entry), all that
+      // tl_fused_attn_static has to stage
       auto& o = p->off;
+      o.ftiles = reserve(sizeof(Work) * p->ftiles.size());
+      o.tile_base = reserve(sizeof(int32_t) * p->tile_base.size());
+      o.part_tile = reserve(sizeof(int32_t) * p->part_tile.size());
+      o.tile_lm = reserve(sizeof(float) * p->tile_lm.size());
+      o.part_lm = reserve(sizeof(float) * p->part_lm.size());
+      o.prior_rows = reserve(sizeof(int32_t) * p->prior_rows.size());
+      o.tok = reserve(sizeof(int32_t) * p->tok.size());
+      p->one_pass_bytes = ((o.tok + sizeof(int32_t) * own_toks + 255) & ~(size_t)255) + 256;    // with the block's slack at its end
       o.tiles = reserve(sizeof(Work) * p->tiles.size());
       o.units = reserve(sizeof(Work) * p->units.size());
       o.ctiles = reserve(sizeof(Work) * p->ctiles.size());
-      o.ftiles = reserve(sizeof(Work) * p->ftiles.size());
-      o.tok = reserve(sizeof(int32_t) * p->tok.size());
       o.unit_slots = reserve(sizeof(int32_t) * p->unit_slots.size());
       o.unit_lm = reserve(sizeof(float) * p->unit_lm.size());
       o.merge_ptr = reserve(sizeof(int32_t) * p->merge_ptr.size());
       o.merge_rows = reserve(sizeof(int32_t) * p->merge_rows.size());
-      o.tile_base = reserve(sizeof(int32_t) * p->tile_base.size());
-      o.part_tile = reserve(sizeof(int32_t) * p->part_tile.size());
       o.merge_tok = reserve(sizeof(int32_t) * p->merge_tok.size());
       o.single_tok = reserve(sizeof(int32_t) * p->single_tok.size());
-      o.tile_lm = reserve(sizeof(float) * p->tile_lm.size());
-      o.part_lm = reserve(sizeof(float) * p->part_lm.size());
-      o.prior_rows = reserve(sizeof(int32_t) * p->prior_rows.size());
       o.merge_fix = reserve(sizeof(int32_t) * p->merge_fix.size());
       p->blob_host.assign(total + 256, 0);
       auto fill = [&](size_t at, const void* src, size_t bytes) {
