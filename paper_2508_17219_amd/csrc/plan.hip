@@ -143,6 +143,30 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     auto slot_at = [&](int32_t r, int32_t pos) { return slots[req_seg_ptr[r] + pos]; };
     auto ntok_of = [&](int32_t r) { return req_row_ptr[r + 1] - req_row_ptr[r]; };
 
+    // What a work item over positions [begin, end) of a request's list walks: a slot that is named several
+    // times once, unless TL_PLAN_WALK_REPEATS.
+    const bool dedupe = !(flags & TL_PLAN_WALK_REPEATS);
+    std::vector<int32_t> walked_by(dedupe ? pool->n_slots : 0, 0);
+    int32_t walker = 0;
+    struct Walk {
+      int32_t slots;
+      int64_t kv_tiles;
+    };
+    auto walk_of = [&](int32_t r, int32_t begin, int32_t end) {
+      Walk w{0, 0};
+      ++walker;
+      for (int32_t pos = begin; pos < end; ++pos) {
+        const int32_t sl = slot_at(r, pos);
+        if (dedupe) {
+          if (walked_by[sl] == walker) continue;
+          walked_by[sl] = walker;
+        }
+        ++w.slots;
+        w.kv_tiles += (pool->fill[sl] + kKvTile - 1) / kKvTile;
+      }
+      return w;
+    };
+
     // ---- group requests along shared runs ----------------------------------------------
     // With TL_PLAN_FUSE_ROWS a request is set aside for the one-pass kernel if sharing a run of slots
     // with other requests gains it nothing: it has no slot in common with another request of the
@@ -199,8 +223,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         int64_t n_fused = 0, load = 0;
         for (int32_t r = 0; r < n_req; ++r) {
           if (!fused[r]) continue;
-          int64_t kv = 0;
-          for (int32_t pos = 0; pos < len_of(r); ++pos) kv += (pool->fill[slot_at(r, pos)] + kKvTile - 1) / kKvTile;
+          const int64_t kv = walk_of(r, 0, len_of(r)).kv_tiles;
           const int64_t n_row = (ntok_of(r) + tok_tile - 1) / tok_tile;
           ++n_fused;
           load += kv * n_row;
@@ -333,7 +356,6 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     // multisets: Section 3.1 has no order or uniqueness among the segments a request attends to) is
     // walked once; its tiles carry log2 of the multiplicity, which the kernel adds to the exponent
     // (m equal keys weigh m exp(s) in numerator and denominator alike).  Returns the pairs computed.
-    const bool dedupe = !(flags & TL_PLAN_WALK_REPEATS);
     std::vector<int32_t> mult_of(dedupe ? pool->n_slots : 0, 0);
     auto emit_tiles = [&](auto slot_of_pos, int32_t n_pos) -> int64_t {
       int64_t kv_tokens = 0;
@@ -456,7 +478,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         if (unit_item(it, n_tok)) continue;
         const int64_t n_row = (n_tok + tok_tile - 1) / tok_tile;
         wgs += n_row * pool->kv_heads;
-        whole.push_back(RowWork{((int64_t)(it.end - it.begin) * pool->seg_len + kKvTile - 1) / kKvTile, n_row});
+        whole.push_back(RowWork{walk_of(it.src_req, it.begin, it.end).kv_tiles, n_row});
         load += whole.back().kv_tiles * n_row;
       }
       if (wgs > 0 && wgs < n_cu) tile_chunks = (int)std::min<int64_t>(16, (2 * n_cu + wgs - 1) / wgs);
@@ -472,11 +494,10 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
           longest_piece = std::max<int64_t>(2048 / kKvTile, mean / 2);
       }
     }
-    auto even_step = [&](int32_t run) -> int32_t {       // slots per piece of a run of that many
-      if (longest_piece == 0) return run;
-      const int64_t tiles = ((int64_t)run * pool->seg_len + kKvTile - 1) / kKvTile;
-      const int64_t n = (tiles + longest_piece - 1) / longest_piece;
-      return (int32_t)((run + n - 1) / std::max<int64_t>(1, n));
+    auto even_step = [&](const Walk& w) -> int32_t {       // slots per piece
+      if (longest_piece == 0) return w.slots;
+      const int64_t n = std::max<int64_t>(1, (w.kv_tiles + longest_piece - 1) / longest_piece);
+      return (int32_t)((w.slots + n - 1) / n);
     };
     int32_t row_cursor = 0;
     const int32_t own_toks = (flags & TL_PLAN_SELF_BLOCK) ? T : 0;      // the token array: every token in order, then the items' tokens
@@ -491,14 +512,24 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       int32_t n_tok = 0;
       for (int32_t r : it.reqs) n_tok += ntok_of(r);
       const bool few_rows = unit_item(it, n_tok);
+      // Pieces are cut from the slots that the run walks, not from its list: a piece of the list would
+      // walk again what another piece names too.
+      int32_t step = split;
+      bool cut = few_rows;
+      if (!few_rows) {
+        const Walk w = walk_of(it.src_req, it.begin, it.end);
+        step = tile_chunks > 1 ? std::max(min_chunk_slots, (w.slots + tile_chunks - 1) / tile_chunks) : even_step(w);
+        cut = step < w.slots;
+        if (!cut) step = it.end - it.begin;
+      }
       // The run's slots, each with the number of times the run lists it.  Split-K units walk a slot
       // that is listed m times once, with weight m, like the row tiles (reading 8 of the paper's
-      // silence on repeated segments: a list is a multiset); row-tile items dedupe in emit_tiles,
-      // so for them every list position stays an entry of its own here.
+      // silence on repeated segments: a list is a multiset); row-tile items that stay whole dedupe in
+      // emit_tiles, so for them every list position stays an entry of its own here.
       std::vector<std::pair<int32_t, int32_t>> run_slots;
       {
         const int32_t n_pos = it.end - it.begin;
-        if (few_rows && dedupe) {
+        if (cut && dedupe) {
           for (int32_t pos = it.begin; pos < it.end; ++pos) mult_of[slot_at(it.src_req, pos)]++;
           for (int32_t pos = it.begin; pos < it.end; ++pos) {
             const int32_t sl = slot_at(it.src_req, pos);
@@ -512,9 +543,6 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         }
       }
       const int32_t run = (int32_t)run_slots.size();
-      const int32_t step = few_rows ? split
-                           : tile_chunks > 1 ? std::max(min_chunk_slots, (run + tile_chunks - 1) / tile_chunks)
-                                             : even_step(run);
       for (int32_t c0 = 0; c0 < run; c0 += step) {
         const int32_t c1 = std::min(run, c0 + step);
         const int32_t tok_base = own_toks + (int32_t)p->item_tokens.size();

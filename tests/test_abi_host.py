@@ -347,6 +347,33 @@ def test_uneven_chunks_beside_decode_leave_the_one_pass_kernel(heads):
     assert plan_of(900, 30000, 40, 0)[0].n_fused_tokens == 600 * n_chunk
 
 
+@pytest.mark.parametrize("n_chunk,new,n_decode,fuse,compute_units", [
+    (1, 300, 0, False, -1),        # fewer row tiles than CUs: about two pieces per CU
+    (5, 300, 0, False, -1),        # lists of uneven lengths
+    (3, 300, 40, True, -1),        # prefill chunks beside decode
+    (8, 512, 60, True, -1),
+    (5, 300, 12, False, 64),
+])
+def test_cutting_lists_with_repeats_walks_no_slot_twice(n_chunk, new, n_decode, fuse, compute_units):
+    """Long lists drawn with replacement from 40 popular segments: whatever the plan cuts, the row tiles walk
+    every distinct slot of a request once, as the uncut plan does; with TL_PLAN_WALK_REPEATS every occurrence."""
+    C, popular = 512, 40
+    rng = np.random.Generator(np.random.PCG64(n_chunk))
+    lists = [rng.integers(0, popular, size=n).tolist() for n in [250, 16, 60, 120, 30, 200, 90, 16][:n_chunk]]
+    lists += [rng.integers(0, popular, size=20).tolist() for _ in range(n_decode)]
+    b = wl._finish("repeats", 3, 32, 8, C, 64, [new] * n_chunk + [1] * n_decode, lists, {7: 100, 9: 511}, rng)
+    plan_pool[0] = _pool_for(b)
+    fill_of = dict(zip(b.pool_ids.tolist(), b.pool_fills.tolist()))
+    for walk, once in ((0, True), (B.TL_PLAN_WALK_REPEATS, False)):
+        flags = B.TL_PLAN_SELF_BLOCK | walk | (B.TL_PLAN_FUSE_ROWS if fuse else B.TL_PLAN_NO_SHARING)
+        plan = B.tl_plan_create(plan_pool[0], b.q_heads, b.req_row_ptr, b.req_seg_ptr, b.seg_ids, flags, 0, compute_units)
+        info = B.tl_plan_get_info(plan)
+        _check_plan_covers(b, plan, flags, fused_req=tuple(range(n_chunk)) if info.n_fused_tokens else ())
+        assert info.tile_pairs == new * sum(fill_of[s] for l in lists[:n_chunk] for s in (set(l) if once else l))
+        B.tl_plan_destroy(plan)
+    B.tl_pool_destroy(plan_pool[0])
+
+
 def test_one_pass_tails_keep_shared_runs_as_work_items():
     """TL_PLAN_FUSE_TAILS: the shared system prompt stays one work item read once for every session's
     rows; each session's private history and its new tokens are one-pass rows that merge the session's

@@ -538,6 +538,23 @@ def test_repeated_segments_in_split_k_units_are_walked_once():
         runs[0].close(); runs[1].close()
 
 
+@pytest.mark.parametrize("n_decode,fuse", [(0, False), (30, True)])
+def test_cut_lists_with_repeats_against_the_oracle(n_decode, fuse):
+    """Lists with repeats that the plan cuts, alone and beside decoded tokens: a piece holds distinct slots,
+    each with its multiplicity over the whole list."""
+    _say("cut lists with repeats, %d decoded" % n_decode)
+    rng = np.random.Generator(np.random.PCG64(8))
+    lists = [rng.integers(0, 60, size=n).tolist() for n in (200, 40, 90, 16, 16)] + [rng.integers(0, 60, size=7).tolist() for _ in range(n_decode)]
+    b = wl._finish("cut_repeats", 9, 32, 8, 256, 64, [300, 300, 150, 130, 300] + [1] * n_decode, lists, {7: 100, 9: 255}, rng)
+    run = H.run_gpu(b, flags=B.TL_PLAN_SELF_BLOCK | B.TL_PLAN_NO_SHARING, fuse=fuse, compute_units=-1)
+    lens = np.diff(b.req_row_ptr)
+    once = sum(int(n) * sum(dict(zip(b.pool_ids.tolist(), b.pool_fills.tolist()))[s] for s in set(l)) for n, l in zip(lens, lists) if n > 1)
+    assert run.info.tile_pairs == once
+    assert run.info.n_tiles > 2 * 21 and (run.info.n_units > 0) == (n_decode > 0)       # 21 row tiles, their lists cut
+    _check_all_requests(run, rows_per_req=8, seed=6, reqs=range(8 if n_decode else 5))
+    run.close()
+
+
 @pytest.mark.parametrize("turn", range(8))
 def test_full_multiturn_config_every_session(turn):
     """Every session of every turn, three-step plan (the shared prompt as one work item read once
