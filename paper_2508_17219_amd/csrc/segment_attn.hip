@@ -119,12 +119,32 @@ __device__ __forceinline__ float max16(const f32x16& s) {
   return fmaxf(fmaxf(fmaxf(a, b), fmaxf(c, d)), fmaxf(e, s[15]));
 }
 
+__host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) {
+  return ((unsigned)a.n_units * (unsigned)(a.kv_heads >> a.unit_heads_log2) + 7u) & ~7u;
+}
+
 // MODE 0: pool work item (tile lists) -> partial.  MODE 1: causal block of the new tokens ->
 // partial.  MODE 2: both in one pass -- the row tile walks its request's pool tiles, then the
 // new tokens up to its own rows -- and writes the final, normalised output: such rows have one
 // partial, so they need no merge.
-template <int MODE, int VREAD>
-__device__ __forceinline__ void row_tile(const AttnArgs& a, const int block, uint16_t* lds) {
+//
+// JOINT (MODE 0): row tiles of the pool and split-K units in one launch: units first, which are bound by HBM and by their own
+// chain, then row tiles, which find the CUs that the units leave and finish evenly on all of them.  The first
+// row tile's block is a multiple of eight, so that a kv head stays on its XCD.  One launch after the other, the
+// first leaves CUs idle at its end and HBM idles through the row tiles: 5 chunks of up to 941 tokens beside 67 decoded
+// ones 407 us a step, together 372; 3 chunks of 64 to 438 beside 12, 266 and 239 us.  (Groups of eight blocks of each
+// kind in turn: a unit takes a whole round whatever runs beside it, so the units' second round ends late, 574 us
+// where units first are 510.)  The branch is in the kernel itself, not around a function that both kernels call: passed
+// to such a function, the block's number cost the one-pass kernel two spilled registers.
+template <int MODE, int VREAD, bool JOINT = false>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void row_tile_attn_kernel(const AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  if (JOINT && blockIdx.x < unit_blocks(a)) {
+    if (blockIdx.x < (unsigned)a.n_units * (unsigned)(a.kv_heads >> a.unit_heads_log2))
+      unit::splitk_unit<VREAD>(a, a.units[blockIdx.x % a.n_units], blockIdx.x / a.n_units, lds);
+    return;
+  }
+  const unsigned block = JOINT ? blockIdx.x - unit_blocks(a) : blockIdx.x;
   uint16_t* lds_k = lds;                 // [kBufs][64][kKS]
   uint16_t* lds_v = lds + kBufs * kKTile;    // [kBufs][64][kVS]
   int32_t* lds_idx = (int32_t*)(lds + kBufs * (kKTile + kVTile));   // [kIdxRing]
@@ -734,32 +754,6 @@ __device__ __forceinline__ void row_tile(const AttnArgs& a, const int block, uin
   }
 }
 
-template <int MODE, int VREAD>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void row_tile_attn_kernel(const AttnArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
-  row_tile<MODE, VREAD>(a, blockIdx.x, lds);
-}
-
-// Row tiles of the pool and split-K units in one launch: units first, which are bound by HBM and by their own
-// chain, then row tiles, which find the CUs that the units leave and finish evenly on all of them.  The first
-// row tile's block is a multiple of eight, so that a kv head stays on its XCD.  One launch after the other, the
-// first leaves CUs idle at its end and HBM idles through the row tiles: 5 chunks of up to 941 tokens beside 67 decoded
-// ones 407 us a step, together 372; 3 chunks of 64 to 438 beside 12, 266 and 239 us.  (Groups of eight blocks of each
-// kind in turn: a unit takes a whole round whatever runs beside it, so the units' second round ends late, 574 us
-// where units first are 510.)
-__host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) {
-  return ((unsigned)a.n_units * (unsigned)(a.kv_heads >> a.unit_heads_log2) + 7u) & ~7u;
-}
-template <int VREAD>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void tiles_and_units_attn_kernel(const AttnArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
-  const unsigned n_unit_blocks = unit_blocks(a);
-  if (blockIdx.x >= n_unit_blocks) {
-    row_tile<0, VREAD>(a, blockIdx.x - n_unit_blocks, lds);
-  } else if (blockIdx.x < (unsigned)a.n_units * (unsigned)(a.kv_heads >> a.unit_heads_log2)) {
-    unit::splitk_unit<VREAD>(a, a.units[blockIdx.x % a.n_units], blockIdx.x / a.n_units, lds);
-  }
-}
 static_assert(kThreads == unit::kThreads, "one block size for both kinds");
 
 template <int MODE>
@@ -785,7 +779,7 @@ tl_status launch_tiles_and_units(const AttnArgs& a, hipStream_t st) {
   const dim3 grid(unit_blocks(a) + (unsigned)a.n_work * a.kv_heads), block(kThreads);
   static std::atomic<uint64_t> allowed[2];
   const bool scalar_v = get_option_vread() != 0;
-  auto kern = scalar_v ? tiles_and_units_attn_kernel<1> : tiles_and_units_attn_kernel<0>;
+  auto kern = scalar_v ? row_tile_attn_kernel<0, 1, true> : row_tile_attn_kernel<0, 0, true>;
   constexpr size_t lds_bytes = kLdsBytes > unit::kLdsBytes ? kLdsBytes : unit::kLdsBytes;
   const tl_status rc = allow_lds((const void*)kern, lds_bytes, allowed[scalar_v]);
   if (rc != TL_OK) return rc;
