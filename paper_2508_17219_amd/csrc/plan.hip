@@ -549,7 +549,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         for (int32_t r : it.reqs)
           for (int32_t t = req_row_ptr[r]; t < req_row_ptr[r + 1]; ++t) p->item_tokens.push_back(t);
         const int32_t slot_base = (int32_t)p->item_slots.size();
-        const int32_t unit_base = (int32_t)p->unit_slots.size() / 2;
+        const int32_t unit_base = (int32_t)(p->unit_slots.size() / 2);
         for (int32_t u = c0; u < c1; ++u) {
           const int32_t sl = run_slots[u].first, m = run_slots[u].second;
           for (int32_t k = 0; k < m; ++k) p->item_slots.push_back(sl);       // the item's list keeps every occurrence

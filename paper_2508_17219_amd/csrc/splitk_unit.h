@@ -35,6 +35,14 @@ constexpr size_t kLdsBytes = (size_t)kWaves * kWaveElems * sizeof(uint16_t);
 constexpr int kSliceStats = 8 * 64 * 4;                    // offset of the statistics, in floats
 static_assert((kSliceStats + 3 * 16) * sizeof(float) <= kWaveElems * sizeof(uint16_t), "a slice fits its wave's region");
 
+// The plan's lists through the constant address space: nothing in a launch writes them.  In a kernel that the
+// compiler cannot see this of (row tiles beside units), it would take the cursor's loads through the vector unit,
+// whose wait is for the tile in flight as well: 128 requests of 500 to 32k tokens 713 us there, 634 with scalar loads.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* scalar_loads(const T* p) {
+  return (const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
+
 template <int VREAD>
 __device__ __forceinline__ void splitk_unit(const AttnArgs& a, const Work wk, const int head_block, uint16_t* lds) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -116,12 +124,14 @@ __device__ __forceinline__ void splitk_unit(const AttnArgs& a, const Work wk, co
   // of the list is (first kv row of the slot, valid tokens)
   // (a slot that the unit's run lists m times is walked once; its keys weigh m: lm = log2 m is
   // added to the exponent of the tile's probabilities)
+  const auto* entries = scalar_loads((const int2*)a.unit_slots + wk.kv_off);
+  const auto* lms = scalar_loads(a.slot_lm + wk.kv_off);
   int li = 0, kk = slice;
   auto next_tile = [&](int& base, int& valid, float& lm) __attribute__((always_inline)) -> bool {
     int i = li, k = kk, first = 0, f = 0;
     for (; i < wk.kv_len; ++i) {
-      first = a.unit_slots[2 * (wk.kv_off + i)];
-      f = a.unit_slots[2 * (wk.kv_off + i) + 1];
+      first = entries[i].x;
+      f = entries[i].y;
       if (k * kTok < f) break;
       k -= (f + kTok - 1) / kTok;
     }
@@ -129,7 +139,7 @@ __device__ __forceinline__ void splitk_unit(const AttnArgs& a, const Work wk, co
     if (found) {
       base = first + k * kTok;
       valid = min(kTok, f - k * kTok);
-      lm = a.slot_lm ? a.slot_lm[wk.kv_off + i] : 0.f;
+      lm = a.slot_lm ? lms[i] : 0.f;
     }
     li = i;
     kk = k + slices;

@@ -1,5 +1,5 @@
 """What the compiler makes of the attention kernels: the variants that run by default (transposing LDS reads
-of V) hold everything in registers.  The kernels are compiled for the device, nothing is run."""
+of V) hold everything in registers, and the split-K unit's lists are read by scalar loads.  The kernels are compiled for the device, nothing is run."""
 import os
 import re
 import subprocess
@@ -10,16 +10,37 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2508_17219_amd", "csrc")
 
 
-@pytest.mark.parametrize("source,n_kernels", [("segment_attn.hip", 4), ("decode_attn.hip", 1)])
-def test_default_attention_kernels_spill_no_register(source, n_kernels):
+def _device_compile(source, out, *flags):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not os.path.exists(hipcc):
         pytest.skip("no hipcc here")
     cmd = [hipcc, "-O3", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "--cuda-device-only", "-c", os.path.join(CSRC, source),
-           "-o", os.devnull, "-Rpass-analysis=kernel-resource-usage"]
-    text = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, check=True).stdout
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "--cuda-device-only", os.path.join(CSRC, source), "-o", out] + list(flags)
+    return subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, check=True).stdout
+
+
+@pytest.mark.parametrize("source,n_kernels", [("segment_attn.hip", 4), ("decode_attn.hip", 1)])
+def test_default_attention_kernels_spill_no_register(source, n_kernels):
+    text = _device_compile(source, os.devnull, "-c", "-Rpass-analysis=kernel-resource-usage")
     spills = re.findall(r"Function Name: (\S+).*?VGPRs Spill: (\d+)", text, re.S)
     default = {name: int(n) for name, n in spills if re.search(r"row_tile_attn_kernelILi\dELi0E|splitk_unit_attn_kernelILi0E", name)}
     assert len(default) == n_kernels, spills
     assert not any(default.values()), default
+
+
+def test_units_beside_row_tiles_walk_their_lists_through_scalar_loads(tmp_path):
+    """The tile cursor of a split-K unit loads from the plan's lists between two tiles: a vector load there would be
+    waited for together with the tile in flight.  In a launch of its own or beside row tiles, the one
+    single-word vector load of a unit is its tokens' numbers (each lane has its own)."""
+    loads = {}
+    for source in ("segment_attn.hip", "decode_attn.hip"):
+        asm = str(tmp_path / (source + ".s"))
+        _device_compile(source, asm, "-S")
+        text = open(asm).read()
+        for m in re.finditer(r"^(_ZN\S+):", text, re.M):
+            body = text[m.end():text.index(".Lfunc_end", m.end())]
+            loads[m.group(1)] = len(re.findall(r"\bglobal_load_dword ", body))
+    row_tiles = next(n for k, n in loads.items() if "row_tile_attn_kernelILi0ELi0ELb0E" in k)
+    joint = next(n for k, n in loads.items() if "row_tile_attn_kernelILi0ELi0ELb1E" in k)
+    units = next(n for k, n in loads.items() if "splitk_unit_attn_kernelILi0E" in k)
+    assert units <= 2 and joint <= row_tiles + units + 1, loads
