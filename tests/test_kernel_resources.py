@@ -30,17 +30,14 @@ def test_default_attention_kernels_spill_no_register(source, n_kernels):
 
 def test_units_beside_row_tiles_walk_their_lists_through_scalar_loads(tmp_path):
     """The tile cursor of a split-K unit loads from the plan's lists between two tiles: a vector load there would be
-    waited for together with the tile in flight.  In a launch of its own or beside row tiles, the one
-    single-word vector load of a unit is its tokens' numbers (each lane has its own)."""
-    loads = {}
-    for source in ("segment_attn.hip", "decode_attn.hip"):
+    waited for together with the tile in flight.  In a launch of its own or beside row tiles, the unit's
+    loop over tiles has no single-word vector load."""
+    for source, kernel in (("segment_attn.hip", "row_tile_attn_kernelILi0ELi0ELb1E"), ("decode_attn.hip", "splitk_unit_attn_kernelILi0E")):
         asm = str(tmp_path / (source + ".s"))
         _device_compile(source, asm, "-S")
         text = open(asm).read()
-        for m in re.finditer(r"^(_ZN\S+):", text, re.M):
-            body = text[m.end():text.index(".Lfunc_end", m.end())]
-            loads[m.group(1)] = len(re.findall(r"\bglobal_load_dword ", body))
-    row_tiles = next(n for k, n in loads.items() if "row_tile_attn_kernelILi0ELi0ELb0E" in k)
-    joint = next(n for k, n in loads.items() if "row_tile_attn_kernelILi0ELi0ELb1E" in k)
-    units = next(n for k, n in loads.items() if "splitk_unit_attn_kernelILi0E" in k)
-    assert units <= 2 and joint <= row_tiles + units + 1, loads
+        start = re.search(r"^_ZN\S*%s\S*:" % kernel, text, re.M).end()
+        body = text[start:text.index(".Lfunc_end", start)]
+        first, last = body.index("v_mfma_f32_16x16x32"), body.rindex("v_mfma_f32_16x16x32")
+        loop = body[body.rindex("Loop Header: Depth=1", 0, first):last]
+        assert "s_load_dword" in loop and not re.search(r"\bglobal_load_dword ", loop), kernel
