@@ -15,9 +15,9 @@ __global__ __launch_bounds__(unit::kThreads) void splitk_unit_attn_kernel(const 
 
 tl_status launch_splitk_units(const AttnArgs& a, int n_work, hipStream_t st) {
   if (n_work == 0) return TL_OK;
-  if (a.unit_heads_log2 < 0 || a.unit_heads_log2 > 3 || a.kv_heads & ((1 << a.unit_heads_log2) - 1))
+  if (!unit::can_deal(a))
     TL_FAIL(TL_EINVAL, "launch_splitk_units: %d kv heads cannot be dealt %d to a workgroup", a.kv_heads, 1 << a.unit_heads_log2);
-  const dim3 grid((unsigned)n_work, (unsigned)(a.kv_heads >> a.unit_heads_log2)), block(unit::kThreads);
+  const dim3 grid((unsigned)n_work, (unsigned)unit_head_blocks(a.kv_heads, a.unit_heads_log2)), block(unit::kThreads);
   static std::atomic<uint64_t> allowed[2];
   const bool scalar_v = get_option_vread() != 0;
   auto kern = scalar_v ? splitk_unit_attn_kernel<1> : splitk_unit_attn_kernel<0>;

@@ -27,17 +27,32 @@ struct RawItem {
   int32_t begin, end;          // list positions [begin, end)
 };
 
+// The split-K units of a batch.
+struct UnitLoad {
+  int64_t units = 0, tokens = 0, longest = 0;      // kv tokens of all units and of the longest
+
+  bool even() const { return 10 * tokens >= 7 * units * longest; }
+};
+
 // kv heads per workgroup of the split-K kernel: the most of 8, 4, 2 or 1 that divides kv_heads (whole
-// token rows per workgroup stream best), halved while the launch would be fewer workgroups than
-// three quarters of the CUs: then a unit's heads go to several workgroups, whose waves share the
-// unit's tokens.  Measured, a workgroup per unit with one wave per head against this deal: 64 requests
-// of a one-kv-head layer 391 -> 123 us (1.8 -> 5.8 TB/s; seven of eight waves had no head), one request
-// of 15.9k tokens with 8 kv heads 34 -> 15 us (32 workgroups became 256); with 8 heads and 200 units or
-// more the two are the same launch (234 us, 5.97 TB/s; 811 units 3.83 ms, 6.0 TB/s).
-int32_t plan_unit_heads_log2(int32_t kv_heads, int64_t n_units, int64_t n_cu) {
+// token rows per workgroup stream best), halved while the launch stays one round of the CUs: then a unit's heads
+// go to several workgroups, whose waves share the unit's tokens.  Measured, a workgroup per unit with one wave per head
+// against this deal: 64 requests of a one-kv-head layer 391 -> 123 us (1.8 -> 5.8 TB/s; seven of eight waves had no
+// head), one request of 15.9k tokens with 8 kv heads 34 -> 15 us (32 workgroups became 256); with 8 heads and 200 units
+// or more the two are the same launch (234 us, 5.97 TB/s; 811 units 3.83 ms, 6.0 TB/s).
+// More than half a round of units of one length is left alone, a thin second round costs more than the first
+// gains (168 units of 512 tokens, 8 heads: 55.9 us, halved 62.6); units of uneven length are halved up to three
+// quarters of a round, the shorter ones then fill the second (131 units of up to 512 tokens 35.7, halved 33.9).
+// Where 8 does not divide the heads, 8 to a workgroup with up to three waves idle is better for one round of even
+// units (227 units of 5 heads: 92 us, 102 with a workgroup per head; 118 of 12 heads 58 and 61; but 196 uneven units of
+// 5 heads 190 and 156).
+int32_t plan_unit_heads_log2(int32_t kv_heads, const UnitLoad& load, int64_t n_cu) {
+  const int32_t eights = unit_head_blocks(kv_heads, 3);
+  if (kv_heads % 8 && kv_heads >= 5 * eights && load.even() && 8 * load.units * eights > 3 * n_cu && load.units * eights <= n_cu) return 3;
   int32_t log2 = 3;
   while (kv_heads & ((1 << log2) - 1)) --log2;
-  while (log2 > 0 && 4 * n_units * (kv_heads >> log2) < 3 * n_cu) --log2;
+  while (log2 > 0 && 2 * load.units * unit_head_blocks(kv_heads, log2) <= n_cu) --log2;
+  if (log2 > 0 && !load.even() && 4 * load.units * unit_head_blocks(kv_heads, log2) < 3 * n_cu) --log2;
   return log2;
 }
 
@@ -597,7 +612,15 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         row_cursor += n_tok;
       }
     }
-    p->unit_heads_log2 = plan_unit_heads_log2(pool->kv_heads, (int64_t)p->units.size(), n_cu > 0 ? n_cu : kComputeUnits);
+    UnitLoad unit_load;
+    for (const Work& w : p->units) {
+      int64_t tokens = 0;
+      for (int32_t i = w.kv_off; i < w.kv_off + w.kv_len; ++i) tokens += p->unit_slots[2 * (size_t)i + 1];
+      ++unit_load.units;
+      unit_load.tokens += tokens;
+      unit_load.longest = std::max(unit_load.longest, tokens);
+    }
+    p->unit_heads_log2 = plan_unit_heads_log2(pool->kv_heads, unit_load, n_cu > 0 ? n_cu : kComputeUnits);
     p->tok.resize(own_toks);
     std::iota(p->tok.begin(), p->tok.end(), 0);
     p->tok.insert(p->tok.end(), p->item_tokens.begin(), p->item_tokens.end());

@@ -120,7 +120,7 @@ __device__ __forceinline__ float max16(const f32x16& s) {
 }
 
 __host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) {
-  return ((unsigned)a.n_units * (unsigned)(a.kv_heads >> a.unit_heads_log2) + 7u) & ~7u;
+  return ((unsigned)a.n_units * (unsigned)unit_head_blocks(a.kv_heads, a.unit_heads_log2) + 7u) & ~7u;
 }
 
 // MODE 0: pool work item (tile lists) -> partial.  MODE 1: causal block of the new tokens ->
@@ -140,7 +140,7 @@ template <int MODE, int VREAD, bool JOINT = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void row_tile_attn_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   if (JOINT && blockIdx.x < unit_blocks(a)) {
-    if (blockIdx.x < (unsigned)a.n_units * (unsigned)(a.kv_heads >> a.unit_heads_log2))
+    if (blockIdx.x < (unsigned)a.n_units * (unsigned)unit_head_blocks(a.kv_heads, a.unit_heads_log2))
       unit::splitk_unit<VREAD>(a, a.units[blockIdx.x % a.n_units], blockIdx.x / a.n_units, lds);
     return;
   }
@@ -774,7 +774,7 @@ tl_status launch_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) {
 
 tl_status launch_pool_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) { return launch_row_tiles<0>(a, n_work, st); }
 tl_status launch_tiles_and_units(const AttnArgs& a, hipStream_t st) {
-  if (a.unit_heads_log2 < 0 || a.unit_heads_log2 > 3 || a.kv_heads & ((1 << a.unit_heads_log2) - 1))
+  if (!unit::can_deal(a))
     TL_FAIL(TL_EINVAL, "launch_tiles_and_units: %d kv heads cannot be dealt %d to a workgroup", a.kv_heads, 1 << a.unit_heads_log2);
   const dim3 grid(unit_blocks(a) + (unsigned)a.n_work * a.kv_heads), block(kThreads);
   static std::atomic<uint64_t> allowed[2];

@@ -3,7 +3,7 @@
 // the memory-bound side of max(4Cd/F, 4Cd/B_mem)).
 //
 // One workgroup = one unit (a few query tokens x a chunk of the slot list) for `unit_heads` kv heads
-// (1, 2, 4 or 8, a divisor of kv_heads).  Its 8 waves are dealt to (head, slice) pairs: wave w takes
+// (1, 2, 4 or 8; a divisor of kv_heads, or 8 with idle waves).  Its 8 waves are dealt to (head, slice) pairs: wave w takes
 // head unit_heads * head_block + w % unit_heads and, of the chunk's 32-token tiles, every
 // (8 / unit_heads)-th from w / unit_heads on; the slices of a head are added up through LDS at the end,
 // so that a unit gives one partial whatever the deal.  With 8 heads the workgroup as a whole reads
@@ -43,6 +43,11 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* scalar_loa
   return (const __attribute__((address_space(4))) T*)(uintptr_t)p;
 }
 
+// Whole workgroups, or a wave per head (waves that share a head meet at a barrier: none may be without one).
+inline bool can_deal(const AttnArgs& a) {
+  return a.unit_heads_log2 == 3 || (a.unit_heads_log2 >= 0 && a.unit_heads_log2 < 3 && !(a.kv_heads & ((1 << a.unit_heads_log2) - 1)));
+}
+
 template <int VREAD>
 __device__ __forceinline__ void splitk_unit(const AttnArgs& a, const Work wk, const int head_block, uint16_t* lds) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -50,6 +55,7 @@ __device__ __forceinline__ void splitk_unit(const AttnArgs& a, const Work wk, co
   const int heads = 1 << a.unit_heads_log2, slices = kWaves >> a.unit_heads_log2;
   const int slice = wave >> a.unit_heads_log2;          // scalar, as the tile cursor has to be
   const int g = head_block * heads + (wave & (heads - 1));
+  if (g >= a.kv_heads) return;                          // 8 heads to a workgroup, no barrier below
   const int G = a.group;
   uint16_t* kt = lds + wave * kWaveElems;
   uint16_t* vt = kt + kTok * kLdsStride;

@@ -44,6 +44,11 @@ constexpr int kUnitRows = 16;    // max rows per kv head of a split-K unit
 constexpr int kFuseRows = 2 * kRowTile;
 constexpr int kComputeUnits = 256;   // MI355X (tl_plan_create's default; the plan builder makes no HIP call)
 
+// Workgroups per split-K unit where each takes 2^heads_log2 kv heads.
+__host__ __device__ inline int32_t unit_head_blocks(int32_t kv_heads, int32_t heads_log2) {
+  return (kv_heads + (1 << heads_log2) - 1) >> heads_log2;
+}
+
 // One unit of kernel work.  Its query tokens are tok[tok_off .. tok_off+n_tok) (batch token
 // indices), its partial rows out_row .. out_row+n_tok-1.
 //  pool work:   split-K units: kv_off/kv_len index the plan's unit slot list, entries of two ints (with unit_lm[]);

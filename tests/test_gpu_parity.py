@@ -1171,6 +1171,22 @@ def test_split_k_units_with_their_waves_dealt_to_heads_and_slices(hq, hkv, compu
         run.close()
 
 
+@pytest.mark.parametrize("hq,hkv,compute_units", [(10, 5, 16), (12, 6, 16), (28, 7, 16), (24, 12, 24), (8, 8, 16), (4, 4, 16)])
+@pytest.mark.parametrize("chunk", [False, True])
+def test_split_k_units_of_one_length_in_one_round(hq, hkv, compute_units, chunk):
+    """12 units of about one length, which fill half a round or more: head counts that 8 does not divide take 8 heads to
+    a workgroup with idle waves, 4 and 8 heads are not spread further; alone and beside row tiles."""
+    _say("even units hq=%d hkv=%d beside row tiles: %s" % (hq, hkv, chunk))
+    lengths = np.array([512, 500, 511, 480, 449, 512, 470, 505, 512, 490, 460, 481] + [300] * chunk)
+    lists, fills = wl._lists_from_lengths(lengths, 64)
+    rng = np.random.Generator(np.random.PCG64(6))
+    b = wl._finish("even_units", 54, hq, hkv, 64, 128, [1] * 12 + [130] * chunk, lists, fills, rng, k_gain=4.0, v_offset_mod=7)
+    run = H.run_gpu(b, compute_units=compute_units)
+    assert run.info.n_units == 12 and (run.info.n_tiles > 0) == chunk
+    _check_all_requests(run)
+    run.close()
+
+
 def test_single_long_prompt_is_cut_along_its_kv_and_merged():
     """A batch too small to fill the GPU with row tiles: the plan cuts the slot list into chunks,
     each chunk yields a partial per row, the merge puts them together."""
