@@ -208,8 +208,13 @@ enum {
                              whose lists are long enough (> 2048 tokens) to be cut along the
                              KV instead, and except, in a batch that also has requests of at
                              most 16 rows (decode) with a list, where cutting the lists and
-                             sharing a launch with those is estimated to be faster by a tenth
-                             or more (lists of uneven lengths).  Such rows have a single partial, so nothing is
+                             sharing a launch with those is estimated to be faster (lists of
+                             uneven lengths, CUs that the decode work leaves idle).  Requests of
+                             the last two kinds are planned as without the flag and need partial
+                             rows, one per token and piece of the list and one per token for the
+                             self block: a batch of 4 chunks of 300 to 600 tokens beside 48 decoded
+                             ones (32 q-heads) has 7177 partial rows, 118 MB, instead of 2356;
+                             tl_plan_get_info's n_partial_rows says how many.  One-pass rows have a single partial, so nothing is
                              written to out_partial for them and tl_segment_attn /
                              tl_causal_block / tl_merge skip them.  Needs TL_PLAN_SELF_BLOCK. */
   TL_PLAN_FUSE_TAILS = 16 /* every request with more than 16 query rows per kv head (that

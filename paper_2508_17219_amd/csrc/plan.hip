@@ -56,10 +56,33 @@ int32_t plan_unit_heads_log2(int32_t kv_heads, const UnitLoad& load, int64_t n_c
   return log2;
 }
 
-// What the row tiles of a batch cost, in KV tiles of a workgroup (1.5 us): a workgroup's start, first
-// loads and epilogue, and a step's causal launch and merge where the one-pass kernel needs neither.
-constexpr int64_t kTileStart = 5, kThreeStepLaunches = 10;
-constexpr double kBytesPerTile = 7.8e6;      // what HBM moves in the time of one KV tile (5.2 TB/s)
+// What a batch costs, in KV tiles of a row-tile workgroup (1.5 us): a workgroup's start, first loads and epilogue;
+// the launch of one-pass rows behind the split-K units', and the causal launch and merge of the three steps; bytes of
+// partials and of split-K units in the time of a tile.  Fitted to 758 random batches of 1 to 12 prefill chunks beside 2 to
+// 250 decoded tokens in eight layer shapes, 37 us to 3.2 ms, each timed both as one-pass rows and on the three
+// steps; the two estimates are off by 12 and 16 % in the root mean square.
+constexpr int64_t kTileStart = 5;
+constexpr double kOnePassLaunch = 8, kThreeStepLaunches = 6;
+constexpr double kBytesPerTile = 7.8e6, kUnitBytesPerTile = 9.75e6;
+
+// KV tiles from which a list is cut where its launch ends unevenly, so that a piece's start stays small: the pieces are
+// even, so half of it (1024 tokens) is the shortest.  (At least this much a piece instead: 4 chunks of 64 to 364 tokens on
+// 1.4k to 11k beside 27 decoded tokens 246 us for 235.)
+constexpr int32_t kMinPieceTiles = 2048 / kKvTile;
+
+// Partial rows of `row_tiles` row tiles, written and read.
+double merge_tiles(int64_t row_tiles, int32_t kv_heads) {
+  return (double)row_tiles * kRowTile * kv_heads * (2 * 4 * kHeadDim) / kBytesPerTile;
+}
+
+// A launch of split-K units and row tiles together, both given as launches of their own.  Row tiles fill the CUs that
+// the units' last round of workgroups leaves idle (up to half of them: they are as long as their lists), and some
+// of what either waits for beside that.
+double joint_tiles(double units, int64_t unit_blocks, double tiles, int64_t n_cu) {
+  const int64_t room = (unit_blocks + n_cu - 1) / n_cu * n_cu;
+  const double idle = units * (double)(room - unit_blocks) / (double)room, shorter = std::min(units, tiles);
+  return units + tiles - std::min(shorter, std::min(idle, 0.5 * tiles) + 0.25 * shorter);
+}
 
 struct RowWork {
   int64_t kv_tiles, row_tiles;
@@ -91,11 +114,76 @@ int64_t makespan(std::vector<RowWork> work, int64_t lanes) {
   return end;
 }
 
-// Pieces that a list of `kv_tiles` is cut into where the mean load of a CU is `mean`: pieces of at most half the
-// mean let a launch end evenly; shorter ones (never under 2048 tokens) would only add partials to merge.
-int64_t pieces_of(int64_t kv_tiles, int64_t mean) {
-  const int64_t longest = std::max<int64_t>(2048 / kKvTile, mean / 2);
-  return std::max<int64_t>(1, (kv_tiles + longest - 1) / longest);
+// What a work item over a run of a list walks: slots (a repeated one once), their tokens and KV tiles.
+struct Walk {
+  int32_t slots;
+  int64_t tokens, kv_tiles;
+};
+
+struct RowItem {       // a work item of row tiles
+  Walk walk;
+  int64_t row_tiles;
+};
+
+// How the lists of a launch's row-tile items are cut along the KV: into `chunks` pieces of min_slots or more, or
+// into pieces of about `longest` KV tiles (0: not cut).
+struct RowCut {
+  int32_t chunks = 1, min_slots = 1;
+  int64_t longest = 0;
+
+  // slots per piece; the last piece takes what is left
+  int32_t step(const Walk& w) const {
+    if (chunks > 1) return std::max(min_slots, (w.slots + chunks - 1) / chunks);
+    if (longest == 0) return w.slots;
+    const int64_t n = std::max<int64_t>(1, (w.kv_tiles + longest - 1) / longest);
+    return (int32_t)((w.slots + n - 1) / n);
+  }
+};
+
+// The row tiles of the items' pieces, and the partial rows that they write (x kRowTile).
+int64_t cut_items(const std::vector<RowItem>& items, const RowCut& cut, std::vector<RowWork>& pieces) {
+  int64_t n_partial = 0;
+  pieces.clear();
+  for (const RowItem& it : items) {
+    if (it.walk.slots == 0) continue;
+    const int64_t step = cut.step(it.walk), whole = it.walk.slots / step, rest = it.walk.slots % step;
+    const int64_t kv = (it.walk.kv_tiles * step + it.walk.slots - 1) / it.walk.slots;
+    pieces.push_back(RowWork{kv, whole * it.row_tiles});
+    if (rest > 0) pieces.push_back(RowWork{std::max<int64_t>(1, it.walk.kv_tiles - kv * whole), it.row_tiles});
+    n_partial += (whole + (rest > 0)) * it.row_tiles;
+  }
+  return n_partial;
+}
+
+// Row-tile items of a small batch: when all row tiles together are fewer workgroups than the
+// GPU has CUs, long slot lists are cut into chunks (each a work item with partial rows of its
+// own, merged like any other) until there are about two workgroups per CU; a chunk keeps at
+// least 2048 tokens so that its start-up stays small against its work.  With more row tiles than that,
+// lists longer than half the mean load of a CU are cut if that ends the launch earlier by more than the
+// partials cost (lists of unequal length, or a little more than a whole number of rounds): pieces of half
+// the mean let a launch end evenly, shorter ones would only add partials to merge.
+RowCut plan_row_cut(const std::vector<RowItem>& items, int64_t n_cu, int32_t kv_heads, int32_t seg_len) {
+  RowCut c;
+  c.min_slots = std::max(1, kMinPieceTiles * kKvTile / seg_len);
+  int64_t wgs = 0, load = 0;
+  for (const RowItem& it : items) {
+    wgs += it.row_tiles * kv_heads;
+    load += it.walk.kv_tiles * it.row_tiles;
+  }
+  if (wgs == 0 || n_cu <= 0) return c;
+  if (wgs < n_cu) {
+    c.chunks = (int32_t)std::min<int64_t>(16, (2 * n_cu + wgs - 1) / wgs);
+    return c;
+  }
+  const int64_t lanes = std::max<int64_t>(1, n_cu / kv_heads);
+  RowCut half = c;
+  half.longest = std::max<int64_t>(kMinPieceTiles, load / lanes / 2);
+  std::vector<RowWork> pieces;
+  const int64_t n_whole = cut_items(items, c, pieces);
+  std::vector<RowWork> whole = pieces;
+  const int64_t n_cut = cut_items(items, half, pieces);
+  if (n_cut == n_whole) return c;
+  return 1.05 * makespan(pieces, lanes) + merge_tiles(n_cut - n_whole, kv_heads) < makespan(whole, lanes) ? half : c;
 }
 
 }  // namespace
@@ -163,12 +251,8 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     const bool dedupe = !(flags & TL_PLAN_WALK_REPEATS);
     std::vector<int32_t> walked_by(dedupe ? pool->n_slots : 0, 0);
     int32_t walker = 0;
-    struct Walk {
-      int32_t slots;
-      int64_t kv_tiles;
-    };
     auto walk_of = [&](int32_t r, int32_t begin, int32_t end) {
-      Walk w{0, 0};
+      Walk w{0, 0, 0};
       ++walker;
       for (int32_t pos = begin; pos < end; ++pos) {
         const int32_t sl = slot_at(r, pos);
@@ -177,6 +261,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
           walked_by[sl] = walker;
         }
         ++w.slots;
+        w.tokens += pool->fill[sl];
         w.kv_tiles += (pool->fill[sl] + kKvTile - 1) / kKvTile;
       }
       return w;
@@ -190,9 +275,8 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     // Requests with a token's worth of rows (decode) always take split-K units.
     const int tok_tile = kRowTile / G;
     const int64_t n_cu = compute_units < 0 ? kComputeUnits : compute_units;
-    const int32_t min_chunk_slots = std::max(1, 2048 / pool->seg_len);
+    const int32_t min_chunk_slots = std::max(1, kMinPieceTiles * kKvTile / pool->seg_len);
     std::vector<char> fused(n_req, 0);
-    std::vector<char> alone(n_req, 0);             // on the three steps, but in no run shared with others
     // A one-pass row tile cannot be cut along its KV: when the whole batch is fewer row-tile
     // workgroups than the GPU has CUs (one long prompt, say), requests whose slot lists are long
     // enough to be cut (see below) stay on the three-step path
@@ -223,61 +307,6 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         for (int32_t pos = 0; pos < len_of(r) && !shares; ++pos) shares = users[slot_at(r, pos)] > 1;
         fused[r] = rows >= kFuseRows || !shares;
       }
-      // In a batch that also has split-K units (one that is all one-pass rows stays so: its caller may make the
-      // one-pass call alone): one-pass rows whose lists differ much in length leave CUs idle behind the longest, which cannot be
-      // cut; and they run after the batch's split-K units, in a launch of their own.  On the three steps long
-      // lists are cut, and row tiles and units share a launch, in which the units cost the CUs they need to
-      // saturate HBM (about three fifths of them) rather than all.  The cheaper of the two by this estimate, the
-      // one-pass rows unless the three steps are a tenth cheaper.  (4 prefill chunks of 300 to 600 tokens on
-      // 1.5k to 15k beside 48 decoded tokens: 582 us as one-pass rows, 541 us in three steps; of random mixes
-      // 8 chunks of 64 to 124 beside 67 decoded tokens on 2.9k to 23k 1061 and 833 us, 4 chunks of up to 231 beside
-      // 79 of a 28-on-4-head layer 975 and 577 us; 16 chunks of 512 on 8k to 32k stay one-pass.)
-      if (n_cu > 0 && !(flags & TL_PLAN_FUSE_TAILS)) {
-        const int64_t lanes = std::max<int64_t>(1, n_cu / pool->kv_heads);
-        std::vector<RowWork> one_pass, causal, pool_part;
-        int64_t n_fused = 0, load = 0;
-        for (int32_t r = 0; r < n_req; ++r) {
-          if (!fused[r]) continue;
-          const int64_t kv = walk_of(r, 0, len_of(r)).kv_tiles;
-          const int64_t n_row = (ntok_of(r) + tok_tile - 1) / tok_tile;
-          ++n_fused;
-          load += kv * n_row;
-          for (int64_t i = 0; i < n_row; ++i) {
-            const int64_t self = (std::min<int64_t>((i + 1) * tok_tile, ntok_of(r)) + kKvTile - 1) / kKvTile;
-            one_pass.push_back(RowWork{kv + self, 1});
-            causal.push_back(RowWork{self, 1});
-          }
-          if (kv > 0) pool_part.push_back(RowWork{kv, n_row});
-        }
-        if (n_fused > 0 && !pool_part.empty()) {
-          int64_t unit_tokens = 0;          // of the split-K units, each slot once
-          for (int32_t r = 0; r < n_req; ++r)
-            if (ntok_of(r) > 0 && (int64_t)ntok_of(r) * G <= kUnitRows)
-              for (int32_t pos = 0; pos < len_of(r); ++pos)
-                if (int32_t& u = users[slot_at(r, pos)]; u > 0) {
-                  unit_tokens += pool->fill[slot_at(r, pos)];
-                  u = 0;
-                }
-          const double units = (double)unit_tokens * pool->kv_heads * (4 * kHeadDim) / kBytesPerTile;
-          double partial_rows = 0;
-          const int64_t mean = load / lanes;
-          for (RowWork& w : pool_part) {
-            const int64_t n = pieces_of(w.kv_tiles, mean);
-            partial_rows += (double)(n + 1) * w.row_tiles * kRowTile;
-            w.kv_tiles = (w.kv_tiles + n - 1) / n;
-            w.row_tiles *= n;
-          }
-          const double merge = partial_rows * pool->kv_heads * (2 * 4 * kHeadDim) / kBytesPerTile;     // written and read
-          const double as_one_pass = makespan(one_pass, lanes) + units;
-          const double as_three = makespan(pool_part, lanes) + 0.6 * units + makespan(causal, lanes) + merge + kThreeStepLaunches;
-          if (unit_tokens > 0 && as_three < 0.9 * as_one_pass)
-            for (int32_t r = 0; r < n_req; ++r)
-              if (fused[r] && len_of(r) > 0) {
-                fused[r] = 0;
-                alone[r] = 1;
-              }
-        }
-      }
     }
     // ---- walk the prefix tree ---------------------------------------------------------------------
     // every request with a list, in order, front to back; `grouped` requests are those the planner
@@ -288,7 +317,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     if ((int64_t)tree.size() > (int64_t)kTreeNodesPerSlot * pool->n_slots) tree.reset(pool->n_slots);
     tree.begin_batch();
     std::vector<int32_t> path(n_entries);          // tree node of every list entry
-    auto is_live = [&](int32_t r) { return ntok_of(r) > 0 && len_of(r) > 0 && !fused[r] && !alone[r]; };
+    auto is_live = [&](int32_t r) { return ntok_of(r) > 0 && len_of(r) > 0 && !fused[r]; };
     for (int32_t r = 0; r < n_req; ++r) {
       const bool grouped = is_live(r);
       int32_t node = 0;
@@ -363,9 +392,122 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         }
     }
 
-    // (their rows are many enough: sharing a run would cut their lists at every fork and add partials)
-    for (int32_t r = 0; r < n_req; ++r)
-      if (alone[r]) raw.push_back(RawItem{{r}, r, 0, len_of(r)});
+    // An item goes to split-K units if it has a token's worth of rows, or if it is a run shared by
+    // decode-type requests only (each with a token's worth of rows) that together would not fill
+    // one row tile: such a run has too little arithmetic for a row tile to matter and, as a handful
+    // of workgroups in a launch of its own, would only add its latency to the step.  Its tokens are
+    // then dealt to units of kUnitRows rows, which re-read the run through L2.
+    const int32_t tok_unit = std::max(1, kUnitRows / G);
+    auto unit_item = [&](const RawItem& it, int64_t n_tok) -> bool {
+      if (n_tok * G <= kUnitRows) return true;
+      if (n_tok * G > kRowTile) return false;
+      for (int32_t r : it.reqs)
+        if ((int64_t)ntok_of(r) * G > kUnitRows) return false;
+      return true;
+    };
+    auto tok_of = [&](const RawItem& it) {
+      int64_t n_tok = 0;
+      for (int32_t r : it.reqs) n_tok += ntok_of(r);
+      return n_tok;
+    };
+
+    int split = split_segments;
+    if (split == 0) {
+      // Split-K chunk, in slots.  Measured on decode batches of 1 to 1024 requests: long chunks stream
+      // best (2 slots 5.6 TB/s, 8 slots 6.0, 32 slots 6.1, and fewer partials to merge), as long as
+      // there are about as many units as CUs or more; equal-sized units that overflow one round of CUs
+      // by a little leave a thin second round that cannot fill the memory system.  So: the longest
+      // chunk (at most 32 slots, at least 512 tokens) that still gives three quarters of a unit per
+      // CU, halved if the count then lands between one and one and a half rounds.
+      std::vector<std::pair<int64_t, int64_t>> runs;     // (list entries, token groups) of every unit item
+      for (const RawItem& it : raw) {
+        const int64_t n_tok = tok_of(it);
+        if (unit_item(it, n_tok)) runs.emplace_back(it.end - it.begin, (n_tok + tok_unit - 1) / tok_unit);
+      }
+      auto units_with = [&](int sp) {
+        int64_t u = 0;
+        for (const auto& r : runs) u += (r.first + sp - 1) / sp * r.second;
+        return u;
+      };
+      const int lo = std::max(1, 512 / pool->seg_len);
+      const int64_t cus = n_cu > 0 ? n_cu : kComputeUnits;
+      split = 32;
+      while (split > lo && 4 * units_with(split) < 3 * cus) --split;
+      const int64_t u = units_with(split);
+      if (u > cus && 2 * u < 3 * cus && split >= 2 * lo) split /= 2;
+    }
+
+    // ---- one-pass rows beside split-K units --------------------------------------------------
+    // In a batch that also has split-K units (one that is all one-pass rows stays so: its caller may make the
+    // one-pass call alone): one-pass rows whose lists differ much in length leave CUs idle behind the longest, which cannot
+    // be cut, in a launch of their own behind the units'.  On the three steps their lists can be cut and share the units'
+    // launch: each such request becomes a work item of its own (its rows are many enough: sharing a run would cut its
+    // list at every fork and add partials).  Both plans are weighed as they would be built, with the same pieces and
+    // the units' time in both; the one-pass rows stay unless the three steps are 6 % cheaper.  Of the 758 batches 325 leave
+    // the one-pass kernel: 0.51 to 1.05 of its time, 0.79 in the mean, four of them slower by more than 2 % (8 chunks of up to
+    // 211 tokens beside 42 decoded ones on 3.9k to 31k 1174 and 832 us).  The line is where it is for those four: of the
+    // batches that stay, 47 would have gained a tenth or more.
+    RowCut row_cut;
+    bool row_cut_known = false;
+    if (n_cu > 0 && !(flags & TL_PLAN_FUSE_TAILS) && std::find(fused.begin(), fused.end(), 1) != fused.end()) {
+      int64_t unit_tokens = 0;
+      UnitLoad load;
+      std::vector<RowItem> kept;           // row-tile items of either plan
+      for (const RawItem& it : raw) {
+        const int64_t n_tok = tok_of(it);
+        const Walk w = walk_of(it.src_req, it.begin, it.end);
+        if (unit_item(it, n_tok)) {
+          const int64_t groups = (n_tok + tok_unit - 1) / tok_unit;
+          unit_tokens += w.tokens;
+          load.units += (w.slots + split - 1) / split * groups;
+          load.tokens += w.tokens * groups;
+          load.longest = std::max(load.longest, w.tokens * std::min(split, w.slots) / std::max(1, w.slots));
+        } else {
+          kept.push_back(RowItem{w, (n_tok + tok_tile - 1) / tok_tile});
+        }
+      }
+      // (units of less than a fifth of a tile's time, a token or two on short prefixes, are no launch to share)
+      const double units = (double)unit_tokens * pool->kv_heads * (4 * kHeadDim) / kUnitBytesPerTile;
+      if (units >= 0.2) {
+        const int64_t lanes = std::max<int64_t>(1, n_cu / pool->kv_heads);
+        std::vector<RowItem> all = kept;
+        std::vector<RowWork> one_pass, causal;
+        int64_t self_rows = 0;
+        for (int32_t r = 0; r < n_req; ++r) {
+          if (!fused[r] || len_of(r) == 0) continue;
+          const Walk w = walk_of(r, 0, len_of(r));
+          const int64_t n_row = (ntok_of(r) + tok_tile - 1) / tok_tile;
+          all.push_back(RowItem{w, n_row});
+          self_rows += n_row;
+          for (int64_t i = 0; i < n_row; ++i) {
+            const int64_t self = (std::min<int64_t>((i + 1) * tok_tile, ntok_of(r)) + kKvTile - 1) / kKvTile;
+            one_pass.push_back(RowWork{w.kv_tiles + self, 1});
+            causal.push_back(RowWork{self, 1});
+          }
+        }
+        if (self_rows > 0) {
+          const int64_t unit_blocks = load.units * unit_head_blocks(pool->kv_heads, plan_unit_heads_log2(pool->kv_heads, load, n_cu));
+          std::vector<RowWork> pieces;
+          const RowCut cut_kept = plan_row_cut(kept, n_cu, pool->kv_heads, pool->seg_len);
+          const RowCut cut_all = plan_row_cut(all, n_cu, pool->kv_heads, pool->seg_len);
+          const int64_t rows_kept = cut_items(kept, cut_kept, pieces);
+          const double as_one_pass = joint_tiles(units, unit_blocks, makespan(pieces, lanes), n_cu) + makespan(one_pass, lanes) + kOnePassLaunch;
+          const int64_t rows_all = cut_items(all, cut_all, pieces);
+          const double as_three = joint_tiles(units, unit_blocks, makespan(pieces, lanes), n_cu) + 1.3 * makespan(causal, lanes) +
+                                  1.2 * merge_tiles(rows_all - rows_kept + self_rows, pool->kv_heads) + kThreeStepLaunches;
+          row_cut_known = true;
+          row_cut = cut_kept;
+          if (as_three < 0.94 * as_one_pass) {
+            row_cut = cut_all;
+            for (int32_t r = 0; r < n_req; ++r)
+              if (fused[r] && len_of(r) > 0) {
+                fused[r] = 0;
+                raw.push_back(RawItem{{r}, r, 0, len_of(r)});
+              }
+          }
+        }
+      }
+    }
 
     // The kv tokens of a slot list as tiles of kKvTile rows.  A slot listed several times (lists are
     // multisets: Section 3.1 has no order or uniqueness among the segments a request attends to) is
@@ -432,88 +574,15 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     }
 
     // ---- final items, work lists ----------------------------------------------------------
-    // An item goes to split-K units if it has a token's worth of rows, or if it is a run shared by
-    // decode-type requests only (each with a token's worth of rows) that together would not fill
-    // one row tile: such a run has too little arithmetic for a row tile to matter and, as a handful
-    // of workgroups in a launch of its own, would only add its latency to the step.  Its tokens are
-    // then dealt to units of kUnitRows rows, which re-read the run through L2.
-    const int32_t tok_unit = std::max(1, kUnitRows / G);
-    auto unit_item = [&](const RawItem& it, int64_t n_tok) -> bool {
-      if (n_tok * G <= kUnitRows) return true;
-      if (n_tok * G > kRowTile) return false;
-      for (int32_t r : it.reqs)
-        if ((int64_t)ntok_of(r) * G > kUnitRows) return false;
-      return true;
-    };
-    int split = split_segments;
-    if (split == 0) {
-      // Split-K chunk, in slots.  Measured on decode batches of 1 to 1024 requests: long chunks stream
-      // best (2 slots 5.6 TB/s, 8 slots 6.0, 32 slots 6.1, and fewer partials to merge), as long as
-      // there are about as many units as CUs or more; equal-sized units that overflow one round of CUs
-      // by a little leave a thin second round that cannot fill the memory system.  So: the longest
-      // chunk (at most 32 slots, at least 512 tokens) that still gives three quarters of a unit per
-      // CU, halved if the count then lands between one and one and a half rounds.
-      std::vector<std::pair<int64_t, int64_t>> runs;     // (list entries, token groups) of every unit item
+    if (!row_cut_known) {
+      std::vector<RowItem> items;
       for (size_t i = 0; i < raw.size(); ++i) {
-        const RawItem& it = raw[i];
-        if (is_tail_item[i]) continue;
-        int64_t n_tok = 0;
-        for (int32_t r : it.reqs) n_tok += ntok_of(r);
-        if (unit_item(it, n_tok)) runs.emplace_back(it.end - it.begin, (n_tok + tok_unit - 1) / tok_unit);
+        const int64_t n_tok = is_tail_item[i] ? 0 : tok_of(raw[i]);
+        if (n_tok > 0 && !unit_item(raw[i], n_tok))
+          items.push_back(RowItem{walk_of(raw[i].src_req, raw[i].begin, raw[i].end), (n_tok + tok_tile - 1) / tok_tile});
       }
-      auto units_with = [&](int sp) {
-        int64_t u = 0;
-        for (const auto& r : runs) u += (r.first + sp - 1) / sp * r.second;
-        return u;
-      };
-      const int lo = std::max(1, 512 / pool->seg_len);
-      const int64_t cus = n_cu > 0 ? n_cu : kComputeUnits;
-      split = 32;
-      while (split > lo && 4 * units_with(split) < 3 * cus) --split;
-      const int64_t u = units_with(split);
-      if (u > cus && 2 * u < 3 * cus && split >= 2 * lo) split /= 2;
+      row_cut = plan_row_cut(items, n_cu, pool->kv_heads, pool->seg_len);
     }
-    // Row-tile items of a small batch: when all row tiles together are fewer workgroups than the
-    // GPU has CUs, long slot lists are cut into chunks (each a work item with partial rows of its
-    // own, merged like any other) until there are about two workgroups per CU; a chunk keeps at
-    // least 2048 tokens so that its start-up stays small against its work.  With more row tiles than that,
-    // lists longer than half the mean load of a CU are cut if that ends the launch earlier by more than the
-    // partials cost (lists of unequal length, or a little more than a whole number of rounds).
-    int tile_chunks = 1;
-    int64_t longest_piece = 0;           // in KV tiles; 0: not cut
-    {
-      int64_t wgs = 0, load = 0;
-      double cut_rows = 0;
-      std::vector<RowWork> whole, cut;
-      for (size_t i = 0; i < raw.size(); ++i) {
-        const RawItem& it = raw[i];
-        if (is_tail_item[i]) continue;
-        int64_t n_tok = 0;
-        for (int32_t r : it.reqs) n_tok += ntok_of(r);
-        if (unit_item(it, n_tok)) continue;
-        const int64_t n_row = (n_tok + tok_tile - 1) / tok_tile;
-        wgs += n_row * pool->kv_heads;
-        whole.push_back(RowWork{walk_of(it.src_req, it.begin, it.end).kv_tiles, n_row});
-        load += whole.back().kv_tiles * n_row;
-      }
-      if (wgs > 0 && wgs < n_cu) tile_chunks = (int)std::min<int64_t>(16, (2 * n_cu + wgs - 1) / wgs);
-      if (n_cu > 0 && wgs >= n_cu) {
-        const int64_t lanes = std::max<int64_t>(1, n_cu / pool->kv_heads), mean = load / lanes;
-        for (const RowWork& w : whole) {
-          const int64_t n = pieces_of(w.kv_tiles, mean);
-          cut_rows += (double)(n - 1) * w.row_tiles * kRowTile;
-          cut.push_back(RowWork{(w.kv_tiles + n - 1) / n, w.row_tiles * n});
-        }
-        const double merge = cut_rows * pool->kv_heads * (2 * 4 * kHeadDim) / kBytesPerTile;
-        if (cut_rows > 0 && 1.05 * makespan(cut, lanes) + merge < makespan(whole, lanes))
-          longest_piece = std::max<int64_t>(2048 / kKvTile, mean / 2);
-      }
-    }
-    auto even_step = [&](const Walk& w) -> int32_t {       // slots per piece
-      if (longest_piece == 0) return w.slots;
-      const int64_t n = std::max<int64_t>(1, (w.kv_tiles + longest_piece - 1) / longest_piece);
-      return (int32_t)((w.slots + n - 1) / n);
-    };
     int32_t row_cursor = 0;
     const int32_t own_toks = (flags & TL_PLAN_SELF_BLOCK) ? T : 0;      // the token array: every token in order, then the items' tokens
     p->item_tok_ptr.push_back(0);
@@ -524,8 +593,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     for (size_t ri = 0; ri < raw.size(); ++ri) {
       const RawItem& it = raw[ri];
       if (is_tail_item[ri]) continue;
-      int32_t n_tok = 0;
-      for (int32_t r : it.reqs) n_tok += ntok_of(r);
+      const int32_t n_tok = (int32_t)tok_of(it);
       const bool few_rows = unit_item(it, n_tok);
       // Pieces are cut from the slots that the run walks, not from its list: a piece of the list would
       // walk again what another piece names too.
@@ -533,7 +601,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       bool cut = few_rows;
       if (!few_rows) {
         const Walk w = walk_of(it.src_req, it.begin, it.end);
-        step = tile_chunks > 1 ? std::max(min_chunk_slots, (w.slots + tile_chunks - 1) / tile_chunks) : even_step(w);
+        step = row_cut.step(w);
         cut = step < w.slots;
         if (!cut) step = it.end - it.begin;
       }

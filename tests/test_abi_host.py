@@ -347,6 +347,28 @@ def test_uneven_chunks_beside_decode_leave_the_one_pass_kernel(heads):
     assert plan_of(900, 30000, 40, 0)[0].n_fused_tokens == 600 * n_chunk
 
 
+@pytest.mark.parametrize("case", ["heavy decode", "cannot be cut", "can be cut"])
+def test_chunks_beside_decode_leave_the_one_pass_kernel_for_a_plan_that_gains(case):
+    """What moves prefill chunks to the three steps is the plan that would be built there.  Short even chunks
+    beside decode work of many times their size cannot gain; lists of one long segment have nowhere to be
+    cut (beside units that leave no CU idle); the same lists in segments of 256 tokens are cut."""
+    n_chunk, new, n_decode, C = (2, 512, 200, 256) if case == "heavy decode" else (10, 300, 64, 256 if case == "can be cut" else 16384)
+    if case == "heavy decode":
+        lengths = [1024] * n_chunk + [16384] * n_decode
+    else:
+        lengths = [16384] + [300] * (n_chunk - 1) + [4096] * n_decode
+    lists, fills = wl._lists_from_lengths(lengths, C)
+    b = wl._finish("route", 3, 32, 8, C, sum(len(l) for l in lists), [new] * n_chunk + [1] * n_decode, lists, fills, np.random.default_rng(0))
+    plan_pool[0] = _pool_for(b)
+    flags = B.TL_PLAN_SELF_BLOCK | B.TL_PLAN_FUSE_ROWS
+    plan = B.tl_plan_create(plan_pool[0], b.q_heads, b.req_row_ptr, b.req_seg_ptr, b.seg_ids, flags)
+    info = B.tl_plan_get_info(plan)
+    _check_plan_covers(b, plan, flags, fused_req=tuple(range(n_chunk)) if info.n_fused_tokens else ())
+    assert info.n_fused_tokens == (0 if case == "can be cut" else n_chunk * new)
+    B.tl_plan_destroy(plan)
+    B.tl_pool_destroy(plan_pool[0])
+
+
 @pytest.mark.parametrize("n_chunk,new,n_decode,fuse,compute_units", [
     (1, 300, 0, False, -1),        # fewer row tiles than CUs: about two pieces per CU
     (5, 300, 0, False, -1),        # lists of uneven lengths
