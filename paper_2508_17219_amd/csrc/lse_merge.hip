@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict_
 // accumulates with the same weights w_j = exp(LSE_j - M) as the kernel above, and slice 0 adds
 // the slices up in a fixed order.
 constexpr int kMergeSlices = 8;
-constexpr int64_t kMidMergePairs = 4096;    // (token, head) pairs from which lists of 8 to 15 partials are worth a launch
+constexpr int64_t kMidMergePairs = 8192;    // (token, head) pairs beyond which lists of 8 to 15 partials are worth a launch
 template <bool OUT_BF16>
 __global__ __launch_bounds__(32 * kMergeSlices) void lse_merge_sliced_kernel(
     const float* __restrict__ part, const float* __restrict__ lse, const int32_t* __restrict__ mptr,
@@ -392,10 +392,12 @@ tl_status tl_merge(tl_plan* plan, const float* out_partial, const float* lse, vo
   const PlanDev d = plan_dev(plan, plan->blob_dev);
   // Lists of 8 to 15 partials (a prompt's list cut into pieces) take a launch of the plain kernel: 9 partials for
   // each of 512 tokens x 32 heads, 75 MB, 15 us there against 27 us from the slices.  A few such tokens beside long
-  // lists (a decode batch) go with those: below some 4096 (token, head) pairs a launch of their own costs more.
+  // lists (a decode batch) go with those, up to 8192 (token, head) pairs: with 12 partials each beside 4 long lists,
+  // 4096 pairs 7.6 to 8.3 us in one launch, 8.9 to 9.1 in two; 8192 15.4 and 15.5; 16384 27.2 and 23.4.  Without long
+  // lists either is one launch, and the plain kernel as fast or faster (6 us up to 2048 pairs; 4096 5.9 and 7.9).
   const int n_short = plan->n_merge_short;
   int n_mid = plan->n_merge_mid, n_long = (int)plan->merge_tok.size() - n_short - n_mid;
-  if (n_long > 0 && (int64_t)n_mid * plan->q_heads < kMidMergePairs) {
+  if (n_long > 0 && (int64_t)n_mid * plan->q_heads <= kMidMergePairs) {
     n_long += n_mid;
     n_mid = 0;
   }

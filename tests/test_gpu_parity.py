@@ -1321,7 +1321,9 @@ def test_uneven_chunks_beside_decode_against_the_oracle():
     ([6, 7, 14], 8, False),                          # lists of 7, 8 and 15 partials: fixed records, plain kernel; no long list
     ([6, 7, 14], 8, True),
     ([6, 7, 14, 15, 16], 8, True),                   # a few lists of 8 and 15 beside long ones go with those
-    ([7] * 60 + [14] * 6 + [15, 3], 64, False),      # 66 tokens x 64 heads of 8 and 15 beside long ones: a launch of their own
+    ([7] * 60 + [14] * 6 + [15, 3], 64, False),      # 66 tokens x 64 heads of 8 and 15 beside long ones: still with those
+    ([7] * 122 + [14] * 6 + [15, 3], 64, False),     # 8192 (token, head) pairs: the last that go with them
+    ([7] * 122 + [14] * 7 + [15, 3], 64, True),      # one token more: a launch of their own
 ])
 def test_merge_lists_at_the_edges_of_their_kernels(segs, q_heads, out_bf16):
     """Decode tokens with one partial per segment and one for themselves: every row against the oracle."""
