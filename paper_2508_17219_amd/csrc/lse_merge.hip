@@ -328,8 +328,9 @@ tl_status tl_segment_attn(const tl_pool* pool, tl_plan* plan, const void* q_dev,
   a.n_work = (int)plan->tiles.size();
   a.units = d.units;
   a.n_units = (int)plan->units.size();
-  // (a grid beyond 2^30 blocks would not fit the joint launch's block numbers)
-  if (a.n_work > 0 && a.n_units > 0 && ((int64_t)a.n_work + a.n_units) * a.kv_heads < (1 << 30)) return launch_tiles_and_units(a, st);
+  // (a launch has less than 2^32 threads: 2^23 blocks of 512, the unit blocks rounded up to a multiple of 8)
+  const int64_t blocks = (int64_t)a.n_work * a.kv_heads + (int64_t)a.n_units * unit_head_blocks(a.kv_heads, a.unit_heads_log2) + 7;
+  if (a.n_work > 0 && a.n_units > 0 && blocks < (1 << 23)) return launch_tiles_and_units(a, st);
   rc = launch_pool_row_tiles(a, a.n_work, st);
   if (rc != TL_OK) return rc;
   a.work = d.units;
