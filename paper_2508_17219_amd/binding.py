@@ -113,7 +113,15 @@ def _host(a, dtype) -> np.ndarray:
     return np.ascontiguousarray(np.asarray(a), dtype=dtype)
 
 
-_raw_stream = None      # (device index) -> handle of torch's current stream there, once torch can use a GPU
+_raw_stream = None      # () -> handle of torch's current stream, once torch can use a GPU
+
+
+def _stream_getter(torch):
+    """torch's own getters where this torch has them: they are not part of its public interface."""
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
 
 
 def _stream(stream) -> Optional[int]:
@@ -126,8 +134,8 @@ def _stream(stream) -> Optional[int]:
             if not torch.cuda.is_available():
                 return None
             torch.cuda.init()
-            _raw_stream = torch._C._cuda_getCurrentRawStream
-        return _raw_stream(torch._C._cuda_getDevice()) or None
+            _raw_stream = _stream_getter(torch)
+        return _raw_stream() or None
     return int(stream) or None
 
 

@@ -517,6 +517,16 @@ def test_tile_pairs_count_each_distinct_slot_of_a_work_item_once():
         B.tl_plan_create(pool, b.q_heads, b.req_row_ptr, b.req_seg_ptr, b.seg_ids, flags, 0, 5000)   # compute_units above 4096
 
 
+def test_current_stream_without_torchs_private_getters():
+    """The getters that make the lookup cheap are private to torch: without either the public stream is asked."""
+    from types import SimpleNamespace as NS
+    cuda = NS(current_stream=lambda: NS(cuda_stream=77))
+    for private in ({}, {"_cuda_getDevice": lambda: 1}, {"_cuda_getCurrentRawStream": lambda d: 1}):
+        assert B._stream_getter(NS(_C=NS(**private), cuda=cuda))() == 77
+    both = {"_cuda_getDevice": lambda: 3, "_cuda_getCurrentRawStream": lambda d: 100 + d}
+    assert B._stream_getter(NS(_C=NS(**both), cuda=cuda))() == 103
+
+
 def test_plan_errors():
     b = wl.tiny()
     pool = _pool_for(b)
