@@ -879,7 +879,7 @@ def test_batched_append_equals_the_oracles_chain_by_chain_appends():
     for i, (s_, f) in enumerate(zip(slots, table.fill(slots))):
         assert np.array_equal(gkb[i, :f], opk[s_, :f]) and np.array_equal(gvb[i, :f], opv[s_, :f]), "slot %d" % s_
         assert not gkb[i, f:].any() and not gvb[i, f:].any()
-    # the device's fill table is what the attention kernels mask with: a plan over every chain
+    # what the attention kernels mask with are the fills that the plan took from the host's table: a plan over every chain
     lq = 3
     req_ids = [ch for ch in chains if ch]
     b_seg_ptr = np.concatenate([[0], np.cumsum([len(x) for x in req_ids])]).astype(np.int32)
@@ -1001,7 +1001,7 @@ def test_evicted_slots_are_reused_and_attended_over():
     releases, a plan that refreshes two segments, LRU evictions (same victims as the oracle), then
     tl_pool_append and tl_pool_put into the freed slots, the stale plan refused, and attention over
     lists that mix old segments with the ones now living in reused slots -- row tiles, one-pass rows
-    and split-K units (which read the live fill table) -- against the oracle's own table and pool."""
+    and split-K units (whose lists carry the slots' fills as of the plan) -- against the oracle's own table and pool."""
     _say("evict, reuse, attend")
     seed, hq, hkv, C, n_slots, d = 97, 8, 2, 64, 12, 128
     dev = "cuda"
