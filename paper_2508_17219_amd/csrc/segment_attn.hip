@@ -144,7 +144,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
       unit::splitk_unit<VREAD>(a, a.units[blockIdx.x % a.n_units], blockIdx.x / a.n_units, lds);
     return;
   }
-  const unsigned block = JOINT ? blockIdx.x - unit_blocks(a) : blockIdx.x;
+  const int block = JOINT ? (int)(blockIdx.x - unit_blocks(a)) : (int)blockIdx.x;   // (unsigned: 0.7 % slower on 128k lists, 6414 -> 6462 us)
   uint16_t* lds_k = lds;                 // [kBufs][64][kKS]
   uint16_t* lds_v = lds + kBufs * kKTile;    // [kBufs][64][kVS]
   int32_t* lds_idx = (int32_t*)(lds + kBufs * (kKTile + kVTile));   // [kIdxRing]
