@@ -131,11 +131,11 @@ __host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) {
 // JOINT (MODE 0): row tiles of the pool and split-K units in one launch: units first, which are bound by HBM and by their own
 // chain, then row tiles, which find the CUs that the units leave and finish evenly on all of them.  The first
 // row tile's block is a multiple of eight, so that a kv head stays on its XCD.  One launch after the other, the
-// first leaves CUs idle at its end and HBM idles through the row tiles: 5 chunks of up to 941 tokens beside 67 decoded
-// ones 407 us a step, together 372; 3 chunks of 64 to 438 beside 12, 266 and 239 us.  (Groups of eight blocks of each
-// kind in turn: a unit takes a whole round whatever runs beside it, so the units' second round ends late, 574 us
-// where units first are 510.)  The branch is in the kernel itself, not around a function that both kernels call: passed
-// to such a function, the block's number cost the one-pass kernel two spilled registers.
+// first leaves CUs idle at its end and HBM idles through the row tiles: 4 chunks of 300 to 600 tokens beside 48 decoded
+// ones 614 us a step, together 520; over 120 random batches tl_segment_attn takes 0.87 of its time in two launches, 0.99
+// at most.  (Groups of eight blocks of each kind in turn: a unit takes a whole round whatever runs beside it, so the
+// units' second round ends late, a tenth slower.)  The branch is in the kernel itself, not around a function that both
+// kernels call: passed to such a function, the block's number cost the one-pass kernel two spilled registers.
 template <int MODE, int VREAD, bool JOINT = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void row_tile_attn_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
