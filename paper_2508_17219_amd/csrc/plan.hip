@@ -43,14 +43,16 @@ struct UnitLoad {
 // More than half a round of units of one length is left alone, a thin second round costs more than the first
 // gains (168 units of 512 tokens, 8 heads: 55.9 us, halved 62.6); units of uneven length are halved up to three
 // quarters of a round, the shorter ones then fill the second (131 units of up to 512 tokens 35.7, halved 33.9).
-// Where 8 does not divide the heads, 8 to a workgroup with up to three waves idle is better for one round of even
-// units (227 units of 5 heads: 92 us, 102 with a workgroup per head; 118 of 12 heads 58 and 61; but 196 uneven units of
-// 5 heads 190 and 156).
+// Where 8 does not divide the heads, 8 to a workgroup with some waves idle (at most 7 of 16) is better for one round of even
+// units that dealt by a divisor would be more (227 units of 5 heads: 92 us, 102 with a workgroup per head; 118 of 12 heads
+// 58 and 61, of 9 heads 47 and 55; but 196 uneven units of 5 heads 190 and 156, and 64 of 12 heads, a round either way, 31.5 and 26.7).
 int32_t plan_unit_heads_log2(int32_t kv_heads, const UnitLoad& load, int64_t n_cu) {
-  const int32_t eights = unit_head_blocks(kv_heads, 3);
-  if (kv_heads % 8 && kv_heads >= 5 * eights && load.even() && 8 * load.units * eights > 3 * n_cu && load.units * eights <= n_cu) return 3;
   int32_t log2 = 3;
   while (kv_heads & ((1 << log2) - 1)) --log2;
+  const int32_t eights = unit_head_blocks(kv_heads, 3);
+  if (kv_heads % 8 && 2 * kv_heads >= 9 * eights && load.even() && 8 * load.units * eights > 3 * n_cu && load.units * eights <= n_cu &&
+      load.units * unit_head_blocks(kv_heads, log2) > n_cu)
+    return 3;
   while (log2 > 0 && 2 * load.units * unit_head_blocks(kv_heads, log2) <= n_cu) --log2;
   if (log2 > 0 && !load.even() && 4 * load.units * unit_head_blocks(kv_heads, log2) < 3 * n_cu) --log2;
   return log2;

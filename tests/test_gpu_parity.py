@@ -1171,7 +1171,7 @@ def test_split_k_units_with_their_waves_dealt_to_heads_and_slices(hq, hkv, compu
         run.close()
 
 
-@pytest.mark.parametrize("hq,hkv,compute_units", [(10, 5, 16), (12, 6, 16), (28, 7, 16), (24, 12, 24), (8, 8, 16), (4, 4, 16)])
+@pytest.mark.parametrize("hq,hkv,compute_units", [(10, 5, 16), (12, 6, 16), (28, 7, 16), (18, 9, 24), (24, 12, 24), (8, 8, 16), (4, 4, 16)])
 @pytest.mark.parametrize("chunk", [False, True])
 def test_split_k_units_of_one_length_in_one_round(hq, hkv, compute_units, chunk):
     """12 units of about one length, which fill half a round or more: head counts that 8 does not divide take 8 heads to
