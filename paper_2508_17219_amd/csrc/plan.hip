@@ -148,7 +148,7 @@ int64_t cut_items(const std::vector<RowItem>& items, const RowCut& cut, std::vec
   pieces.clear();
   for (const RowItem& it : items) {
     if (it.walk.slots == 0) continue;
-    const int64_t step = cut.step(it.walk), whole = it.walk.slots / step, rest = it.walk.slots % step;
+    const int64_t step = std::min(cut.step(it.walk), it.walk.slots), whole = it.walk.slots / step, rest = it.walk.slots % step;
     const int64_t kv = (it.walk.kv_tiles * step + it.walk.slots - 1) / it.walk.slots;
     pieces.push_back(RowWork{kv, whole * it.row_tiles});
     if (rest > 0) pieces.push_back(RowWork{std::max<int64_t>(1, it.walk.kv_tiles - kv * whole), it.row_tiles});
