@@ -46,6 +46,7 @@ struct AttnArgs {
   const float* prior_lse;     // [rows, q_heads]
   float* out;             // [rows, q_heads, 128]
   float* lse;             // [rows, q_heads]
+  int32_t n_tokens;       // rows of the new tokens' K/V
   int32_t q_heads, kv_heads, group, n_work;   // group = q_heads / kv_heads
   const Work* units;      // row tiles and split-K units in one launch: the units (work: the row tiles)
   int32_t n_units;

@@ -213,6 +213,7 @@ void fill_args(AttnArgs& a, const tl_plan* plan, const PlanDev& d, const void* q
   a.n_units = 0;
   a.out = out;
   a.lse = lse;
+  a.n_tokens = plan->n_tokens;
   a.q_heads = plan->q_heads;
   a.kv_heads = plan->kv_heads;
   a.group = plan->group;

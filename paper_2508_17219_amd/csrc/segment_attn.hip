@@ -28,7 +28,10 @@
 // -- the workgroup discards the result and redoes the full tiles on the careful path.
 // Careful path (tiles cut short by a slot's fill, tiles on the causal diagonal, and the
 // redo): one tile at a time, masked, running maximum raised (and O rescaled) when a block
-// exceeds it by more than 2^8.
+// exceeds it by more than 2^8; the next tile streams into the same LDS buffers meanwhile, and the first one
+// comes behind the fast path's last tile as if it were one more of them, so that nothing waits for it.
+// (Staged through registers, a masked tile cost 8.2k cycles, three of the fast path's; now 5.7k, with the phase's first loads
+// issued ahead of its lists: 8 prompts of 700 to 4096 tokens 559 -> 548 us, 7 of 261 to 1044 with 16 heads 55.2 -> 50.5.)
 // Repeated slots: a work item's list may name a slot several times (a multiset); the plan's tile
 // lists hold each distinct slot once with log2 of its multiplicity, which is added to the exponent
 // of the tile's probabilities (m equal keys weigh m exp(s) in numerator and denominator alike).
@@ -60,8 +63,6 @@ namespace {
 constexpr int kRG = 1;                                    // 32-row groups per wave
 constexpr int kWaves = kRowTile / (32 * kRG);             // 8
 constexpr int kThreads = 64 * kWaves;                     // 512
-constexpr int kChunks = kKvTile * 16 / kThreads;          // 16-byte chunks per thread per K (or V) tile: 2
-constexpr int kChunkRows = kThreads / 16;                 // rows covered by one chunk index: 32
 constexpr int kKS = kHeadDim;        // K row stride in LDS (bf16): unpadded, 16-byte chunks swizzled
 constexpr int kVS = kHeadDim;        // V row stride in LDS (bf16): unpadded, 16-byte chunks swizzled
 constexpr int kKTile = kKvTile * kKS;
@@ -156,8 +157,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int G = a.group;
-  const int first_token = a.tok[wk.tok_off];   // causal work: tokens of a tile are consecutive
   constexpr bool kHasPool = MODE != 1, kHasSelf = MODE != 0;
+  const int first_token = wk.tok_off;          // causal work: tokens of a tile are consecutive, and the token array starts with
+                                               // every token in order (one dependent load less before the queries)
   // K/V of the new tokens: the launch's main K/V for the causal block alone, the second pair when fused
   const uint16_t* self_k = MODE == 2 ? a.k2 : a.k;
   const uint16_t* self_v = MODE == 2 ? a.v2 : a.v;
@@ -171,8 +173,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     tok_local[rg] = row / G;                    // any group size: the last 256 % G rows of a tile are idle
     head_j[rg] = row - tok_local[rg] * G;
     row_ok[rg] = tok_local[rg] < wk.n_tok;
-    token[rg] = row_ok[rg] ? a.tok[wk.tok_off + tok_local[rg]] : -1;
+    token[rg] = !row_ok[rg] ? -1 : kHasSelf ? first_token + tok_local[rg] : a.tok[wk.tok_off + tok_local[rg]];
   }
+
+  // the last token that one of this wave's rows belongs to, -1 for a wave without rows (the item's last row tile)
+  const int n_rows = wk.n_tok * G, wave_row = __builtin_amdgcn_readfirstlane(wave) * (32 * kRG);
+  const int wave_last = wave_row >= n_rows ? -1 : first_token + (min(wave_row + 32 * kRG, n_rows) - 1) / G;
 
   // Q as the B operand: lane holds its row, head-dim elements 16 s + 8 h .. +7 of step s
   bf16x8 qreg[kRG][8];
@@ -218,35 +224,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   // first kv row of a full pool tile comes from the item's tile list, kept in an LDS ring (a
   // dependent global load per iteration would stall the wave); that of a full tile of new tokens
   // is arithmetic
-  auto ring_fill = [&](int first, int count) __attribute__((always_inline)) {   // entries [first, first+count) of the list, clipped
-    for (int i = first + tid; i < first + count && i < nf_pool; i += kThreads)
-    {
-      lds_idx[i & (kIdxRing - 1)] = a.tile_base[wk.full_off + i];
-      if (a.tile_lm) lds_lm[i & (kIdxRing - 1)] = a.tile_lm[wk.full_off + i];
+  auto ring_fill = [&](int first, int count) __attribute__((always_inline)) {   // entries [first, first+count) of the list
+    for (int i = first + tid; i < first + count && i < nf_pool + 1; i += kThreads) {
+      if (i < nf_pool) {
+        lds_idx[i & (kIdxRing - 1)] = a.tile_base[wk.full_off + i];
+        if (a.tile_lm) lds_lm[i & (kIdxRing - 1)] = a.tile_lm[wk.full_off + i];
+      } else if (np_pool > 0) {       // one entry more: the first tile cut short
+        lds_idx[i & (kIdxRing - 1)] = a.part_tile[2 * wk.part_off];
+      }
     }
   };
 
-  // ---- careful path staging (global -> registers -> LDS): kChunks chunks of 16 B per thread per
-  // tile, for K and for V; chunk i of a thread: tile row (tid >> 4) + kChunkRows i, 16-byte column tid & 15
   const size_t kv_row = (size_t)a.kv_heads * kHeadDim;
-  const int c_tr = tid >> 4, c_part = tid & 15;
-  // address = (tile's first row: workgroup-uniform, 64-bit, scalar registers) + (this thread's
-  // constant 32-bit offset inside a tile), so that a tile costs no per-lane 64-bit arithmetic
-  const unsigned lane_off0 = (unsigned)((c_tr * kv_row + (size_t)g * kHeadDim) * 2 + c_part * 16);
-  const unsigned chunk_step = (unsigned)(kChunkRows * kv_row * 2);
-  auto chunk_ptr = [&](const uint16_t* src, int base, int i) __attribute__((always_inline)) -> const uint4* {
-    const char* tile = (const char*)src + (size_t)__builtin_amdgcn_readfirstlane(base) * (kv_row * 2);
-    return (const uint4*)(tile + (lane_off0 + chunk_step * i));
-  };
-  auto lds_chunk_k = [&](uint16_t* tile, int i) __attribute__((always_inline)) -> uint4* {
-    const int r_ = c_tr + kChunkRows * i;
-    return (uint4*)&tile[r_ * kKS + 8 * (c_part ^ (r_ & 15))];
-  };
-  auto lds_chunk_v = [&](uint16_t* tile, int i) __attribute__((always_inline)) -> uint4* {
-    const int r_ = c_tr + kChunkRows * i;
-    return (uint4*)&tile[r_ * kVS + 8 * (c_part ^ (4 * (r_ & 3)))];
-  };
-  // ---- fast path staging: direct global -> LDS load of a whole tile.  A tile is 16 wave
+  // ---- staging: direct global -> LDS load of a whole tile.  A tile is 16 wave
   // instructions; wave w issues instructions w + kWaves u, instruction i filling rows 4 i .. 4 i + 3;
   // lane L lands at row 4 i + L / 16, position L % 16, so it fetches the logical chunk that belongs there
   unsigned dma_off_k[kDmaPerWave], dma_off_v[kDmaPerWave];
@@ -277,6 +267,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         : [sv] "=&s"(saved_m0)
         : [o0] "v"(off[0]), [o1] "v"(off[1]), [d0] "s"(dst0), [d1] "s"(dst1), [b] "s"(trow)
         : "memory");
+  };
+  // the same for the first `rows` rows of a tile; the others' places in LDS keep what they hold
+  auto dma_rows = [&](const uint16_t* src, int base, int rows, uint16_t* tile, const unsigned (&off)[kDmaPerWave]) __attribute__((always_inline)) {
+    const char* trow = (const char*)src + (size_t)__builtin_amdgcn_readfirstlane(base) * (kv_row * 2);
+#pragma unroll
+    for (int u = 0; u < kDmaPerWave; ++u) {
+      const unsigned dst = lds_base_addr + (unsigned)(tile - lds) * 2u + dma_wave_off + (unsigned)(u * kWaves * 4 * kHeadDim) * 2u;
+      unsigned saved_m0;
+      if (4 * (wave + kWaves * u) + (lane >> 4) < rows)
+        asm volatile("s_mov_b32 %[sv], m0\n\ts_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[o], %[b]\n\ts_mov_b32 m0, %[sv]"
+                     : [sv] "=&s"(saved_m0)
+                     : [o] "v"(off[u]), [d] "s"(dst), [b] "s"(trow)
+                     : "memory");
+    }
   };
   // wait for all of this wave's direct loads (vmcnt(0); the other counters are left alone so that
   // LDS operand reads already in flight stay in flight)
@@ -372,49 +376,94 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         for (int r = 0; r < 16; ++r) o[rg][d][r] *= alpha;
     }
   };
-  // careful path: one tile (rows beyond `valid` hidden; causal work also hides later tokens)
-  auto careful_tile = [&](auto SELF, const uint16_t* src_k, const uint16_t* src_v, int base, int valid, float lm) __attribute__((always_inline)) {
+  // Tiles that are masked or walked carefully, by number t in a phase's list: the kv row at the tile's first place, the
+  // places [lo, hi) that are the tile's, log2 of the multiplicity.  Pool: the full tiles, then those cut short by a
+  // fill; new tokens: in order.
+  struct Tile {
+    int base, lo, hi;
+    float lm;
+  };
+  auto tile_at = [&](auto SELF, int t) __attribute__((always_inline)) -> Tile {
+    if constexpr (decltype(SELF)::value) return {wk.kv_off + kKvTile * t, 0, min(kKvTile, wk.kv_len - kKvTile * t), 0.f};
+    if (t < nf_pool) return {unit::scalar_loads(a.tile_base)[wk.full_off + t], 0, kKvTile, a.tile_lm ? unit::scalar_loads(a.tile_lm)[wk.full_off + t] : 0.f};
+    const int pt = wk.part_off + t - nf_pool;
+    return {unit::scalar_loads(a.part_tile)[2 * pt], 0, unit::scalar_loads(a.part_tile)[2 * pt + 1], a.part_lm ? unit::scalar_loads(a.part_lm)[pt] : 0.f};
+  };
+  // where the fast path loads 64 rows for tile t of the new tokens: inside the memory (there is a full tile, hence 64 rows).
+  // (A pool tile's 64 rows are always its slot's: seg_len is a multiple of 64.)
+  auto self_load_base = [&](int t) __attribute__((always_inline)) -> int { return min(wk.kv_off + kKvTile * t, a.n_tokens - kKvTile); };
+  // a barrier for LDS alone: direct loads on their way stay on their way
+  auto lds_barrier = [&]() __attribute__((always_inline)) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  // careful path: tiles [from, to) of a phase, tile t in LDS buffers t % kBufs; the next tile is on its way while one is
+  // computed.  `loaded`: tile `from` is there already, fetched by the fast path behind its last full tile.
+  auto careful_tiles = [&](auto SELF, const uint16_t* src_k, const uint16_t* src_v, const int from, const int to, const bool loaded) __attribute__((always_inline)) {
     constexpr bool CAUSAL = decltype(SELF)::value;
-    {
-      // rows beyond `valid` are written as zero: 0 * garbage cannot make NaN
-      const uint4 z = make_uint4(0, 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < kChunks; ++i) {
-        const bool in = c_tr + kChunkRows * i < valid;
-        const uint4 kk = in ? *chunk_ptr(src_k, base, i) : z;
-        const uint4 vv = in ? *chunk_ptr(src_v, base, i) : z;
-        *lds_chunk_k(lds_k, i) = kk;
-        *lds_chunk_v(lds_v, i) = vv;
+    if (from >= to) return;
+    Tile cur = tile_at(SELF, from);
+    int buf = from % kBufs;
+    if (loaded) {
+      if constexpr (CAUSAL) {
+        cur.lo = cur.base - self_load_base(from);
+        cur.hi += cur.lo;
+        cur.base -= cur.lo;
       }
+    } else {
+      dma_rows(src_k, cur.base, cur.hi, lds_k + buf * kKTile, dma_off_k);
+      dma_rows(src_v, cur.base, cur.hi, lds_v + buf * kVTile, dma_off_v);
+      dma_wait();
+      lds_barrier();
     }
-    __syncthreads();
 #pragma unroll 1
-    for (int hb = 0; hb < 2; ++hb) {
-      if (32 * hb >= valid) break;              // uniform
-      f32x16 s[kRG];
-      qk_block(lds_k, hb, s);
-      bf16x8 pb[kRG][2];
-#pragma unroll
-      for (int rg = 0; rg < kRG; ++rg) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kv = 32 * hb + 8 * (r >> 2) + 4 * h + (r & 3);
-          bool hide = kv >= valid;
-          if (CAUSAL) hide = hide || (base + kv > token[rg]);
-          if (hide) s[rg][r] = -INFINITY;
-        }
-        maybe_rescale(rg, s[rg]);
-        if (m_ref[rg] == -INFINITY) {
-          // every key so far is hidden from this row: probabilities are zero
-          pb[rg][0] = pack_bf16x8(0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f);
-          pb[rg][1] = pb[rg][0];
-        } else {
-          exp_block(rg, s[rg], pb[rg], lm);
-        }
+    for (int t = from; t < to; ++t) {
+      const uint16_t* kt = lds_k + buf * kKTile;
+      uint16_t* vt = lds_v + buf * kVTile;
+      buf = buf + 1 == kBufs ? 0 : buf + 1;
+      Tile next = cur;
+      if (t + 1 < to) {
+        next = tile_at(SELF, t + 1);
+        dma_rows(src_k, next.base, next.hi, lds_k + buf * kKTile, dma_off_k);
+        dma_rows(src_v, next.base, next.hi, lds_v + buf * kVTile, dma_off_v);
       }
-      pv_block(lds_v, hb, pb);
+      if (cur.hi - cur.lo < kKvTile) {
+        // places of V that are not the tile's are zero: 0 * garbage cannot make NaN (their scores are hidden below)
+        for (int i = tid; i < 16 * kKvTile; i += kThreads)
+          if (i < 16 * cur.lo || i >= 16 * cur.hi) ((uint4*)vt)[i] = make_uint4(0, 0, 0, 0);
+        lds_barrier();
+      }
+#pragma unroll 1
+      for (int hb = 0; hb < 2; ++hb) {
+        if (32 * hb >= cur.hi || (CAUSAL ? cur.base + 32 * hb > wave_last : wave_last < 0)) break;   // wave-uniform
+        f32x16 s[kRG];
+        qk_block(kt, hb, s);
+        bf16x8 pb[kRG][2];
+#pragma unroll
+        for (int rg = 0; rg < kRG; ++rg) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int kv = 32 * hb + 8 * (r >> 2) + 4 * h + (r & 3);
+            bool hide = kv < cur.lo || kv >= cur.hi;
+            if (CAUSAL) hide = hide || (cur.base + kv > token[rg]);
+            if (hide) s[rg][r] = -INFINITY;
+          }
+          maybe_rescale(rg, s[rg]);
+          if (m_ref[rg] == -INFINITY) {
+            // every key so far is hidden from this row: probabilities are zero
+            pb[rg][0] = pack_bf16x8(0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f);
+            pb[rg][1] = pb[rg][0];
+          } else {
+            exp_block(rg, s[rg], pb[rg], cur.lm);
+          }
+        }
+        pv_block(vt, hb, pb);
+      }
+      dma_wait();
+      lds_barrier();
+      cur = next;
     }
-    __syncthreads();
   };
 
   // ======================= fast path: full tiles, software-pipelined by 32-token block =======================
@@ -426,9 +475,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   // kDepth groups earlier.  sched_barrier(0) after every group keeps the compiler to this order.
   // Runs the n_full (> 0) full tiles of one phase; have_ref says whether the exponent's reference
   // point exists already.  Returns false if the result overflowed and has to be discarded.
-  auto fast_phase = [&](auto SELF, const uint16_t* src_k, const uint16_t* src_v, const int n_full, const bool have_ref) __attribute__((always_inline)) -> bool {
+  // A masked tile behind the full ones (`more`) is fetched like one more of them.
+  auto fast_phase = [&](auto SELF, const uint16_t* src_k, const uint16_t* src_v, const int n_full, const bool more, const bool have_ref) __attribute__((always_inline)) -> bool {
     constexpr bool CAUSAL = decltype(SELF)::value;
-    auto full_base = [&](int t) __attribute__((always_inline)) -> int { return CAUSAL ? wk.kv_off + kKvTile * t : lds_idx[t & (kIdxRing - 1)]; };
+    auto full_base = [&](int t) __attribute__((always_inline)) -> int { return CAUSAL ? self_load_base(t) : lds_idx[t & (kIdxRing - 1)]; };
+    // the first loads leave before anything else: the list's first entries come by scalar loads
+    const int n_load = n_full + (more ? 1 : 0);
+    const int first_base = tile_at(SELF, 0).base;
+    dma_tile(src_k, first_base, lds_k, dma_off_k);
+    dma_tile(src_v, first_base, lds_v, dma_off_v);
+    if (n_load > 1) dma_tile(src_k, CAUSAL ? self_load_base(1) : tile_at(SELF, 1).base, lds_k + kKTile, dma_off_k);
     if (tid == 0) *lds_flag = 0;
     if (!CAUSAL) ring_fill(0, kIdxRing);
     {
@@ -436,10 +492,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
       const uint4 z = make_uint4(0, 0, 0, 0);
       for (int i = tid; i < kVTile / 8; i += kThreads) ((uint4*)(lds_v + (kBufs - 1) * kVTile))[i] = z;
     }
-    __syncthreads();
-    dma_tile(src_k, full_base(0), lds_k, dma_off_k);
-    dma_tile(src_v, full_base(0), lds_v, dma_off_v);
-    if (n_full > 1) dma_tile(src_k, full_base(1), lds_k + kKTile, dma_off_k);
     dma_wait();
     __syncthreads();
 
@@ -480,7 +532,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
 
     // first rows of the tiles that the coming iteration streams in, K(t+2) and V(t+1) (indices past
     // the end are clamped: such a value is never used for a load)
-    int base_k = full_base(min(2, n_full - 1)), base_v = full_base(min(1, n_full - 1));
+    int base_k = full_base(min(2, n_load - 1)), base_v = full_base(min(1, n_load - 1));
     // log2 of the multiplicity of the tile whose probabilities the coming iteration forms
     // (a.tile_lm is null when no list of the plan names a slot twice: then nothing is read)
     auto tile_lm = [&](int t) __attribute__((always_inline)) -> float { return CAUSAL || !a.tile_lm ? 0.f : lds_lm[t & (kIdxRing - 1)]; };
@@ -499,8 +551,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
       const uint16_t* v_p = lds_v + km1 * kVTile;    // V(t-1)
       if (!CAUSAL && t > 0 && (t & (kIdxRing / 2 - 1)) == 0) ring_fill(t + kIdxRing / 2, kIdxRing / 2);
       // K(t+2) replaces K(t-1), V(t+1) replaces V(t-2): both were last read before the previous barrier
-      if (t + 2 < n_full) dma_tile(src_k, base_k, lds_k + km1 * kKTile, dma_off_k);
-      if (t + 1 < n_full) dma_tile(src_v, base_v, lds_v + km2 * kVTile, dma_off_v);
+      if (t + 2 < n_load) dma_tile(src_k, base_k, lds_k + km1 * kKTile, dma_off_k);
+      if (t + 1 < n_load) dma_tile(src_v, base_v, lds_v + km2 * kVTile, dma_off_v);
       int base_k_next = 0, base_k_next_v = 0;
       float lm_next = 0.f;
       float nmc[kRG];               // exponent offset of this tile's probabilities: p = m 2^(c (s - m_ref))
@@ -512,7 +564,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         const int step = gq >> 4, gi = gq & 15, idx = gi >> 1;
         // read early and made wave-uniform well before the next iteration's start needs it
         if (gq == 6) {
-          base_k_next_v = full_base(min(t + 3, n_full - 1));
+          base_k_next_v = full_base(min(t + 3, n_load - 1));
           lm_next = tile_lm(min(t + 1, n_full - 1));
         }
         if (gq == 20) {
@@ -622,55 +674,36 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     return !redo;
   };
 
-  // ======================= the same tiles on the careful path =======================
+  // ======================= the phases =======================
+  // A phase is its full tiles on the fast path, then its masked ones.  Where the fixed reference fails the full
+  // tiles are walked carefully too; in the second phase everything so far is spoilt and starts again.
   const std::false_type kPoolPhase{};
   const std::true_type kSelfPhase{};
-  auto careful_pool_full = [&]() __attribute__((always_inline)) {
-    ring_fill(0, kIdxRing);
-    __syncthreads();
-    for (int t = 0; t < nf_pool; ++t) {
-      if (t > 0 && (t & (kIdxRing / 2 - 1)) == 0) {
-        __syncthreads();
-        ring_fill(t + kIdxRing / 2, kIdxRing / 2);
-        __syncthreads();
-      }
-      careful_tile(kPoolPhase, a.k, a.v, lds_idx[t & (kIdxRing - 1)], kKvTile, a.tile_lm ? lds_lm[t & (kIdxRing - 1)] : 0.f);
-    }
-  };
-  auto careful_pool_part = [&]() __attribute__((always_inline)) {   // tiles cut short by a slot's fill
-    for (int pt = 0; pt < np_pool; ++pt)
-      careful_tile(kPoolPhase, a.k, a.v, a.part_tile[2 * (wk.part_off + pt)], a.part_tile[2 * (wk.part_off + pt) + 1],
-                   a.part_lm ? a.part_lm[wk.part_off + pt] : 0.f);
-  };
-  auto careful_self = [&](int first_tile, int n_tiles) __attribute__((always_inline)) {
-    for (int t = first_tile; t < first_tile + n_tiles; ++t)
-      careful_tile(kSelfPhase, self_k, self_v, wk.kv_off + kKvTile * t, min(kKvTile, wk.kv_len - kKvTile * t), 0.f);
-  };
-
-  // ======================= the phases =======================
   if constexpr (kHasPool) {
-    const bool ok = nf_pool > 0 ? fast_phase(kPoolPhase, a.k, a.v, nf_pool, false) : true;
-    if (!ok) {
-      reset_state();
-      careful_pool_full();
+    int from = 0;
+    if (nf_pool > 0) {
+      if (fast_phase(kPoolPhase, a.k, a.v, nf_pool, np_pool > 0, false)) from = nf_pool;
+      else reset_state();
     }
-    careful_pool_part();
+    careful_tiles(kPoolPhase, a.k, a.v, from, nf_pool + np_pool, from > 0);
   }
   if constexpr (kHasSelf) {
-    const bool have_ref = kHasPool && nf_pool + np_pool > 0;
-    const bool ok = nf_self > 0 ? fast_phase(kSelfPhase, self_k, self_v, nf_self, have_ref) : true;
-    if (!ok) {   // everything so far is spoilt: start again, carefully
-      reset_state();
-      if constexpr (kHasPool) {
-        careful_pool_full();
-        careful_pool_part();
+    int from = 0;
+    if (nf_self > 0) {
+      if (fast_phase(kSelfPhase, self_k, self_v, nf_self, np_self > 0, kHasPool && nf_pool + np_pool > 0)) {
+        from = nf_self;
+      } else {
+        reset_state();
+        if constexpr (kHasPool) careful_tiles(kPoolPhase, a.k, a.v, 0, nf_pool + np_pool, false);
       }
-      careful_self(0, nf_self);
     }
-    careful_self(nf_self, np_self);   // tiles on the diagonal
+    careful_tiles(kSelfPhase, self_k, self_v, from, nf_self + np_self, from > 0);     // the last ones are on the diagonal
   }
 
-  // ---- epilogue: normalise, LSE, store ----
+  // ---- epilogue: normalise, LSE, store (its arguments are read here: held in scalar registers from the start they push
+  // others of the loop's out; the empty asm keeps the loads in this place) ----
+  auto args = (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));
 #pragma unroll
   for (int rg = 0; rg < kRG; ++rg) {
     const float l_tot = xor32_sum(l_run[rg]);
@@ -678,7 +711,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     if (row_ok[rg]) {
       float inv = lr_tot > 0.f ? 1.f / lr_tot : 0.f;
       const int head = g * G + head_j[rg];
-      float lse_val = l_tot > 0.f ? m_ref[rg] * a.scale + __logf(l_tot) : -INFINITY;
+      float lse_val = l_tot > 0.f ? m_ref[rg] * args->scale + __logf(l_tot) : -INFINITY;
       if (MODE == 2 && wk.n_prior > 0) {
         // One-pass tail: the row's partials in the work items above it (shared runs, computed by an
         // earlier launch) are merged in with the rule of the merge kernel,
@@ -692,12 +725,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         float M = lse_val, W = lse_val > -INFINITY ? 1.f : 0.f;
         const int tok_in_req = wk.out_row - wk.kv_off + tok_local[rg];
         for (int j = 0; j < wk.n_prior; ++j) {
-          const size_t prow = (size_t)(a.prior_rows[wk.prior_off + j] + tok_in_req) * a.q_heads + head;
-          const float L = a.prior_lse[prow];
+          const size_t prow = (size_t)(args->prior_rows[wk.prior_off + j] + tok_in_req) * args->q_heads + head;
+          const float L = args->prior_lse[prow];
           if (!(L > -INFINITY)) continue;              // a partial without keys has weight 0
           const float Mn = fmaxf(M, L);
           const float ea = M > -INFINITY ? __expf(M - Mn) : 0.f, eb = __expf(L - Mn);
-          const float* pp = a.prior_out + prow * kHeadDim;
+          const float* pp = args->prior_out + prow * kHeadDim;
 #pragma unroll
           for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -716,9 +749,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
       }
       if (MODE == 2) {
         // final output of the token, in the caller's layout and type
-        const size_t orow = (size_t)token[rg] * a.q_heads + head;
-        if (a.final_is_bf16) {
-          uint16_t* op = (uint16_t*)a.final_out + orow * kHeadDim;
+        const size_t orow = (size_t)token[rg] * args->q_heads + head;
+        if (args->final_is_bf16) {
+          uint16_t* op = (uint16_t*)args->final_out + orow * kHeadDim;
 #pragma unroll
           for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -728,7 +761,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
               *(uint2*)&op[32 * d + 8 * q4 + 4 * h] = __builtin_bit_cast(uint2, b);
             }
         } else {
-          float* op = (float*)a.final_out + orow * kHeadDim;
+          float* op = (float*)args->final_out + orow * kHeadDim;
 #pragma unroll
           for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -736,10 +769,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
               *(float4*)&op[32 * d + 8 * q4 + 4 * h] = make_float4(o[rg][d][4 * q4 + 0] * inv, o[rg][d][4 * q4 + 1] * inv,
                                                                     o[rg][d][4 * q4 + 2] * inv, o[rg][d][4 * q4 + 3] * inv);
         }
-        if (h == 0 && a.final_lse) a.final_lse[orow] = lse_val;
+        if (h == 0 && args->final_lse) args->final_lse[orow] = lse_val;
       } else {
-        const size_t orow = (size_t)(wk.out_row + tok_local[rg]) * a.q_heads + head;
-        float* op = a.out + orow * kHeadDim;
+        const size_t orow = (size_t)(wk.out_row + tok_local[rg]) * args->q_heads + head;
+        float* op = args->out + orow * kHeadDim;
 #pragma unroll
         for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -748,7 +781,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
                                      o[rg][d][4 * q4 + 3] * inv);
             *(float4*)&op[32 * d + 8 * q4 + 4 * h] = val;
           }
-        if (h == 0) a.lse[orow] = lse_val;
+        if (h == 0) args->lse[orow] = lse_val;
       }
     }
   }

@@ -1287,6 +1287,47 @@ def test_random_batches_with_peaked_scores_and_offset_values():
             run.close()
 
 
+def _batch_of_lists(name, seed, hq, hkv, seg_len, lists, fills, ntok):
+    """Every slot of the pool in use, the last request's last segment in the pool's last slot."""
+    ids = sorted(fills, key=lambda i: (lists[-1][-1:] == [i], i))
+    return wl.Batch(name=name, seed=seed, q_heads=hq, kv_heads=hkv, seg_len=seg_len, n_slots=len(ids),
+                    req_row_ptr=np.concatenate([[0], np.cumsum(ntok)]).astype(np.int32),
+                    req_seg_ptr=np.concatenate([[0], np.cumsum([len(l) for l in lists])]).astype(np.int32),
+                    seg_ids=np.array([x for l in lists for x in l], dtype=np.uint64), pool_ids=np.array(ids, dtype=np.uint64),
+                    pool_slots=np.arange(len(ids), dtype=np.int32), pool_fills=np.array([fills[i] for i in ids], dtype=np.int32))
+
+
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (4, 4), (16, 2)])
+@pytest.mark.parametrize("fuse", [False, True])
+@pytest.mark.parametrize("k_boost", [(), (1, 1 << 30, 32.0)])
+def test_masked_tiles_behind_any_number_of_full_ones(hq, hkv, fuse, k_boost):
+    """Zero to four full tiles, then tiles cut short at 1, 31, 33 and 63 tokens, in the pool and among the new tokens: every
+    place in the ring of LDS buffers, a list with two such tiles, the last of them at the end of the pool and of the
+    new tokens' memory; with keys that send the full tiles to the careful path as well."""
+    _say("masked tiles hq=%d hkv=%d fuse=%d boost=%r" % (hq, hkv, fuse, k_boost))
+    lists, fills, ntok, nid = [], {}, [], 0
+    for n_full in range(5):
+        for valid in (1, 31, 33, 63):
+            mine = [nid + j for j in range(n_full)] + [nid + n_full] + ([nid + n_full + 1] if valid == 31 else [])
+            fills.update({i: 64 for i in mine})
+            fills[mine[n_full]] = valid
+            if valid == 31:
+                fills[mine[-1]] = 5
+            nid += len(mine)
+            lists.append(mine)
+            ntok.append(64 * ((n_full + 2) % 5) + valid)
+    b = _batch_of_lists("masked", 81, hq, hkv, 64, lists, fills, ntok)
+    b.k_boost = k_boost
+    run = H.run_gpu(b, fuse=fuse)
+    assert (run.info.n_fused_tokens > 0) == fuse
+    _check_all_requests(run)
+    run.close()
+    one = _batch_of_lists("masked, 65 tokens", 82, hq, hkv, 64, [[]], {0: 64}, [65])     # 64 rows reach back to the second token
+    run = H.run_gpu(one, fuse=fuse)
+    _check_all_requests(run)
+    run.close()
+
+
 @pytest.mark.parametrize("q_heads,kv_heads,n_decode,vread", [(8, 1, 1, 0), (8, 2, 9, 0), (28, 4, 3, 0), (64, 8, 8, 0), (16, 16, 5, 0), (8, 2, 3, 1)])
 def test_row_tiles_and_units_in_one_launch(q_heads, kv_heads, n_decode, vread):
     """Prefill chunks on the three steps and decode tokens share the launch of tl_segment_attn: unit counts
