@@ -495,6 +495,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     dma_wait();
     __syncthreads();
 
+    if (wave_row >= n_rows) {
+      // A wave without rows (a short chunk, an item's last row tile) brings its share of the tiles and leaves the matrix unit
+      // to the wave it shares a SIMD with: a row tile of 128 rows or less takes 0.71 to 0.76 us a tile by itself, 1.12
+      // when the idle waves multiplied zeros (the tiny configuration, 128 rows: 17.7 -> 14.6 us); of 129 rows or more no change.
+      int buf = 0;
+#pragma unroll 1
+      for (int t = 0; t < n_full; ++t) {
+        const int next = buf + 1 == kBufs ? 0 : buf + 1, prev = buf == 0 ? kBufs - 1 : buf - 1;
+        if (!CAUSAL && t > 0 && (t & (kIdxRing / 2 - 1)) == 0) ring_fill(t + kIdxRing / 2, kIdxRing / 2);
+        if (t + 2 < n_load) dma_tile(src_k, full_base(t + 2), lds_k + prev * kKTile, dma_off_k);
+        if (t + 1 < n_load) dma_tile(src_v, full_base(t + 1), lds_v + next * kVTile, dma_off_v);
+        buf = next;
+        dma_wait();
+        lds_barrier();
+      }
+      __syncthreads();
+      const bool redo = *lds_flag != 0;
+      __syncthreads();
+      return !redo;
+    }
+
     float l_prev[kRG];                  // the lane's row sum before the current tile
 #pragma unroll
     for (int rg = 0; rg < kRG; ++rg) l_prev[rg] = l_run[rg];

@@ -1328,6 +1328,25 @@ def test_masked_tiles_behind_any_number_of_full_ones(hq, hkv, fuse, k_boost):
     run.close()
 
 
+@pytest.mark.parametrize("n_tok", [5, 8, 9, 16, 17, 24, 32, 33, 40])
+@pytest.mark.parametrize("k_boost", [(), (3, 1 << 30, 32.0)])
+def test_waves_without_rows(n_tok, k_boost):
+    """Row tiles of 20 to 160 rows (group of 4): one wave or more has no row of its own and only moves tiles, on a list longer than the
+    ring of tile bases, on the careful path too, and beside a wave with one row."""
+    _say("waves without rows, %d tokens, boost %r" % (n_tok, k_boost))
+    seg = 128
+    lists = [list(range(300)), list(range(300, 303))]
+    fills = {i: seg for l in lists for i in l}
+    fills[299], fills[302] = 70, 3
+    b = _batch_of_lists("idle waves", 83, 4, 1, seg, lists, fills, [n_tok, n_tok])
+    b.k_boost = k_boost
+    for kw in (dict(), dict(fuse=True)):
+        run = H.run_gpu(b, **kw)
+        assert run.info.n_units == 0
+        _check_all_requests(run)
+        run.close()
+
+
 @pytest.mark.parametrize("q_heads,kv_heads,n_decode,vread", [(8, 1, 1, 0), (8, 2, 9, 0), (28, 4, 3, 0), (64, 8, 8, 0), (16, 16, 5, 0), (8, 2, 3, 1)])
 def test_row_tiles_and_units_in_one_launch(q_heads, kv_heads, n_decode, vread):
     """Prefill chunks on the three steps and decode tokens share the launch of tl_segment_attn: unit counts
