@@ -70,6 +70,9 @@ constexpr int kVTile = kKvTile * kVS;
 constexpr int kIdxRing = 512;        // tile-base entries kept in LDS (ring over the work item's tile list)
 constexpr int kBufs = 3;             // LDS tile buffers: K(t+2) and V(t+1) stream in while tile t is computed
 constexpr size_t kLdsBytes = (size_t)kBufs * (kKTile + kVTile) * sizeof(uint16_t) + (2 * kIdxRing + 4) * sizeof(int32_t);
+constexpr int kOutStride = 2 * kHeadDim + 16;    // epilogue: bytes from row to row of a wave's stretch of LDS (half an fp32 row or a bf16 one, and
+                                                 // 16 so that eight rows' 16-byte writes fall in different banks)
+static_assert(kWaves * 32 * kOutStride <= kBufs * (kKTile + kVTile) * (int)sizeof(uint16_t), "the rows of a tile fit the LDS of its kv tiles");
 constexpr float kRescaleLog2 = 8.0f;             // careful path: raise the maximum when exceeded by 2^8
 constexpr float kFastPathLimit = 1.152921504606846976e18f;  // 2^60
 constexpr int kDmaPerWave = 16 / kWaves;                  // direct-load instructions per wave per K (or V) tile
@@ -725,84 +728,96 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   // others of the loop's out; the empty asm keeps the loads in this place) ----
   auto args = (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(args));
+  if (wave_row >= n_rows) return;
+  // place of the lane's row behind the tile's first, in rows of the output; -1: the row does not exist
+  const size_t out_row0 = (size_t)wk.out_row * args->q_heads + g * G;      // (one-pass rows: out_row is the tile's first token)
+  char* mine = (char*)lds + wave * (32 * kOutStride);
+  auto lane_order = []() __attribute__((always_inline)) {       // the wave's LDS writes above, its reads below, as issued
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
 #pragma unroll
   for (int rg = 0; rg < kRG; ++rg) {
     const float l_tot = xor32_sum(l_run[rg]);
     const float lr_tot = l_tot + xor32_sum(lr_run[rg]);
-    if (row_ok[rg]) {
-      float inv = lr_tot > 0.f ? 1.f / lr_tot : 0.f;
-      const int head = g * G + head_j[rg];
-      float lse_val = l_tot > 0.f ? m_ref[rg] * args->scale + __logf(l_tot) : -INFINITY;
-      if (MODE == 2 && wk.n_prior > 0) {
-        // One-pass tail: the row's partials in the work items above it (shared runs, computed by an
-        // earlier launch) are merged in with the rule of the merge kernel,
-        //   M = max LSE_j, w_j = exp(LSE_j - M), O = sum w_j O_j / sum w_j, LSE = M + ln sum w_j,
-        // taken one partial at a time: (M, W, acc) <- (max(M, L), W e^(M-M') + e^(L-M'), acc e^(M-M') + O_j e^(L-M')).
-        // The accumulators are brought to their normalised values first.
+    const int rel = row_ok[rg] ? tok_local[rg] * args->q_heads + head_j[rg] : -1;
+    float inv = lr_tot > 0.f ? 1.f / lr_tot : 0.f;
+    float lse_val = l_tot > 0.f ? m_ref[rg] * args->scale + __logf(l_tot) : -INFINITY;
+    if (MODE == 2 && wk.n_prior > 0 && row_ok[rg]) {
+      // One-pass tail: the row's partials in the work items above it (shared runs, computed by an
+      // earlier launch) are merged in with the rule of the merge kernel,
+      //   M = max LSE_j, w_j = exp(LSE_j - M), O = sum w_j O_j / sum w_j, LSE = M + ln sum w_j,
+      // taken one partial at a time: (M, W, acc) <- (max(M, L), W e^(M-M') + e^(L-M'), acc e^(M-M') + O_j e^(L-M')).
+      // The accumulators are brought to their normalised values first.
 #pragma unroll
-        for (int d = 0; d < 4; ++d)
+      for (int d = 0; d < 4; ++d)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) o[rg][d][r] *= inv;
-        float M = lse_val, W = lse_val > -INFINITY ? 1.f : 0.f;
-        const int tok_in_req = wk.out_row - wk.kv_off + tok_local[rg];
-        for (int j = 0; j < wk.n_prior; ++j) {
-          const size_t prow = (size_t)(args->prior_rows[wk.prior_off + j] + tok_in_req) * args->q_heads + head;
-          const float L = args->prior_lse[prow];
-          if (!(L > -INFINITY)) continue;              // a partial without keys has weight 0
-          const float Mn = fmaxf(M, L);
-          const float ea = M > -INFINITY ? __expf(M - Mn) : 0.f, eb = __expf(L - Mn);
-          const float* pp = args->prior_out + prow * kHeadDim;
-#pragma unroll
-          for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-              const float4 x = *(const float4*)&pp[32 * d + 8 * q4 + 4 * h];
-              o[rg][d][4 * q4 + 0] = o[rg][d][4 * q4 + 0] * ea + x.x * eb;
-              o[rg][d][4 * q4 + 1] = o[rg][d][4 * q4 + 1] * ea + x.y * eb;
-              o[rg][d][4 * q4 + 2] = o[rg][d][4 * q4 + 2] * ea + x.z * eb;
-              o[rg][d][4 * q4 + 3] = o[rg][d][4 * q4 + 3] * ea + x.w * eb;
-            }
-          W = W * ea + eb;
-          M = Mn;
-        }
-        inv = W > 0.f ? 1.f / W : 0.f;
-        lse_val = W > 0.f ? M + __logf(W) : -INFINITY;
-      }
-      if (MODE == 2) {
-        // final output of the token, in the caller's layout and type
-        const size_t orow = (size_t)token[rg] * args->q_heads + head;
-        if (args->final_is_bf16) {
-          uint16_t* op = (uint16_t*)args->final_out + orow * kHeadDim;
-#pragma unroll
-          for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-              const bf16x4 b = __builtin_convertvector(
-                  f32x4{o[rg][d][4 * q4 + 0] * inv, o[rg][d][4 * q4 + 1] * inv, o[rg][d][4 * q4 + 2] * inv, o[rg][d][4 * q4 + 3] * inv}, bf16x4);
-              *(uint2*)&op[32 * d + 8 * q4 + 4 * h] = __builtin_bit_cast(uint2, b);
-            }
-        } else {
-          float* op = (float*)args->final_out + orow * kHeadDim;
-#pragma unroll
-          for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-              *(float4*)&op[32 * d + 8 * q4 + 4 * h] = make_float4(o[rg][d][4 * q4 + 0] * inv, o[rg][d][4 * q4 + 1] * inv,
-                                                                    o[rg][d][4 * q4 + 2] * inv, o[rg][d][4 * q4 + 3] * inv);
-        }
-        if (h == 0 && args->final_lse) args->final_lse[orow] = lse_val;
-      } else {
-        const size_t orow = (size_t)(wk.out_row + tok_local[rg]) * args->q_heads + head;
-        float* op = args->out + orow * kHeadDim;
+        for (int r = 0; r < 16; ++r) o[rg][d][r] *= inv;
+      float M = lse_val, W = lse_val > -INFINITY ? 1.f : 0.f;
+      const int tok_in_req = wk.out_row - wk.kv_off + tok_local[rg];
+      for (int j = 0; j < wk.n_prior; ++j) {
+        const size_t prow = (size_t)(args->prior_rows[wk.prior_off + j] + tok_in_req) * args->q_heads + g * G + head_j[rg];
+        const float L = args->prior_lse[prow];
+        if (!(L > -INFINITY)) continue;              // a partial without keys has weight 0
+        const float Mn = fmaxf(M, L);
+        const float ea = M > -INFINITY ? __expf(M - Mn) : 0.f, eb = __expf(L - Mn);
+        const float* pp = args->prior_out + prow * kHeadDim;
 #pragma unroll
         for (int d = 0; d < 4; ++d)
 #pragma unroll
           for (int q4 = 0; q4 < 4; ++q4) {
-            float4 val = make_float4(o[rg][d][4 * q4 + 0] * inv, o[rg][d][4 * q4 + 1] * inv, o[rg][d][4 * q4 + 2] * inv,
-                                     o[rg][d][4 * q4 + 3] * inv);
-            *(float4*)&op[32 * d + 8 * q4 + 4 * h] = val;
+            const float4 x = *(const float4*)&pp[32 * d + 8 * q4 + 4 * h];
+            o[rg][d][4 * q4 + 0] = o[rg][d][4 * q4 + 0] * ea + x.x * eb;
+            o[rg][d][4 * q4 + 1] = o[rg][d][4 * q4 + 1] * ea + x.y * eb;
+            o[rg][d][4 * q4 + 2] = o[rg][d][4 * q4 + 2] * ea + x.z * eb;
+            o[rg][d][4 * q4 + 3] = o[rg][d][4 * q4 + 3] * ea + x.w * eb;
           }
-        if (h == 0) args->lse[orow] = lse_val;
+        W = W * ea + eb;
+        M = Mn;
+      }
+      inv = W > 0.f ? 1.f / W : 0.f;
+      lse_val = W > 0.f ? M + __logf(W) : -INFINITY;
+    }
+    float* lse_out = MODE == 2 ? args->final_lse : args->lse;
+    if (h == 0 && rel >= 0 && lse_out) lse_out[out_row0 + rel] = lse_val;
+    // The accumulators hold a row in two lanes, 16 bytes of it here and there.  They go to memory by way of the wave's own
+    // stretch of LDS (the tiles are done with), so that 16 lanes write 256 bytes of one row.
+    int rel_of[8];                       // of row 4 i + lane / 16, which this lane helps to write
+#pragma unroll
+    for (int i = 0; i < 8; ++i) rel_of[i] = __shfl(rel, 4 * i + (lane >> 4));
+    const int col = 16 * (lane & 15);
+    auto write_rows = [&](char* out, int row_bytes) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint4 x = *(const uint4*)(mine + (4 * i + (lane >> 4)) * kOutStride + col);
+        if (rel_of[i] >= 0) *(uint4*)(out + (size_t)rel_of[i] * row_bytes + col) = x;
+      }
+    };
+    if (MODE == 2 && args->final_is_bf16) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const bf16x4 b = __builtin_convertvector(
+              f32x4{o[rg][d][4 * q4 + 0] * inv, o[rg][d][4 * q4 + 1] * inv, o[rg][d][4 * q4 + 2] * inv, o[rg][d][4 * q4 + 3] * inv}, bf16x4);
+          *(uint2*)(mine + l32 * kOutStride + 2 * (32 * d + 8 * q4 + 4 * h)) = __builtin_bit_cast(uint2, b);
+        }
+      lane_order();
+      write_rows((char*)args->final_out + out_row0 * (2 * kHeadDim), 2 * kHeadDim);
+      lane_order();
+    } else {
+      char* out = (char*)(MODE == 2 ? (float*)args->final_out : args->out) + out_row0 * (4 * kHeadDim);
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+#pragma unroll
+        for (int d = 2 * half; d < 2 * half + 2; ++d)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4)
+            *(float4*)(mine + l32 * kOutStride + 4 * (32 * (d & 1) + 8 * q4 + 4 * h)) =
+                make_float4(o[rg][d][4 * q4 + 0] * inv, o[rg][d][4 * q4 + 1] * inv, o[rg][d][4 * q4 + 2] * inv, o[rg][d][4 * q4 + 3] * inv);
+        lane_order();
+        write_rows(out + half * (2 * kHeadDim), 4 * kHeadDim);
+        lane_order();
       }
     }
   }
