@@ -69,7 +69,11 @@ constexpr int kKTile = kKvTile * kKS;
 constexpr int kVTile = kKvTile * kVS;
 constexpr int kIdxRing = 512;        // tile-base entries kept in LDS (ring over the work item's tile list)
 constexpr int kBufs = 3;             // LDS tile buffers: K(t+2) and V(t+1) stream in while tile t is computed
-constexpr size_t kLdsBytes = (size_t)kBufs * (kKTile + kVTile) * sizeof(uint16_t) + (2 * kIdxRing + 4) * sizeof(int32_t);
+constexpr int kQWave = 32 * kHeadDim;              // a wave's queries, staged through LDS: waves 0 and 1 in the third K buffer, the others from the
+                                                   // second V buffer on, which the first tiles leave free, and kQExtra behind the third
+constexpr int kQExtra = 6 * kQWave - 2 * kVTile;
+static_assert(2 * kQWave == kKTile && kQExtra >= 0, "the queries fit beside the first tiles");
+constexpr size_t kLdsBytes = (size_t)(kBufs * (kKTile + kVTile) + kQExtra) * sizeof(uint16_t) + (2 * kIdxRing + 4) * sizeof(int32_t);
 constexpr int kOutStride = 2 * kHeadDim + 16;    // epilogue: bytes from row to row of a wave's stretch of LDS (half an fp32 row or a bf16 one, and
                                                  // 16 so that eight rows' 16-byte writes fall in different banks)
 static_assert(kWaves * 32 * kOutStride <= kBufs * (kKTile + kVTile) * (int)sizeof(uint16_t), "the rows of a tile fit the LDS of its kv tiles");
@@ -151,7 +155,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   const int block = JOINT ? (int)(blockIdx.x - unit_blocks(a)) : (int)blockIdx.x;   // (unsigned: 0.7 % slower on 128k lists, 6414 -> 6462 us)
   uint16_t* lds_k = lds;                 // [kBufs][64][kKS]
   uint16_t* lds_v = lds + kBufs * kKTile;    // [kBufs][64][kVS]
-  int32_t* lds_idx = (int32_t*)(lds + kBufs * (kKTile + kVTile));   // [kIdxRing]
+  int32_t* lds_idx = (int32_t*)(lds + kBufs * (kKTile + kVTile) + kQExtra);   // [kIdxRing]
   float* lds_lm = (float*)(lds_idx + kIdxRing);   // [kIdxRing] log2(multiplicity) of the same tiles
   int32_t* lds_flag = lds_idx + 2 * kIdxRing;
 
@@ -168,7 +172,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   const uint16_t* self_v = MODE == 2 ? a.v2 : a.v;
 
   // per row group: this lane's row, its token and head
-  int tok_local[kRG], head_j[kRG], token[kRG];
+  int tok_local[kRG], head_j[kRG], token[kRG], q_row[kRG];
   bool row_ok[kRG];
 #pragma unroll
   for (int rg = 0; rg < kRG; ++rg) {
@@ -176,26 +180,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     tok_local[rg] = row / G;                    // any group size: the last 256 % G rows of a tile are idle
     head_j[rg] = row - tok_local[rg] * G;
     row_ok[rg] = tok_local[rg] < wk.n_tok;
-    token[rg] = !row_ok[rg] ? -1 : kHasSelf ? first_token + tok_local[rg] : a.tok[wk.tok_off + tok_local[rg]];
+    const int at = row_ok[rg] ? tok_local[rg] : 0;         // a row that does not exist takes the queries of the tile's first
+    const int t = kHasSelf ? first_token + at : a.tok[wk.tok_off + at];
+    token[rg] = row_ok[rg] ? t : -1;
+    q_row[rg] = t * a.q_heads + g * G + (row_ok[rg] ? head_j[rg] : 0);
   }
 
   // the last token that one of this wave's rows belongs to, -1 for a wave without rows (the item's last row tile)
   const int n_rows = wk.n_tok * G, wave_row = __builtin_amdgcn_readfirstlane(wave) * (32 * kRG);
   const int wave_last = wave_row >= n_rows ? -1 : first_token + (min(wave_row + 32 * kRG, n_rows) - 1) / G;
 
-  // Q as the B operand: lane holds its row, head-dim elements 16 s + 8 h .. +7 of step s
-  bf16x8 qreg[kRG][8];
-#pragma unroll
-  for (int rg = 0; rg < kRG; ++rg) {
-    const uint4* qp =
-        (const uint4*)(a.q + ((size_t)(row_ok[rg] ? token[rg] : 0) * a.q_heads + g * G + head_j[rg]) * kHeadDim);
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      uint4 u = make_uint4(0, 0, 0, 0);
-      if (row_ok[rg]) u = qp[2 * s + h];
-      qreg[rg][s] = as_bf16x8(u);
-    }
-  }
+  bf16x8 qreg[kRG][8];    // Q as the B operand: lane holds its row, head-dim elements 16 s + 8 h .. +7 of step s
 
   // O^T accumulators: o[rg][d][r] = channel 32 d + 8 (r/4) + 4 h + r%4 of the lane's row in group rg
   f32x16 o[kRG][4];
@@ -288,6 +283,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   // wait for all of this wave's direct loads (vmcnt(0); the other counters are left alone so that
   // LDS operand reads already in flight stay in flight)
   auto dma_wait = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };
+
+  // ---- queries: a wave's 32 rows by direct loads, 256 bytes of a row by 16 lanes, in the swizzle of a K tile; to
+  // registers once the first tiles are on their way too.  (Loaded by the lanes that hold them, 16 bytes of 32 rows an
+  // instruction, they kept the first tiles waiting: prologue and first loads 8.0k cycles, now 5.1k; 64 sessions with shared
+  // runs 1736 -> 1723 us, one 32k prompt 264.3 -> 261.3, 24 chunks of 150 to 301 tokens on short prefixes 71.5 -> 68.3.)
+  static_assert(kRG == 1, "one K-shaped stretch of 32 rows a wave");
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  uint16_t* q_lds = wave_u < 2 ? lds_k + 2 * kKTile + wave_u * kQWave : lds_v + kVTile + (wave_u - 2) * kQWave;
+  {
+    const unsigned dst0 = lds_base_addr + (unsigned)(q_lds - lds) * 2u;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r_ = 4 * i + (lane >> 4);
+      const char* src = (const char*)a.q + (size_t)__shfl(q_row[0], r_) * (2 * kHeadDim) + 16 * ((lane & 15) ^ (r_ & 15));
+      unsigned saved_m0;
+      asm volatile("s_mov_b32 %[sv], m0\n\ts_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[p], off\n\ts_mov_b32 m0, %[sv]"
+                   : [sv] "=&s"(saved_m0)
+                   : [p] "v"(src), [d] "s"(dst0 + (unsigned)i * (4 * kHeadDim * 2))
+                   : "memory");
+    }
+  }
 
   // ---- building blocks ----
   // LDS tiles are unpadded rows of 256 B = 16 chunks of 16 B, written by direct global->LDS
@@ -401,6 +417,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
+  // a phase's first loads: the list's first entries come by scalar loads
+  auto first_loads = [&](auto SELF, const uint16_t* src_k, const uint16_t* src_v, const int n_load) __attribute__((always_inline)) {
+    constexpr bool CAUSAL = decltype(SELF)::value;
+    const int first_base = tile_at(SELF, 0).base;
+    dma_tile(src_k, first_base, lds_k, dma_off_k);
+    dma_tile(src_v, first_base, lds_v, dma_off_v);
+    if (n_load > 1) dma_tile(src_k, CAUSAL ? self_load_base(1) : tile_at(SELF, 1).base, lds_k + kKTile, dma_off_k);
+  };
   // careful path: tiles [from, to) of a phase, tile t in LDS buffers t % kBufs; the next tile is on its way while one is
   // computed.  `loaded`: tile `from` is there already, fetched by the fast path behind its last full tile.
   auto careful_tiles = [&](auto SELF, const uint16_t* src_k, const uint16_t* src_v, const int from, const int to, const bool loaded) __attribute__((always_inline)) {
@@ -478,22 +502,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   // kDepth groups earlier.  sched_barrier(0) after every group keeps the compiler to this order.
   // Runs the n_full (> 0) full tiles of one phase; have_ref says whether the exponent's reference
   // point exists already.  Returns false if the result overflowed and has to be discarded.
-  // A masked tile behind the full ones (`more`) is fetched like one more of them.
-  auto fast_phase = [&](auto SELF, const uint16_t* src_k, const uint16_t* src_v, const int n_full, const bool more, const bool have_ref) __attribute__((always_inline)) -> bool {
+  // A masked tile behind the full ones (`more`) is fetched like one more of them.  `started`: the first loads are on their way.
+  auto fast_phase = [&](auto SELF, const uint16_t* src_k, const uint16_t* src_v, const int n_full, const bool more, const bool started, const bool have_ref) __attribute__((always_inline)) -> bool {
     constexpr bool CAUSAL = decltype(SELF)::value;
     auto full_base = [&](int t) __attribute__((always_inline)) -> int { return CAUSAL ? self_load_base(t) : lds_idx[t & (kIdxRing - 1)]; };
-    // the first loads leave before anything else: the list's first entries come by scalar loads
     const int n_load = n_full + (more ? 1 : 0);
-    const int first_base = tile_at(SELF, 0).base;
-    dma_tile(src_k, first_base, lds_k, dma_off_k);
-    dma_tile(src_v, first_base, lds_v, dma_off_v);
-    if (n_load > 1) dma_tile(src_k, CAUSAL ? self_load_base(1) : tile_at(SELF, 1).base, lds_k + kKTile, dma_off_k);
+    if (!started) first_loads(SELF, src_k, src_v, n_load);
     if (tid == 0) *lds_flag = 0;
     if (!CAUSAL) ring_fill(0, kIdxRing);
-    {
-      // "tile -1" (V buffer kBufs-1) is multiplied by zero probabilities in the first iteration
+    if (wave_u == 4 || wave_u == 5) {
+      // "tile -1" (V buffer kBufs-1) is multiplied by zero probabilities in the first iteration; written by the waves
+      // whose queries were there
+      static_assert(kBufs == 3 && 2 * kQWave == kVTile, "the third V buffer is waves 4 and 5's");
       const uint4 z = make_uint4(0, 0, 0, 0);
-      for (int i = tid; i < kVTile / 8; i += kThreads) ((uint4*)(lds_v + (kBufs - 1) * kVTile))[i] = z;
+#pragma unroll
+      for (int i = 0; i < kQWave / 8 / 64; ++i) ((uint4*)(lds_v + (kBufs - 1) * kVTile + (wave_u - 4) * kQWave))[64 * i + lane] = z;
     }
     dma_wait();
     __syncthreads();
@@ -703,10 +726,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   // tiles are walked carefully too; in the second phase everything so far is spoilt and starts again.
   const std::false_type kPoolPhase{};
   const std::true_type kSelfPhase{};
+  // the first phase's first loads, then the queries to registers (four loads or six left behind them, or none)
+  const bool self_first = kHasSelf && nf_pool + np_pool == 0;
+  const bool started = self_first ? nf_self > 0 : nf_pool > 0;
+  if (kHasPool && nf_pool > 0) first_loads(kPoolPhase, a.k, a.v, nf_pool + (np_pool > 0));
+  if (kHasSelf && self_first && nf_self > 0) first_loads(kSelfPhase, self_k, self_v, nf_self + (np_self > 0));
+  if (started) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int s = 0; s < 8; ++s) qreg[0][s] = k_operand(q_lds, 0, s);
   if constexpr (kHasPool) {
     int from = 0;
     if (nf_pool > 0) {
-      if (fast_phase(kPoolPhase, a.k, a.v, nf_pool, np_pool > 0, false)) from = nf_pool;
+      if (fast_phase(kPoolPhase, a.k, a.v, nf_pool, np_pool > 0, true, false)) from = nf_pool;
       else reset_state();
     }
     careful_tiles(kPoolPhase, a.k, a.v, from, nf_pool + np_pool, from > 0);
@@ -714,7 +746,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   if constexpr (kHasSelf) {
     int from = 0;
     if (nf_self > 0) {
-      if (fast_phase(kSelfPhase, self_k, self_v, nf_self, np_self > 0, kHasPool && nf_pool + np_pool > 0)) {
+      if (fast_phase(kSelfPhase, self_k, self_v, nf_self, np_self > 0, self_first, kHasPool && nf_pool + np_pool > 0)) {
         from = nf_self;
       } else {
         reset_state();
