@@ -30,7 +30,7 @@
 // redo): one tile at a time, masked, running maximum raised (and O rescaled) when a block
 // exceeds it by more than 2^8; the next tile streams into the same LDS buffers meanwhile, and the first one
 // comes behind the fast path's last tile as if it were one more of them, so that nothing waits for it.
-// (Staged through registers, a masked tile cost 8.2k cycles, three of the fast path's; now 5.7k, with the phase's first loads
+// (Staged through registers, a masked tile cost 8.2k cycles, three of the fast path's; now 4.9k, with the phase's first loads
 // issued ahead of its lists: 8 prompts of 700 to 4096 tokens 559 -> 548 us, 7 of 261 to 1044 with 16 heads 55.2 -> 50.5.)
 // Repeated slots: a work item's list may name a slot several times (a multiset); the plan's tile
 // lists hold each distinct slot once with log2 of its multiplicity, which is added to the exponent
@@ -469,12 +469,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         bf16x8 pb[kRG][2];
 #pragma unroll
         for (int rg = 0; rg < kRG; ++rg) {
+          // register r of the lane is place 32 hb + 4 h + (8 (r / 4) + r % 4) of the tile: visible before `end`
+          const int end = (CAUSAL ? min(cur.hi, token[rg] + 1 - cur.base) : cur.hi) - 32 * hb - 4 * h;
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int kv = 32 * hb + 8 * (r >> 2) + 4 * h + (r & 3);
-            bool hide = kv < cur.lo || kv >= cur.hi;
-            if (CAUSAL) hide = hide || (cur.base + kv > token[rg]);
-            if (hide) s[rg][r] = -INFINITY;
+            if (8 * (r >> 2) + (r & 3) >= end) s[rg][r] = -INFINITY;
+          }
+          if (CAUSAL && cur.lo > 32 * hb) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              if (8 * (r >> 2) + (r & 3) < cur.lo - 32 * hb - 4 * h) s[rg][r] = -INFINITY;
           }
           maybe_rescale(rg, s[rg]);
           if (m_ref[rg] == -INFINITY) {
@@ -763,7 +767,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   if (wave_row >= n_rows) return;
   // place of the lane's row behind the tile's first, in rows of the output; -1: the row does not exist
   const size_t out_row0 = (size_t)wk.out_row * args->q_heads + g * G;      // (one-pass rows: out_row is the tile's first token)
-  char* mine = (char*)lds + wave * (32 * kOutStride);
+  char* mine = (char*)lds + wave_u * (32 * kOutStride);      // the wave's stretch of LDS
   auto lane_order = []() __attribute__((always_inline)) {       // the wave's LDS writes above, its reads below, as issued
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -790,10 +794,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
       for (int j = 0; j < wk.n_prior; ++j) {
         const size_t prow = (size_t)(args->prior_rows[wk.prior_off + j] + tok_in_req) * args->q_heads + g * G + head_j[rg];
         const float L = args->prior_lse[prow];
+        const float* pp = args->prior_out + prow * kHeadDim;
         if (!(L > -INFINITY)) continue;              // a partial without keys has weight 0
         const float Mn = fmaxf(M, L);
         const float ea = M > -INFINITY ? __expf(M - Mn) : 0.f, eb = __expf(L - Mn);
-        const float* pp = args->prior_out + prow * kHeadDim;
 #pragma unroll
         for (int d = 0; d < 4; ++d)
 #pragma unroll
