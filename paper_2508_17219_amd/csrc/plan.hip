@@ -744,10 +744,27 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     std::stable_sort(p->tiles.begin(), p->tiles.end(), by_len);
     std::stable_sort(p->units.begin(), p->units.end(), by_len);
     std::stable_sort(p->ctiles.begin(), p->ctiles.end(), by_len);
-    // one-pass rows: by the request's pool length only, so that the row tiles of a request stay
-    // next to each other in the launch order, run at the same time and share its KV through L2
-    std::stable_sort(p->ftiles.begin(), p->ftiles.end(),
-                     [](const Work& x, const Work& y) { return x.n_full + x.n_part > y.n_full + y.n_part; });
+    // one-pass rows: the row tiles of a request stay next to each other in the launch order, run at the same time and share
+    // its KV through L2; requests by their pool length, then by their new tokens, and of a request the last rows,
+    // which see the most of them, first (in the order of the batch, the longest row tiles of a
+    // prompt started last: 8 prompts of 700 to 4096 tokens 537 -> 517 us)
+    {
+      std::vector<std::pair<int32_t, int32_t>> spans;       // [first, last) row tile of a request
+      for (int32_t i = 0; i < (int32_t)p->ftiles.size(); ++i) {
+        if (i == 0 || p->ftiles[i].kv_off != p->ftiles[i - 1].kv_off) spans.emplace_back(i, i);
+        spans.back().second = i + 1;
+      }
+      std::stable_sort(spans.begin(), spans.end(), [&](const std::pair<int32_t, int32_t>& x, const std::pair<int32_t, int32_t>& y) {
+        const Work &a = p->ftiles[x.second - 1], &b = p->ftiles[y.second - 1];
+        const int32_t na = a.n_full + a.n_part, nb = b.n_full + b.n_part;
+        return na != nb ? na > nb : a.kv_len > b.kv_len;
+      });
+      std::vector<Work> sorted;
+      sorted.reserve(p->ftiles.size());
+      for (const auto& s : spans)
+        for (int32_t i = s.second - 1; i >= s.first; --i) sorted.push_back(p->ftiles[i]);
+      p->ftiles.swap(sorted);
+    }
 
     // ---- merge lists --------------------------------------------------------------------------
     // (tokens of one-pass requests are in no merge list: a one-pass tail's partial rows in the shared
