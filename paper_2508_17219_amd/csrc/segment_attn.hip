@@ -77,6 +77,9 @@ constexpr size_t kLdsBytes = (size_t)(kBufs * (kKTile + kVTile) + kQExtra) * siz
 constexpr int kOutStride = 2 * kHeadDim + 16;    // epilogue: bytes from row to row of a wave's stretch of LDS (half an fp32 row or a bf16 one, and
                                                  // 16 so that eight rows' 16-byte writes fall in different banks)
 static_assert(kWaves * 32 * kOutStride <= kBufs * (kKTile + kVTile) * (int)sizeof(uint16_t), "the rows of a tile fit the LDS of its kv tiles");
+constexpr int kPriorWave = 32 * 4 * kHeadDim;    // epilogue of one-pass tails: bytes of a wave's rows of one prior partial
+template <int MODE>
+constexpr size_t kLds = MODE == 2 && kWaves * kPriorWave > kLdsBytes ? kWaves * kPriorWave : kLdsBytes;
 constexpr float kRescaleLog2 = 8.0f;             // careful path: raise the maximum when exceeded by 2^8
 constexpr float kFastPathLimit = 1.152921504606846976e18f;  // 2^60
 constexpr int kDmaPerWave = 16 / kWaves;                  // direct-load instructions per wave per K (or V) tile
@@ -767,7 +770,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   if (wave_row >= n_rows) return;
   // place of the lane's row behind the tile's first, in rows of the output; -1: the row does not exist
   const size_t out_row0 = (size_t)wk.out_row * args->q_heads + g * G;      // (one-pass rows: out_row is the tile's first token)
-  char* mine = (char*)lds + wave_u * (32 * kOutStride);      // the wave's stretch of LDS
+  char* mine = (char*)lds + wave_u * (MODE == 2 ? kPriorWave : 32 * kOutStride);      // the wave's stretch of LDS
   auto lane_order = []() __attribute__((always_inline)) {       // the wave's LDS writes above, its reads below, as issued
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -779,7 +782,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     const int rel = row_ok[rg] ? tok_local[rg] * args->q_heads + head_j[rg] : -1;
     float inv = lr_tot > 0.f ? 1.f / lr_tot : 0.f;
     float lse_val = l_tot > 0.f ? m_ref[rg] * args->scale + __logf(l_tot) : -INFINITY;
-    if (MODE == 2 && wk.n_prior > 0 && row_ok[rg]) {
+    if (MODE == 2 && wk.n_prior > 0) {
       // One-pass tail: the row's partials in the work items above it (shared runs, computed by an
       // earlier launch) are merged in with the rule of the merge kernel,
       //   M = max LSE_j, w_j = exp(LSE_j - M), O = sum w_j O_j / sum w_j, LSE = M + ln sum w_j,
@@ -790,11 +793,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[rg][d][r] *= inv;
       float M = lse_val, W = lse_val > -INFINITY ? 1.f : 0.f;
-      const int tok_in_req = wk.out_row - wk.kv_off + tok_local[rg];
+      // (a row that does not exist takes the first one's: it is not written)
+      const int own = max(rel, 0);
+      const unsigned prior_lds = lds_base_addr + (unsigned)wave_u * kPriorWave;
       for (int j = 0; j < wk.n_prior; ++j) {
-        const size_t prow = (size_t)(args->prior_rows[wk.prior_off + j] + tok_in_req) * args->q_heads + g * G + head_j[rg];
-        const float L = args->prior_lse[prow];
-        const float* pp = args->prior_out + prow * kHeadDim;
+        // the wave's 32 rows of 512 bytes through LDS, 16-byte chunk c of row r at place c ^ r (by loads of 16 bytes of 32 rows
+        // each: 3 chunks of 88 to 177 tokens with six partials a row 111 us, 104.5; one partial a row in 2048 workgroups is bound by
+        // HBM, 134 MB read as the row tiles of a round end together, either way)
+        const size_t prow0 = (size_t)(unit::scalar_loads(args->prior_rows)[wk.prior_off + j] + wk.out_row - wk.kv_off) * args->q_heads + g * G;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll 2
+        for (int i = 0; i < 16; ++i) {
+          const int r_ = 2 * i + (lane >> 5);
+          const float* src = args->prior_out + (prow0 + __shfl(own, r_)) * kHeadDim + 4 * ((lane & 31) ^ r_);
+          unsigned saved_m0;
+          asm volatile("s_mov_b32 %[sv], m0\n\ts_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[p], off\n\ts_mov_b32 m0, %[sv]"
+                       : [sv] "=&s"(saved_m0)
+                       : [p] "v"(src), [d] "s"(prior_lds + (unsigned)i * 1024u)
+                       : "memory");
+        }
+        const float L = args->prior_lse[prow0 + own];
+        dma_wait();
+        asm volatile("" ::: "memory");
         if (!(L > -INFINITY)) continue;              // a partial without keys has weight 0
         const float Mn = fmaxf(M, L);
         const float ea = M > -INFINITY ? __expf(M - Mn) : 0.f, eb = __expf(L - Mn);
@@ -802,7 +822,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         for (int d = 0; d < 4; ++d)
 #pragma unroll
           for (int q4 = 0; q4 < 4; ++q4) {
-            const float4 x = *(const float4*)&pp[32 * d + 8 * q4 + 4 * h];
+            const float4 x = *(const float4*)(mine + l32 * 512 + 16 * ((8 * d + 2 * q4 + h) ^ l32));
             o[rg][d][4 * q4 + 0] = o[rg][d][4 * q4 + 0] * ea + x.x * eb;
             o[rg][d][4 * q4 + 1] = o[rg][d][4 * q4 + 1] * ea + x.y * eb;
             o[rg][d][4 * q4 + 2] = o[rg][d][4 * q4 + 2] * ea + x.z * eb;
@@ -811,6 +831,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         W = W * ea + eb;
         M = Mn;
       }
+      lane_order();
       inv = W > 0.f ? 1.f / W : 0.f;
       lse_val = W > 0.f ? M + __logf(W) : -INFINITY;
     }
@@ -868,9 +889,9 @@ tl_status launch_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) {
   static std::atomic<uint64_t> allowed[2];
   const bool scalar_v = get_option_vread() != 0;
   auto kern = scalar_v ? row_tile_attn_kernel<MODE, 1> : row_tile_attn_kernel<MODE, 0>;
-  const tl_status rc = allow_lds((const void*)kern, kLdsBytes, allowed[scalar_v]);
+  const tl_status rc = allow_lds((const void*)kern, kLds<MODE>, allowed[scalar_v]);
   if (rc != TL_OK) return rc;
-  hipLaunchKernelGGL(kern, grid, block, kLdsBytes, st, a);
+  hipLaunchKernelGGL(kern, grid, block, kLds<MODE>, st, a);
   TL_HIP(hipGetLastError());
   return TL_OK;
 }
