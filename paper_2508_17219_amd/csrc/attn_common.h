@@ -48,6 +48,7 @@ struct AttnArgs {
   float* lse;             // [rows, q_heads]
   int32_t n_tokens;       // rows of the new tokens' K/V
   int32_t q_heads, kv_heads, group, n_work;   // group = q_heads / kv_heads
+  int32_t halve;          // a row tile is two workgroups: its first half_row_tile(group) tokens and the rest
   const Work* units;      // row tiles and split-K units in one launch: the units (work: the row tiles)
   int32_t n_units;
   int32_t unit_heads_log2;  // split-K units: log2 of the kv heads per workgroup

@@ -209,6 +209,7 @@ void fill_args(AttnArgs& a, const tl_plan* plan, const PlanDev& d, const void* q
   a.part_tile = d.part_tile;
   a.tile_lm = plan->any_repeat ? d.tile_lm : nullptr;   // null: every tile has multiplicity 1
   a.part_lm = plan->any_repeat ? d.part_lm : nullptr;
+  a.halve = 0;
   a.units = nullptr;
   a.n_units = 0;
   a.out = out;
@@ -253,6 +254,7 @@ tl_status fused_rows(const tl_pool* pool, const tl_plan* plan, const void* base,
   a.final_is_bf16 = out_is_bf16 ? 1 : 0;
   a.work = d.ftiles;
   a.n_work = (int)plan->ftiles.size();
+  a.halve = plan->halve_ftiles;
   return launch_fused_row_tiles(a, a.n_work, st);
 }
 
@@ -327,6 +329,7 @@ tl_status tl_segment_attn(const tl_pool* pool, tl_plan* plan, const void* q_dev,
   a.v = (const uint16_t*)pool->v_dev;
   a.work = d.tiles;
   a.n_work = (int)plan->tiles.size();
+  a.halve = plan->halve_tiles;
   a.units = d.units;
   a.n_units = (int)plan->units.size();
   // (a launch has less than 2^32 threads: 2^23 blocks of 512, the unit blocks rounded up to a multiple of 8)
@@ -355,6 +358,7 @@ tl_status tl_causal_block(tl_plan* plan, const void* q_dev, const void* k_new_de
   a.v = (const uint16_t*)v_new_dev;
   a.work = d.ctiles;
   a.n_work = (int)plan->ctiles.size();
+  a.halve = plan->halve_ctiles;
   if (!plan->single_tok.empty()) {
     const int n_pairs = (int)plan->single_tok.size() * plan->q_heads;
     hipLaunchKernelGGL(single_token_self_kernel, dim3((unsigned)((n_pairs + 7) / 8)), dim3(256), 0, st,

@@ -71,6 +71,7 @@ constexpr double kBytesPerTile = 7.8e6, kUnitBytesPerTile = 9.75e6;
 // even, so half of it (1024 tokens) is the shortest.  (At least this much a piece instead: 4 chunks of 64 to 364 tokens on
 // 1.4k to 11k beside 27 decoded tokens 246 us for 235.)
 constexpr int32_t kMinPieceTiles = 2048 / kKvTile;
+constexpr int64_t kShortPieceTiles = 512 / kKvTile;      // the shortest piece where the launch leaves CUs idle (one_round_cut)
 
 // Partial rows of `row_tiles` row tiles, written and read.
 double merge_tiles(int64_t row_tiles, int32_t kv_heads) {
@@ -124,7 +125,7 @@ struct Walk {
 
 struct RowItem {       // a work item of row tiles
   Walk walk;
-  int64_t row_tiles;
+  int64_t row_tiles, halves;      // workgroups per kv head and piece, whole and where each takes half the rows
 };
 
 // How the lists of a launch's row-tile items are cut along the KV: into `chunks` pieces of min_slots or more, or
@@ -137,7 +138,7 @@ struct RowCut {
   int32_t step(const Walk& w) const {
     if (chunks > 1) return std::max(min_slots, (w.slots + chunks - 1) / chunks);
     if (longest == 0) return w.slots;
-    const int64_t n = std::max<int64_t>(1, (w.kv_tiles + longest - 1) / longest);
+    const int64_t n = std::max<int64_t>(1, std::min((w.kv_tiles + longest - 1) / longest, w.kv_tiles / kShortPieceTiles));
     return (int32_t)((w.slots + n - 1) / n);
   }
 };
@@ -157,6 +158,48 @@ int64_t cut_items(const std::vector<RowItem>& items, const RowCut& cut, std::vec
   return n_partial;
 }
 
+// Workgroups of the items' pieces; `halves`: where a row tile of more than half its rows is two.
+int64_t cut_workgroups(const std::vector<RowItem>& items, const RowCut& cut, int32_t kv_heads, bool halves) {
+  int64_t wgs = 0;
+  for (const RowItem& it : items) {
+    if (it.walk.slots == 0) continue;
+    const int64_t step = cut.step(it.walk);
+    wgs += (it.walk.slots + step - 1) / step * (halves ? it.halves : it.row_tiles) * kv_heads;
+  }
+  return wgs;
+}
+
+// A launch that leaves CUs idle where its lists are cut into pieces of 2048 tokens (half of the CUs, or where row tiles have half
+// their rows or less, which are bound by their chain of tiles alone, any) waits for the longest chain of
+// tiles: pieces as short as they may be (512 tokens) without becoming more than one round of the CUs, of whole row tiles or
+// of halves, which take kHalfTile of the time a tile.
+// Measured, three steps, with pieces of 2048 tokens and whole row tiles against this: 6 chunks of 16 to 32 tokens on 4k to 17k
+// of one kv head 57 -> 33 us, 39 of 3 to 7 on 3k to 11k 57 -> 36, one of 120 to 240 on 1.2k to 5k of two 59 -> 33.
+constexpr double kHalfTile = 0.68;
+RowCut one_round_cut(const std::vector<RowItem>& items, int64_t n_cu, int32_t kv_heads, const RowCut& otherwise) {
+  int64_t longest_list = 0;
+  bool wide = false;
+  for (const RowItem& it : items) {
+    longest_list = std::max(longest_list, it.walk.kv_tiles);
+    wide = wide || it.halves > it.row_tiles;
+  }
+  RowCut best = otherwise;
+  double best_cost = 0;
+  for (const bool halves : {false, true}) {
+    if (halves && !wide) continue;
+    RowCut c;
+    c.longest = kShortPieceTiles;
+    while (c.longest < kMinPieceTiles && cut_workgroups(items, c, kv_heads, halves) > n_cu) c.longest += kShortPieceTiles / 4;
+    if (c.longest >= kMinPieceTiles) continue;
+    const double cost = (halves ? kHalfTile : 1.0) * (double)(std::min(longest_list, c.longest) + kTileStart);
+    if (best_cost == 0 || cost < best_cost) {
+      best_cost = cost;
+      best = c;
+    }
+  }
+  return best;
+}
+
 // Row-tile items of a small batch: when all row tiles together are fewer workgroups than the
 // GPU has CUs, long slot lists are cut into chunks (each a work item with partial rows of its
 // own, merged like any other) until there are about two workgroups per CU; a chunk keeps at
@@ -164,7 +207,7 @@ int64_t cut_items(const std::vector<RowItem>& items, const RowCut& cut, std::vec
 // lists longer than half the mean load of a CU are cut if that ends the launch earlier by more than the
 // partials cost (lists of unequal length, or a little more than a whole number of rounds): pieces of half
 // the mean let a launch end evenly, shorter ones would only add partials to merge.
-RowCut plan_row_cut(const std::vector<RowItem>& items, int64_t n_cu, int32_t kv_heads, int32_t seg_len) {
+RowCut plan_row_cut(const std::vector<RowItem>& items, int64_t n_cu, int32_t kv_heads, int32_t seg_len, bool beside_units) {
   RowCut c;
   c.min_slots = std::max(1, kMinPieceTiles * kKvTile / seg_len);
   int64_t wgs = 0, load = 0;
@@ -173,11 +216,29 @@ RowCut plan_row_cut(const std::vector<RowItem>& items, int64_t n_cu, int32_t kv_
     load += it.walk.kv_tiles * it.row_tiles;
   }
   if (wgs == 0 || n_cu <= 0) return c;
+  const int64_t lanes = std::max<int64_t>(1, n_cu / kv_heads);
   if (wgs < n_cu) {
     c.chunks = (int32_t)std::min<int64_t>(16, (2 * n_cu + wgs - 1) / wgs);
+    if (beside_units) return c;
+    if (cut_workgroups(items, c, kv_heads, true) <= n_cu) return one_round_cut(items, n_cu, kv_heads, c);
+    // more than half a round whole: as many pieces as end the launch earliest, their partials counted (26 row tiles of 8 kv
+    // heads on one list of 6k tokens: whole 285 us, in the three pieces that two workgroups per CU would take 324)
+    if (2 * wgs > n_cu) {
+      RowCut tried = c;
+      double best_cost = 0;
+      std::vector<RowWork> pieces;
+      for (int32_t chunks = c.chunks; chunks >= 1; --chunks) {
+        tried.chunks = chunks;
+        const int64_t n_partial = cut_items(items, tried, pieces);
+        const double cost = (double)makespan(pieces, lanes) + merge_tiles(n_partial, kv_heads);
+        if (best_cost == 0 || cost <= best_cost) {
+          best_cost = cost;
+          c = tried;
+        }
+      }
+    }
     return c;
   }
-  const int64_t lanes = std::max<int64_t>(1, n_cu / kv_heads);
   RowCut half = c;
   half.longest = std::max<int64_t>(kMinPieceTiles, load / lanes / 2);
   std::vector<RowWork> pieces;
@@ -275,7 +336,11 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     // batch, or it has enough rows of its own (the work is then bound by the matrix unit, not by KV
     // traffic) -- either way it would only lose a partial per row, and a merge, on the other path.
     // Requests with a token's worth of rows (decode) always take split-K units.
-    const int tok_tile = kRowTile / G;
+    const int tok_tile = kRowTile / G, half_tile = half_row_tile(G);
+    auto row_item = [&](const Walk& w, int64_t n_tok) {
+      const int64_t whole = n_tok / tok_tile, rest = n_tok % tok_tile;
+      return RowItem{w, whole + (rest > 0), whole * (tok_tile > half_tile ? 2 : 1) + (rest > half_tile ? 2 : rest > 0)};
+    };
     const int64_t n_cu = compute_units < 0 ? kComputeUnits : compute_units;
     const int32_t min_chunk_slots = std::max(1, kMinPieceTiles * kKvTile / pool->seg_len);
     std::vector<char> fused(n_req, 0);
@@ -465,7 +530,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
           load.tokens += w.tokens * groups;
           load.longest = std::max(load.longest, w.tokens * std::min(split, w.slots) / std::max(1, w.slots));
         } else {
-          kept.push_back(RowItem{w, (n_tok + tok_tile - 1) / tok_tile});
+          kept.push_back(row_item(w, n_tok));
         }
       }
       // (units of less than a fifth of a tile's time, a token or two on short prefixes, are no launch to share)
@@ -479,7 +544,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
           if (!fused[r] || len_of(r) == 0) continue;
           const Walk w = walk_of(r, 0, len_of(r));
           const int64_t n_row = (ntok_of(r) + tok_tile - 1) / tok_tile;
-          all.push_back(RowItem{w, n_row});
+          all.push_back(row_item(w, ntok_of(r)));
           self_rows += n_row;
           for (int64_t i = 0; i < n_row; ++i) {
             const int64_t self = (std::min<int64_t>((i + 1) * tok_tile, ntok_of(r)) + kKvTile - 1) / kKvTile;
@@ -490,8 +555,8 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         if (self_rows > 0) {
           const int64_t unit_blocks = load.units * unit_head_blocks(pool->kv_heads, plan_unit_heads_log2(pool->kv_heads, load, n_cu));
           std::vector<RowWork> pieces;
-          const RowCut cut_kept = plan_row_cut(kept, n_cu, pool->kv_heads, pool->seg_len);
-          const RowCut cut_all = plan_row_cut(all, n_cu, pool->kv_heads, pool->seg_len);
+          const RowCut cut_kept = plan_row_cut(kept, n_cu, pool->kv_heads, pool->seg_len, true);
+          const RowCut cut_all = plan_row_cut(all, n_cu, pool->kv_heads, pool->seg_len, true);
           const int64_t rows_kept = cut_items(kept, cut_kept, pieces);
           const double as_one_pass = joint_tiles(units, unit_blocks, makespan(pieces, lanes), n_cu) + makespan(one_pass, lanes) + kOnePassLaunch;
           const int64_t rows_all = cut_items(all, cut_all, pieces);
@@ -578,12 +643,15 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     // ---- final items, work lists ----------------------------------------------------------
     if (!row_cut_known) {
       std::vector<RowItem> items;
+      bool any_unit = false;
       for (size_t i = 0; i < raw.size(); ++i) {
         const int64_t n_tok = is_tail_item[i] ? 0 : tok_of(raw[i]);
         if (n_tok > 0 && !unit_item(raw[i], n_tok))
-          items.push_back(RowItem{walk_of(raw[i].src_req, raw[i].begin, raw[i].end), (n_tok + tok_tile - 1) / tok_tile});
+          items.push_back(row_item(walk_of(raw[i].src_req, raw[i].begin, raw[i].end), n_tok));
+        else if (n_tok > 0)
+          any_unit = true;
       }
-      row_cut = plan_row_cut(items, n_cu, pool->kv_heads, pool->seg_len);
+      row_cut = plan_row_cut(items, n_cu, pool->kv_heads, pool->seg_len, any_unit);
     }
     int32_t row_cursor = 0;
     const int32_t own_toks = (flags & TL_PLAN_SELF_BLOCK) ? T : 0;      // the token array: every token in order, then the items' tokens
@@ -765,6 +833,21 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
         for (int32_t i = s.second - 1; i >= s.first; --i) sorted.push_back(p->ftiles[i]);
       p->ftiles.swap(sorted);
     }
+
+    // Row tiles as two workgroups of half the rows each where that stays one round of the CUs: the four waves of a half have a
+    // SIMD each, and a tile takes 0.76 us instead of 1.12.  (3 chunks of 256 tokens with 8 kv heads, 96 workgroups: pool
+    // launch 15.5 -> 13.4 us, causal launch 13.4 -> 11.4; one of 322 to 645 as one-pass rows 25.8 -> 20.9.)  A second half
+    // without rows ends at once but holds a CU until then: an eighth of the round is left for them (17 row tiles of 8 kv heads of
+    // which 15 have two halves, 256 of 272 workgroups: 41.6 us whole, 47.7 halved).
+    auto halve = [&](const std::vector<Work>& tiles) {
+      const int64_t n = (int64_t)tiles.size();
+      int64_t wgs = n;
+      for (const Work& w : tiles) wgs += w.n_tok > half_tile;
+      return wgs > n && (2 * n * pool->kv_heads <= n_cu || 8 * wgs * pool->kv_heads <= 7 * n_cu);
+    };
+    p->halve_tiles = halve(p->tiles) && p->units.empty();
+    p->halve_ctiles = halve(p->ctiles);
+    p->halve_ftiles = halve(p->ftiles);
 
     // ---- merge lists --------------------------------------------------------------------------
     // (tokens of one-pass requests are in no merge list: a one-pass tail's partial rows in the shared

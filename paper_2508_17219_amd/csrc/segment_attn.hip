@@ -163,7 +163,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   int32_t* lds_flag = lds_idx + 2 * kIdxRing;
 
   const int g = block % a.kv_heads;
-  const Work wk = a.work[block / a.kv_heads];
+  // a row tile as two workgroups: the first halves of all, then the second ones, of which some may be empty
+  int item = block / a.kv_heads;
+  const bool second = a.halve && item >= a.n_work;
+  if (second) item -= a.n_work;
+  Work wk = a.work[item];
+  if (a.halve) {
+    const int first = half_row_tile(a.group), skip = second ? first : 0;
+    if (skip >= wk.n_tok) return;
+    const int n = second ? wk.n_tok - first : min(first, wk.n_tok);
+    wk.tok_off += skip;
+    wk.out_row += skip;
+    wk.kv_len -= wk.n_tok - skip - n;          // (new tokens visible to the half's last row; not used by pool work)
+    wk.n_tok = n;
+  }
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int G = a.group;
@@ -885,7 +898,7 @@ static_assert(kThreads == unit::kThreads, "one block size for both kinds");
 template <int MODE>
 tl_status launch_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) {
   if (n_work == 0) return TL_OK;
-  const dim3 grid((unsigned)n_work * a.kv_heads), block(kThreads);
+  const dim3 grid((unsigned)n_work * a.kv_heads * (a.halve ? 2 : 1)), block(kThreads);
   static std::atomic<uint64_t> allowed[2];
   const bool scalar_v = get_option_vread() != 0;
   auto kern = scalar_v ? row_tile_attn_kernel<MODE, 1> : row_tile_attn_kernel<MODE, 0>;

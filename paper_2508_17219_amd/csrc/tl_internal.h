@@ -44,6 +44,9 @@ constexpr int kUnitRows = 16;    // max rows per kv head of a split-K unit
 constexpr int kFuseRows = 2 * kRowTile;
 constexpr int kComputeUnits = 256;   // MI355X (tl_plan_create's default; the plan builder makes no HIP call)
 
+// Tokens of the first of two workgroups that share a row tile, at most the other's (a group that does not divide the tile: one more).
+__host__ __device__ inline int half_row_tile(int group) { return (kRowTile / group + 1) / 2; }
+
 // Workgroups per split-K unit where each takes 2^heads_log2 kv heads.
 __host__ __device__ inline int32_t unit_head_blocks(int32_t kv_heads, int32_t heads_log2) {
   return (kv_heads + (1 << heads_log2) - 1) >> heads_log2;
@@ -115,6 +118,7 @@ struct tl_plan {
   std::vector<int32_t> unit_slots;      // split-K units: Work::kv_off/kv_len, each distinct slot of a chunk once as (first kv row, valid tokens) ...
   std::vector<float> unit_lm;           // ... with log2 of the number of times the run lists it
   bool any_unit_repeat = false;
+  bool halve_tiles = false, halve_ctiles = false, halve_ftiles = false;   // a row tile is two workgroups of half the rows
   int32_t unit_heads_log2 = 0;          // log2 of the kv heads that a workgroup of the split-K kernel takes
   uint64_t pool_generation;      // the pool's generation when the plan was built
   int32_t pool_n_slots;

@@ -316,6 +316,28 @@ def test_small_batch_of_row_tiles_is_cut_along_its_kv():
     B.tl_pool_destroy(plan_pool[0])
 
 
+@pytest.mark.parametrize("n_req,new,lo,hi,hq,hkv,seg_len", [
+    (6, 24, 4200, 16700, 8, 1, 256),       # narrow row tiles
+    (1, 200, 4700, 4800, 8, 2, 256),       # wide ones, halved
+    (3, 40, 700, 950, 32, 8, 64),          # nothing to cut: 15 tiles at most, 8 are the shortest piece
+    (39, 5, 2700, 10900, 8, 1, 64),
+])
+def test_a_launch_that_leaves_cus_idle_is_cut_into_short_pieces(n_req, new, lo, hi, hq, hkv, seg_len):
+    """Pieces of at least 512 tokens, no more of them than one round of the CUs; every pair is covered once."""
+    b = wl.prefill(seed=12, n_req=n_req, new_tokens=new, lo=lo, hi=hi, seg_len=seg_len, n_slots=8192, n_shared=0, hq=hq, hkv=hkv)
+    plan_pool[0] = _pool_for(b)
+    plan = B.tl_plan_create(plan_pool[0], b.q_heads, b.req_row_ptr, b.req_seg_ptr, b.seg_ids, B.TL_PLAN_SELF_BLOCK | B.TL_PLAN_NO_SHARING)
+    info = _check_plan_covers(b, plan, B.TL_PLAN_SELF_BLOCK | B.TL_PLAN_NO_SHARING)
+    lens = np.diff(B.tl_plan_export(plan)["item_slot_ptr"]) * seg_len
+    assert info.n_tiles * hkv <= 256
+    if hi < 1024:
+        assert info.n_items == n_req
+    else:
+        assert info.n_items > n_req * lo // 2048 and np.mean(lens) < 2048 and np.sort(lens)[n_req:].min() >= 512 - seg_len
+    B.tl_plan_destroy(plan)
+    B.tl_pool_destroy(plan_pool[0])
+
+
 @pytest.mark.parametrize("heads", [(32, 8, 5), (8, 1, 16)])
 def test_uneven_chunks_beside_decode_leave_the_one_pass_kernel(heads):
     """Prefill chunks on prefixes of very different lengths beside decoded tokens: the longest list would

@@ -1347,6 +1347,29 @@ def test_waves_without_rows(n_tok, k_boost):
         run.close()
 
 
+@pytest.mark.parametrize("hq,hkv", [(4, 4), (6, 2), (8, 2), (10, 2), (28, 4), (16, 2), (32, 1)])
+@pytest.mark.parametrize("fuse", [False, True])
+def test_row_tiles_halved_between_two_workgroups_and_lists_in_short_pieces(hq, hkv, fuse):
+    """A batch of few workgroups: a row tile is two of half its rows (a group that does not divide 256 among them), and long lists go in
+    pieces of 512 tokens.  One token less and more than a half and a whole row tile, work items of several requests, every row."""
+    _say("halved row tiles hq=%d hkv=%d fuse=%d" % (hq, hkv, fuse))
+    tile = 256 // (hq // hkv)
+    half = (tile + 1) // 2
+    ntok = [n for n in (half - 1, half, half + 1, tile, tile + 1, tile + half + 1) if n > 0]
+    lists, fills, nid = [], {}, 10
+    for i in range(len(ntok)):
+        own = list(range(nid, nid + (1, 30, 3)[i % 3]))
+        nid += len(own)
+        lists.append([0, 1] * (i % 2) + own)
+    fills.update({i: 64 for i in [0, 1] + list(range(10, nid))})
+    fills[nid - 1] = 17
+    b = _batch_of_lists("halved", 84, hq, hkv, 64, lists, fills, ntok)
+    run = H.run_gpu(b, fuse=fuse, fill_cus=256, compute_units=256)
+    assert run.info.n_items + run.info.n_fused_tiles > len(ntok)
+    _check_all_requests(run)
+    run.close()
+
+
 @pytest.mark.parametrize("q_heads,kv_heads,n_decode,vread", [(8, 1, 1, 0), (8, 2, 9, 0), (28, 4, 3, 0), (64, 8, 8, 0), (16, 16, 5, 0), (8, 2, 3, 1)])
 def test_row_tiles_and_units_in_one_launch(q_heads, kv_heads, n_decode, vread):
     """Prefill chunks on the three steps and decode tokens share the launch of tl_segment_attn: unit counts
