@@ -51,6 +51,7 @@ struct AttnArgs {
   int32_t halve;          // a row tile is two workgroups: its first half_row_tile(group) tokens and the rest
   const Work* units;      // row tiles and split-K units in one launch: the units (work: the row tiles)
   int32_t n_units;
+  int32_t unit_lanes;     // workgroups that take the units (of head blocks), each several in turn
   int32_t unit_heads_log2;  // split-K units: log2 of the kv heads per workgroup
   float scale;            // softmax scale
   float scale_log2e;      // scale * log2(e)

@@ -211,7 +211,7 @@ void fill_args(AttnArgs& a, const tl_plan* plan, const PlanDev& d, const void* q
   a.part_lm = plan->any_repeat ? d.part_lm : nullptr;
   a.halve = 0;
   a.units = nullptr;
-  a.n_units = 0;
+  a.n_units = a.unit_lanes = 0;
   a.out = out;
   a.lse = lse;
   a.n_tokens = plan->n_tokens;
@@ -332,8 +332,9 @@ tl_status tl_segment_attn(const tl_pool* pool, tl_plan* plan, const void* q_dev,
   a.halve = plan->halve_tiles;
   a.units = d.units;
   a.n_units = (int)plan->units.size();
+  a.unit_lanes = plan->unit_lanes;
   // (a launch has less than 2^32 threads: 2^23 blocks of 512, the unit blocks rounded up to a multiple of 8)
-  const int64_t blocks = (int64_t)a.n_work * a.kv_heads + (int64_t)a.n_units * unit_head_blocks(a.kv_heads, a.unit_heads_log2) + 7;
+  const int64_t blocks = (int64_t)a.n_work * a.kv_heads + a.unit_lanes + 7;
   if (a.n_work > 0 && a.n_units > 0 && blocks < (1 << 23)) return launch_tiles_and_units(a, st);
   rc = launch_pool_row_tiles(a, a.n_work, st);
   if (rc != TL_OK) return rc;

@@ -87,6 +87,20 @@ double joint_tiles(double units, int64_t unit_blocks, double tiles, int64_t n_cu
   return units + tiles - std::min(shorter, std::min(idle, 0.5 * tiles) + 0.25 * shorter);
 }
 
+// Workgroups that take the split-K units beside row tiles.  All units at once keep HBM busy and leave row tiles the few CUs that are
+// over; with half as many workgroups that take two units each in turn, row tiles and units run side by side for longer.  That pays
+// where the two take about as long, units by their bytes and row tiles by their KV tiles: of 125 random batches of 1 to 8 chunks
+// beside 4 to 190 decoded tokens 44 have row tiles of 0.95 to 3.5 of the units' time and half a round to one and a half of unit
+// workgroups; tl_segment_attn takes 0.94 of its time in their mean (0.78 to 1.08, five of them more than 1.01; the mixed batch of
+// perf/cases.py 451 -> 441 us).  Below, the units are the longer part and want the CUs (20 row tiles beside 116 decoded tokens
+// 1.42, twelve batches of 0.5 to 0.95 0.67 to 1.28); above, it makes no difference (0.95 to 1.08).  Three in turn: 1.01 in the mean.
+constexpr double kUnitBytesPerUs = 6.0e6, kRowTileUs = 1.5;
+int64_t plan_unit_lanes(int64_t unit_blocks, double unit_bytes, double row_us, int64_t n_cu) {
+  const double units = unit_bytes / kUnitBytesPerUs, rows = n_cu > 0 ? row_us / (double)n_cu : 0;
+  const bool side_by_side = 2 * unit_blocks >= n_cu && 2 * unit_blocks <= 3 * n_cu && rows >= 0.95 * units && rows <= 3.5 * units;
+  return side_by_side ? (unit_blocks + 1) / 2 : unit_blocks;
+}
+
 struct RowWork {
   int64_t kv_tiles, row_tiles;
 };
@@ -759,6 +773,12 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       unit_load.longest = std::max(unit_load.longest, tokens);
     }
     p->unit_heads_log2 = plan_unit_heads_log2(pool->kv_heads, unit_load, n_cu > 0 ? n_cu : kComputeUnits);
+    {
+      double row_us = 0;
+      for (const Work& w : p->tiles) row_us += kRowTileUs * (double)((w.n_full + w.n_part + kTileStart) * pool->kv_heads);
+      p->unit_lanes = (int32_t)plan_unit_lanes(unit_load.units * unit_head_blocks(pool->kv_heads, p->unit_heads_log2),
+                                               (double)unit_load.tokens * pool->kv_heads * (4 * kHeadDim), row_us, n_cu);
+    }
     p->tok.resize(own_toks);
     std::iota(p->tok.begin(), p->tok.end(), 0);
     p->tok.insert(p->tok.end(), p->item_tokens.begin(), p->item_tokens.end());

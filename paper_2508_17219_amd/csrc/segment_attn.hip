@@ -130,16 +130,14 @@ __device__ __forceinline__ float max16(const f32x16& s) {
   return fmaxf(fmaxf(fmaxf(a, b), fmaxf(c, d)), fmaxf(e, s[15]));
 }
 
-__host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) {
-  return ((unsigned)a.n_units * (unsigned)unit_head_blocks(a.kv_heads, a.unit_heads_log2) + 7u) & ~7u;
-}
+__host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) { return ((unsigned)a.unit_lanes + 7u) & ~7u; }
 
 // MODE 0: pool work item (tile lists) -> partial.  MODE 1: causal block of the new tokens ->
 // partial.  MODE 2: both in one pass -- the row tile walks its request's pool tiles, then the
 // new tokens up to its own rows -- and writes the final, normalised output: such rows have one
 // partial, so they need no merge.
 //
-// JOINT (MODE 0): row tiles of the pool and split-K units in one launch: units first, which are bound by HBM and by their own
+// JOINT (MODE 0): row tiles of the pool and split-K units in one launch: units first, in as many workgroups as the plan says (plan_unit_lanes), which are bound by HBM and by their own
 // chain, then row tiles, which find the CUs that the units leave and finish evenly on all of them.  The first
 // row tile's block is a multiple of eight, so that a kv head stays on its XCD.  One launch after the other, the
 // first leaves CUs idle at its end and HBM idles through the row tiles: 4 chunks of 300 to 600 tokens beside 48 decoded
@@ -151,8 +149,13 @@ template <int MODE, int VREAD, bool JOINT = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void row_tile_attn_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   if (JOINT && blockIdx.x < unit_blocks(a)) {
-    if (blockIdx.x < (unsigned)a.n_units * (unsigned)unit_head_blocks(a.kv_heads, a.unit_heads_log2))
-      unit::splitk_unit<VREAD>(a, a.units[blockIdx.x % a.n_units], blockIdx.x / a.n_units, lds);
+    const int n = a.n_units * unit_head_blocks(a.kv_heads, a.unit_heads_log2), lanes = a.unit_lanes, lane_no = blockIdx.x;
+    if (lane_no >= lanes) return;
+    for (int first = 0; first < n; first += lanes) {          // forth and back, as the units come longest first
+      const int i = (first / lanes) & 1 ? first + lanes - 1 - lane_no : first + lane_no;
+      if (first > 0) __syncthreads();                           // the LDS is free again
+      if (i < n) unit::splitk_unit<VREAD>(a, a.units[i % a.n_units], i / a.n_units, lds);
+    }
     return;
   }
   const int block = JOINT ? (int)(blockIdx.x - unit_blocks(a)) : (int)blockIdx.x;   // (unsigned: 0.7 % slower on 128k lists, 6414 -> 6462 us)

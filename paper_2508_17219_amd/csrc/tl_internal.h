@@ -119,6 +119,7 @@ struct tl_plan {
   std::vector<float> unit_lm;           // ... with log2 of the number of times the run lists it
   bool any_unit_repeat = false;
   bool halve_tiles = false, halve_ctiles = false, halve_ftiles = false;   // a row tile is two workgroups of half the rows
+  int32_t unit_lanes = 0;               // workgroups that take the units beside row tiles
   int32_t unit_heads_log2 = 0;          // log2 of the kv heads that a workgroup of the split-K kernel takes
   uint64_t pool_generation;      // the pool's generation when the plan was built
   int32_t pool_n_slots;

@@ -1370,6 +1370,26 @@ def test_row_tiles_halved_between_two_workgroups_and_lists_in_short_pieces(hq, h
     run.close()
 
 
+@pytest.mark.parametrize("hq,hkv,n_decode", [(4, 1, 23), (8, 2, 20), (10, 5, 20), (32, 8, 21), (18, 9, 8)])
+def test_units_in_turn_beside_row_tiles(hq, hkv, n_decode):
+    """For 16 CUs: row tiles that take 0.95 to 3.5 of the units' time, so that half as many workgroups as units take two of them each (an
+    odd number of units, slices of one head that meet at a barrier, waves without a head), units of several lengths but for those, every row."""
+    _say("units in turn hq=%d hkv=%d decode=%d" % (hq, hkv, n_decode))
+    lists, fills, nid = [], {}, 0
+    for r in range(n_decode + 1):
+        n = 1400 // 64 if r == n_decode else 18 if hkv == 9 else 4 + r % 13
+        lists.append(list(range(nid, nid + n)))
+        nid += n
+    fills = {i: 64 for i in range(nid)}
+    fills[lists[0][-1]], fills[nid - 1] = 33, 7
+    b = _batch_of_lists("units in turn", 85, hq, hkv, 64, lists, fills, [1] * n_decode + [32])
+    run = H.run_gpu(b, split_segments=32, compute_units=16)
+    units, rows = (sum(len(l) * 64 for l in lists[:-1]) * hkv * 512 / 6e6, (22 + 5) * 1.5 * run.info.n_tiles * hkv / 16)
+    assert run.info.n_units == n_decode and 0.95 * units < rows < 3.5 * units
+    _check_all_requests(run)
+    run.close()
+
+
 @pytest.mark.parametrize("q_heads,kv_heads,n_decode,vread", [(8, 1, 1, 0), (8, 2, 9, 0), (28, 4, 3, 0), (64, 8, 8, 0), (16, 16, 5, 0), (8, 2, 3, 1)])
 def test_row_tiles_and_units_in_one_launch(q_heads, kv_heads, n_decode, vread):
     """Prefill chunks on the three steps and decode tokens share the launch of tl_segment_attn: unit counts
