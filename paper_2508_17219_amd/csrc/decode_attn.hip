@@ -8,7 +8,7 @@ namespace {
 template <int VREAD>
 __global__ __launch_bounds__(unit::kThreads) void splitk_unit_attn_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
-  unit::splitk_unit<VREAD>(a, a.work[blockIdx.x], blockIdx.y, lds);
+  unit::splitk_unit<VREAD, false>(a, a.work[blockIdx.x], blockIdx.y, lds);
 }
 
 }  // namespace

@@ -137,8 +137,8 @@ __host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) { return ((un
 // new tokens up to its own rows -- and writes the final, normalised output: such rows have one
 // partial, so they need no merge.
 //
-// JOINT (MODE 0): row tiles of the pool and split-K units in one launch: units first, in as many workgroups as the plan says (plan_unit_lanes), which are bound by HBM and by their own
-// chain, then row tiles, which find the CUs that the units leave and finish evenly on all of them.  The first
+// JOINT (MODE 0): row tiles of the pool and split-K units in one launch: units first, which are bound by HBM and by their own
+// chain, in as many workgroups as the plan says (plan_unit_lanes), then row tiles, which find the CUs that the units leave and finish evenly on all of them.  The first
 // row tile's block is a multiple of eight, so that a kv head stays on its XCD.  One launch after the other, the
 // first leaves CUs idle at its end and HBM idles through the row tiles: 4 chunks of 300 to 600 tokens beside 48 decoded
 // ones 614 us a step, together 520; over 120 random batches tl_segment_attn takes 0.87 of its time in two launches, 0.99
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     for (int first = 0; first < n; first += lanes) {          // forth and back, as the units come longest first
       const int i = (first / lanes) & 1 ? first + lanes - 1 - lane_no : first + lane_no;
       if (first > 0) __syncthreads();                           // the LDS is free again
-      if (i < n) unit::splitk_unit<VREAD>(a, a.units[i % a.n_units], i / a.n_units, lds);
+      if (i < n) unit::splitk_unit<VREAD, true>(a, a.units[i % a.n_units], i / a.n_units, lds);
     }
     return;
   }

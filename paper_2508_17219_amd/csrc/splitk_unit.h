@@ -48,7 +48,8 @@ inline bool can_deal(const AttnArgs& a) {
   return a.unit_heads_log2 == 3 || (a.unit_heads_log2 >= 0 && a.unit_heads_log2 < 3 && !(a.kv_heads & ((1 << a.unit_heads_log2) - 1)));
 }
 
-template <int VREAD>
+// IN_TURN: the workgroup takes several units, one after the other.
+template <int VREAD, bool IN_TURN>
 __device__ __forceinline__ void splitk_unit(const AttnArgs& a, const Work wk, const int head_block, uint16_t* lds) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, l16 = lane & 15, c4 = lane >> 4;
@@ -63,7 +64,20 @@ __device__ __forceinline__ void splitk_unit(const AttnArgs& a, const Work wk, co
   const int tok_local = l16 / G;
   const int j = l16 - tok_local * G;
   const bool row_ok = tok_local < wk.n_tok;
-  const int token = row_ok ? a.tok[wk.tok_off + tok_local] : 0;
+  int token = 0;
+  if (!IN_TURN) {
+    token = row_ok ? a.tok[wk.tok_off + tok_local] : 0;
+  } else {
+    // by scalar loads, 16 entries of the token array whatever their number (the plan's block goes on for 256 bytes behind its last
+    // array), each lane its own: a vector load would wait for the last unit's stores.  (Where every unit has a workgroup
+    // of its own, 0.2 us longer than the vector load.)
+    const auto* toks = scalar_loads(a.tok + wk.tok_off);
+#pragma unroll
+    for (int t = 0; t < kUnitRows; ++t) {
+      const int of_t = toks[t];
+      if (row_ok && tok_local == t) token = of_t;
+    }
+  }
 
   // Q as B operand of 16x16x32: lane holds row l16, head-dim 32 s + 8 c4 .. +7
   bf16x8 qreg[4];
