@@ -1443,6 +1443,12 @@ def test_merge_lists_at_the_edges_of_their_kernels(segs, q_heads, out_bf16):
     run.close()
 
 
+@pytest.mark.parametrize("out_bf16", [False, True])
+def test_merge_lists_around_what_a_slice_holds(out_bf16):
+    """Lists of 16 to 131 partials: a slice's eight held in registers not all there, just there, one more, four and more behind them."""
+    test_merge_lists_at_the_edges_of_their_kernels([15, 22, 23, 62, 63, 64, 70, 94, 95, 96, 130], 8, out_bf16)
+
+
 # ---- the step as a HIP graph ----------------------------------------------------------------------
 @pytest.mark.parametrize("fuse", [False, True])
 def test_step_replays_from_a_hip_graph(fuse):
