@@ -184,11 +184,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int G = a.group;
   constexpr bool kHasPool = MODE != 1, kHasSelf = MODE != 0;
+  // Arguments for the parts behind the loops are read from the kernel's argument block where they are needed: held in scalar
+  // registers from the start they push others of the loop's out.  (The empty asm keeps the loads in their place.)
+  auto late_args = []() __attribute__((always_inline)) {
+    auto p = (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+  };
   const int first_token = wk.tok_off;          // causal work: tokens of a tile are consecutive, and the token array starts with
                                                // every token in order (one dependent load less before the queries)
   // K/V of the new tokens: the launch's main K/V for the causal block alone, the second pair when fused
-  const uint16_t* self_k = MODE == 2 ? a.k2 : a.k;
-  const uint16_t* self_v = MODE == 2 ? a.v2 : a.v;
+  auto self_k = [&]() __attribute__((always_inline)) { const auto args = late_args(); return MODE == 2 ? args->k2 : args->k; };
+  auto self_v = [&]() __attribute__((always_inline)) { const auto args = late_args(); return MODE == 2 ? args->v2 : args->v; };
 
   // per row group: this lane's row, its token and head
   int tok_local[kRG], head_j[kRG], token[kRG], q_row[kRG];
@@ -252,7 +259,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     }
   };
 
-  const size_t kv_row = (size_t)a.kv_heads * kHeadDim;
+  const unsigned kv_bytes = (unsigned)a.kv_heads * (2 * kHeadDim);        // from kv row to kv row
   // ---- staging: direct global -> LDS load of a whole tile.  A tile is 16 wave
   // instructions; wave w issues instructions w + kWaves u, instruction i filling rows 4 i .. 4 i + 3;
   // lane L lands at row 4 i + L / 16, position L % 16, so it fetches the logical chunk that belongs there
@@ -260,8 +267,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
 #pragma unroll
   for (int u = 0; u < kDmaPerWave; ++u) {
     const int r_ = 4 * (wave + kWaves * u) + (lane >> 4), pos = lane & 15;
-    dma_off_k[u] = (unsigned)((r_ * kv_row + (size_t)g * kHeadDim) * 2 + 16 * (pos ^ (r_ & 15)));
-    dma_off_v[u] = (unsigned)((r_ * kv_row + (size_t)g * kHeadDim) * 2 + 16 * (pos ^ (4 * (r_ & 3))));
+    dma_off_k[u] = (r_ * kv_bytes + (unsigned)g * (2 * kHeadDim) + 16 * (pos ^ (r_ & 15)));
+    dma_off_v[u] = (r_ * kv_bytes + (unsigned)g * (2 * kHeadDim) + 16 * (pos ^ (4 * (r_ & 3))));
   }
   // (issued as inline assembly: the compiler does not see these loads, so it puts no wait for them
   // in front of the LDS reads that follow; dma_wait() before the iteration's barrier is the wait)
@@ -269,7 +276,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   const unsigned dma_wave_off = __builtin_amdgcn_readfirstlane(wave) * (4 * kHeadDim * 2);
   static_assert(kDmaPerWave == 2, "dma_tile issues exactly two direct loads per wave");
   auto dma_tile = [&](const uint16_t* src, int base, uint16_t* tile, const unsigned (&off)[kDmaPerWave]) {
-    const char* trow = (const char*)src + (size_t)__builtin_amdgcn_readfirstlane(base) * (kv_row * 2);
+    const char* trow = (const char*)src + (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane(base) * kv_bytes;
     const unsigned dst0 = lds_base_addr + (unsigned)(tile - lds) * 2u + dma_wave_off;
     const unsigned dst1 = dst0 + (unsigned)(kWaves * 4 * kHeadDim) * 2u;
     // address = wave-uniform 64-bit tile base (scalar registers) + this lane's constant 32-bit offset;
@@ -285,14 +292,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         : [o0] "v"(off[0]), [o1] "v"(off[1]), [d0] "s"(dst0), [d1] "s"(dst1), [b] "s"(trow)
         : "memory");
   };
-  // the same for the first `rows` rows of a tile; the others' places in LDS keep what they hold
-  auto dma_rows = [&](const uint16_t* src, int base, int rows, uint16_t* tile, const unsigned (&off)[kDmaPerWave]) __attribute__((always_inline)) {
-    const char* trow = (const char*)src + (size_t)__builtin_amdgcn_readfirstlane(base) * (kv_row * 2);
+  // the same for the first `rows` rows of a tile; the others' places in LDS keep what they hold.  `plain`: through registers
+  auto dma_rows = [&](const uint16_t* src, int base, int rows, uint16_t* tile, const unsigned (&off)[kDmaPerWave], const bool plain) __attribute__((always_inline)) {
+    const char* trow = (const char*)src + (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane(base) * kv_bytes;
 #pragma unroll
     for (int u = 0; u < kDmaPerWave; ++u) {
       const unsigned dst = lds_base_addr + (unsigned)(tile - lds) * 2u + dma_wave_off + (unsigned)(u * kWaves * 4 * kHeadDim) * 2u;
       unsigned saved_m0;
-      if (4 * (wave + kWaves * u) + (lane >> 4) < rows)
+      if (4 * (wave + kWaves * u) + (lane >> 4) >= rows) continue;
+      if (plain)
+        ((uint4*)((char*)tile + dma_wave_off + u * kWaves * 4 * kHeadDim * 2))[lane] = *(const uint4*)(trow + off[u]);
+      else
         asm volatile("s_mov_b32 %[sv], m0\n\ts_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[o], %[b]\n\ts_mov_b32 m0, %[sv]"
                      : [sv] "=&s"(saved_m0)
                      : [o] "v"(off[u]), [d] "s"(dst), [b] "s"(trow)
@@ -312,15 +322,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   uint16_t* q_lds = wave_u < 2 ? lds_k + 2 * kKTile + wave_u * kQWave : lds_v + kVTile + (wave_u - 2) * kQWave;
   {
     const unsigned dst0 = lds_base_addr + (unsigned)(q_lds - lds) * 2u;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    auto q_chunk = [&](int i) __attribute__((always_inline)) -> const char* {       // of row 4 i + lane / 16
       const int r_ = 4 * i + (lane >> 4);
-      const char* src = (const char*)a.q + (size_t)__shfl(q_row[0], r_) * (2 * kHeadDim) + 16 * ((lane & 15) ^ (r_ & 15));
-      unsigned saved_m0;
-      asm volatile("s_mov_b32 %[sv], m0\n\ts_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[p], off\n\ts_mov_b32 m0, %[sv]"
-                   : [sv] "=&s"(saved_m0)
-                   : [p] "v"(src), [d] "s"(dst0 + (unsigned)i * (4 * kHeadDim * 2))
-                   : "memory");
+      return (const char*)a.q + (size_t)__shfl(q_row[0], r_) * (2 * kHeadDim) + 16 * ((lane & 15) ^ (r_ & 15));
+    };
+    if (a.off_16 & kUnalignedQ) {
+#pragma unroll 1
+      for (int i = 0; i < 8; ++i) ((uint4*)((char*)q_lds + i * (4 * kHeadDim * 2)))[lane] = *(const uint4*)q_chunk(i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        unsigned saved_m0;
+        asm volatile("s_mov_b32 %[sv], m0\n\ts_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[p], off\n\ts_mov_b32 m0, %[sv]"
+                     : [sv] "=&s"(saved_m0)
+                     : [p] "v"(q_chunk(i)), [d] "s"(dst0 + (unsigned)i * (4 * kHeadDim * 2))
+                     : "memory");
+      }
     }
   }
 
@@ -449,6 +466,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   auto careful_tiles = [&](auto SELF, const uint16_t* src_k, const uint16_t* src_v, const int from, const int to, const bool loaded) __attribute__((always_inline)) {
     constexpr bool CAUSAL = decltype(SELF)::value;
     if (from >= to) return;
+    const bool plain = late_args()->off_16 & (CAUSAL && MODE == 2 ? kUnalignedKv2 : kUnalignedKv);
     Tile cur = tile_at(SELF, from);
     int buf = from % kBufs;
     if (loaded) {
@@ -458,8 +476,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         cur.base -= cur.lo;
       }
     } else {
-      dma_rows(src_k, cur.base, cur.hi, lds_k + buf * kKTile, dma_off_k);
-      dma_rows(src_v, cur.base, cur.hi, lds_v + buf * kVTile, dma_off_v);
+      dma_rows(src_k, cur.base, cur.hi, lds_k + buf * kKTile, dma_off_k, plain);
+      dma_rows(src_v, cur.base, cur.hi, lds_v + buf * kVTile, dma_off_v, plain);
       dma_wait();
       lds_barrier();
     }
@@ -471,8 +489,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
       Tile next = cur;
       if (t + 1 < to) {
         next = tile_at(SELF, t + 1);
-        dma_rows(src_k, next.base, next.hi, lds_k + buf * kKTile, dma_off_k);
-        dma_rows(src_v, next.base, next.hi, lds_v + buf * kVTile, dma_off_v);
+        dma_rows(src_k, next.base, next.hi, lds_k + buf * kKTile, dma_off_k, plain);
+        dma_rows(src_v, next.base, next.hi, lds_v + buf * kVTile, dma_off_v, plain);
       }
       if (cur.hi - cur.lo < kKvTile) {
         // places of V that are not the tile's are zero: 0 * garbage cannot make NaN (their scores are hidden below)
@@ -753,7 +771,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   const bool self_first = kHasSelf && nf_pool + np_pool == 0;
   const bool started = self_first ? nf_self > 0 : nf_pool > 0;
   if (kHasPool && nf_pool > 0) first_loads(kPoolPhase, a.k, a.v, nf_pool + (np_pool > 0));
-  if (kHasSelf && self_first && nf_self > 0) first_loads(kSelfPhase, self_k, self_v, nf_self + (np_self > 0));
+  if (kHasSelf && self_first && nf_self > 0) first_loads(kSelfPhase, self_k(), self_v(), nf_self + (np_self > 0));
   if (started) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
@@ -767,22 +785,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     careful_tiles(kPoolPhase, a.k, a.v, from, nf_pool + np_pool, from > 0);
   }
   if constexpr (kHasSelf) {
+    const uint16_t *new_k = self_k(), *new_v = self_v();
     int from = 0;
     if (nf_self > 0) {
-      if (fast_phase(kSelfPhase, self_k, self_v, nf_self, np_self > 0, self_first, kHasPool && nf_pool + np_pool > 0)) {
+      if (fast_phase(kSelfPhase, new_k, new_v, nf_self, np_self > 0, self_first, kHasPool && nf_pool + np_pool > 0)) {
         from = nf_self;
       } else {
         reset_state();
         if constexpr (kHasPool) careful_tiles(kPoolPhase, a.k, a.v, 0, nf_pool + np_pool, false);
       }
     }
-    careful_tiles(kSelfPhase, self_k, self_v, from, nf_self + np_self, from > 0);     // the last ones are on the diagonal
+    careful_tiles(kSelfPhase, new_k, new_v, from, nf_self + np_self, from > 0);     // the last ones are on the diagonal
   }
 
-  // ---- epilogue: normalise, LSE, store (its arguments are read here: held in scalar registers from the start they push
-  // others of the loop's out; the empty asm keeps the loads in this place) ----
-  auto args = (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(args));
+  // ---- epilogue: normalise, LSE, store ----
+  const auto args = late_args();
   if (wave_row >= n_rows) return;
   // place of the lane's row behind the tile's first, in rows of the output; -1: the row does not exist
   const size_t out_row0 = (size_t)wk.out_row * args->q_heads + g * G;      // (one-pass rows: out_row is the tile's first token)
@@ -795,7 +812,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   for (int rg = 0; rg < kRG; ++rg) {
     const float l_tot = xor32_sum(l_run[rg]);
     const float lr_tot = l_tot + xor32_sum(lr_run[rg]);
-    const int rel = row_ok[rg] ? tok_local[rg] * args->q_heads + head_j[rg] : -1;
+    const int row = wave_row + 32 * rg + l32, row_tok = row / args->group;         // (again: two registers less through the loops)
+    const int rel = row_tok < wk.n_tok ? row_tok * args->q_heads + row - row_tok * args->group : -1;
     float inv = lr_tot > 0.f ? 1.f / lr_tot : 0.f;
     float lse_val = l_tot > 0.f ? m_ref[rg] * args->scale + __logf(l_tot) : -INFINITY;
     if (MODE == 2 && wk.n_prior > 0) {
@@ -818,19 +836,26 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         // HBM, 134 MB read as the row tiles of a round end together, either way)
         const size_t prow0 = (size_t)(unit::scalar_loads(args->prior_rows)[wk.prior_off + j] + wk.out_row - wk.kv_off) * args->q_heads + g * G;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll 2
-        for (int i = 0; i < 16; ++i) {
+        auto prior_chunk = [&](int i) __attribute__((always_inline)) -> const float* {     // of row 2 i + lane / 32
           const int r_ = 2 * i + (lane >> 5);
-          const float* src = args->prior_out + (prow0 + __shfl(own, r_)) * kHeadDim + 4 * ((lane & 31) ^ r_);
-          unsigned saved_m0;
-          asm volatile("s_mov_b32 %[sv], m0\n\ts_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[p], off\n\ts_mov_b32 m0, %[sv]"
-                       : [sv] "=&s"(saved_m0)
-                       : [p] "v"(src), [d] "s"(prior_lds + (unsigned)i * 1024u)
-                       : "memory");
+          return args->prior_out + (prow0 + __shfl(own, r_)) * kHeadDim + 4 * ((lane & 31) ^ r_);
+        };
+        if (args->off_16 & kUnalignedPrior) {
+#pragma unroll 1
+          for (int i = 0; i < 16; ++i) ((uint4*)(mine + i * 1024))[lane] = *(const uint4*)prior_chunk(i);
+        } else {
+#pragma unroll 2
+          for (int i = 0; i < 16; ++i) {
+            unsigned saved_m0;
+            asm volatile("s_mov_b32 %[sv], m0\n\ts_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[p], off\n\ts_mov_b32 m0, %[sv]"
+                         : [sv] "=&s"(saved_m0)
+                         : [p] "v"(prior_chunk(i)), [d] "s"(prior_lds + (unsigned)i * 1024u)
+                         : "memory");
+          }
         }
         const float L = args->prior_lse[prow0 + own];
         dma_wait();
-        asm volatile("" ::: "memory");
+        lane_order();
         if (!(L > -INFINITY)) continue;              // a partial without keys has weight 0
         const float Mn = fmaxf(M, L);
         const float ea = M > -INFINITY ? __expf(M - Mn) : 0.f, eb = __expf(L - Mn);

@@ -1370,6 +1370,35 @@ def test_row_tiles_halved_between_two_workgroups_and_lists_in_short_pieces(hq, h
     run.close()
 
 
+@pytest.mark.parametrize("flags", [B.TL_PLAN_SELF_BLOCK, B.TL_PLAN_SELF_BLOCK | B.TL_PLAN_FUSE_ROWS, B.TL_PLAN_SELF_BLOCK | B.TL_PLAN_FUSE_TAILS])
+@pytest.mark.parametrize("out_bf16", [False, True])
+def test_tensors_off_the_16_byte_grid_give_the_same_bits(flags, out_bf16):
+    """Queries, new K/V of short chunks, partials and outputs that start 8 bytes behind a 16-byte boundary: what goes to LDS by direct
+    loads otherwise goes through registers then, and every output is bit for bit that of aligned tensors."""
+    _say("tensors at 8 bytes, flags %d" % flags)
+    lists = [[0, 1, 2], [0, 1, 3, 4], [0, 1], [5, 6, 7, 8, 9]]
+    b = _batch_of_lists("offset", 86, 8, 2, 64, lists, {i: 64 if i != 9 else 21 for i in range(10)}, [40, 63, 17, 5])
+    run = H.run_gpu(b, flags=flags, compute_units=0, out_bf16=out_bf16)
+
+    def moved(t):
+        n = 8 // t.element_size()
+        flat = torch.zeros(t.numel() + n, dtype=t.dtype, device=t.device)
+        view = flat[n:].view(t.shape)
+        view.copy_(t)
+        assert view.data_ptr() % 16 == 8
+        return view
+
+    q, kn, vn, outp, lsep, out, lse = (moved(t) for t in (run.q, run.k_new, run.v_new, torch.zeros_like(run.out_partial),
+                                                          torch.zeros_like(run.lse_partial), torch.zeros_like(run.out), torch.zeros_like(run.lse)))
+    B.tl_segment_attn(run.pool, run.plan, q, b.scale, outp, lsep)
+    B.tl_causal_block(run.plan, q, kn, vn, b.scale, outp, lsep)
+    B.tl_merge(run.plan, outp, lsep, out, out_bf16, lse)
+    B.tl_fused_attn(run.pool, run.plan, q, kn, vn, b.scale, out, out_bf16, lse, prior_partial=outp, prior_lse=lsep)
+    torch.cuda.synchronize()
+    assert torch.equal(out, run.out) and torch.equal(lse, run.lse)
+    run.close()
+
+
 @pytest.mark.parametrize("hq,hkv,n_decode", [(4, 1, 23), (8, 2, 20), (10, 5, 20), (32, 8, 21), (18, 9, 8)])
 def test_units_in_turn_beside_row_tiles(hq, hkv, n_decode):
     """For 16 CUs: row tiles that take 0.95 to 3.5 of the units' time, so that half as many workgroups as units take two of them each (an
