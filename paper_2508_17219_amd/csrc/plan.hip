@@ -89,16 +89,22 @@ double joint_tiles(double units, int64_t unit_blocks, double tiles, int64_t n_cu
 
 // Workgroups that take the split-K units beside row tiles.  All units at once keep HBM busy and leave row tiles the few CUs that are
 // over; with half as many workgroups that take two units each in turn, row tiles and units run side by side for longer.  That pays
-// where the two take about as long, units by their bytes and row tiles by their KV tiles: of 125 random batches of 1 to 8 chunks
-// beside 4 to 190 decoded tokens 44 have row tiles of 0.95 to 3.5 of the units' time and half a round to one and a half of unit
-// workgroups; tl_segment_attn takes 0.94 of its time in their mean (0.78 to 1.08, five of them more than 1.01; the mixed batch of
-// perf/cases.py 451 -> 441 us).  Below, the units are the longer part and want the CUs (20 row tiles beside 116 decoded tokens
-// 1.42, twelve batches of 0.5 to 0.95 0.67 to 1.28); above, it makes no difference (0.95 to 1.08).  Three in turn: 1.01 in the mean.
+// where the two take about as long, units by their bytes and row tiles by their KV tiles, and row tiles share the CUs beside the
+// units evenly: tl_segment_attn of 878 random batches of 1 to 8 chunks beside 4 to 91 decoded tokens, row tiles of 0.95 to 3.5 of
+// the units' time, half a round to one and a half of unit workgroups, against all units at once:
+//   row tiles in 1.1 to 2.25 rounds of the other CUs: 0.97 (0.80 to 1.14), every fourth more than 1.02, as the second round then
+//     starts where all units at once would be over; otherwise 0.94;
+//   fewer than five eighths of a round of unit workgroups (half of the CUs are free without) 0.99, more than 5/4 rounds 0.98;
+//   in what is left, 511 batches, 0.93 (0.75 to 1.14), 17 of them more than 1.02 and 4 more than 1.05 (mixed batch of perf/cases.py 451 -> 441 us).
+// Units longer than the row tiles want the CUs (20 row tiles beside 116 decoded tokens 1.42, twelve batches of 0.5 to 0.95 0.67
+// to 1.28); row tiles longer than 3.5 make no difference (0.95 to 1.08).  Three in turn: 1.01 in the mean.
 constexpr double kUnitBytesPerUs = 6.0e6, kRowTileUs = 1.5;
-int64_t plan_unit_lanes(int64_t unit_blocks, double unit_bytes, double row_us, int64_t n_cu) {
+int64_t plan_unit_lanes(int64_t unit_blocks, double unit_bytes, int64_t row_blocks, double row_us, int64_t n_cu) {
   const double units = unit_bytes / kUnitBytesPerUs, rows = n_cu > 0 ? row_us / (double)n_cu : 0;
-  const bool side_by_side = 2 * unit_blocks >= n_cu && 2 * unit_blocks <= 3 * n_cu && rows >= 0.95 * units && rows <= 3.5 * units;
-  return side_by_side ? (unit_blocks + 1) / 2 : unit_blocks;
+  const int64_t lanes = (unit_blocks + 1) / 2;
+  if (8 * unit_blocks < 5 * n_cu || 4 * unit_blocks > 5 * n_cu || rows < 0.95 * units || rows > 3.5 * units) return unit_blocks;
+  const double rounds = (double)row_blocks / (double)(n_cu - lanes);
+  return rounds <= 1.1 || rounds > 2.25 ? lanes : unit_blocks;
 }
 
 struct RowWork {
@@ -777,7 +783,8 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       double row_us = 0;
       for (const Work& w : p->tiles) row_us += kRowTileUs * (double)((w.n_full + w.n_part + kTileStart) * pool->kv_heads);
       p->unit_lanes = (int32_t)plan_unit_lanes(unit_load.units * unit_head_blocks(pool->kv_heads, p->unit_heads_log2),
-                                               (double)unit_load.tokens * pool->kv_heads * (4 * kHeadDim), row_us, n_cu);
+                                               (double)unit_load.tokens * pool->kv_heads * (4 * kHeadDim),
+                                               (int64_t)p->tiles.size() * pool->kv_heads, row_us, n_cu);
     }
     p->tok.resize(own_toks);
     std::iota(p->tok.begin(), p->tok.end(), 0);

@@ -1399,14 +1399,14 @@ def test_tensors_off_the_16_byte_grid_give_the_same_bits(flags, out_bf16):
     run.close()
 
 
-@pytest.mark.parametrize("hq,hkv,n_decode", [(4, 1, 23), (8, 2, 20), (10, 5, 20), (32, 8, 21), (18, 9, 8)])
+@pytest.mark.parametrize("hq,hkv,n_decode", [(4, 1, 23), (4, 1, 19), (8, 2, 20), (10, 5, 20), (32, 8, 21), (32, 8, 14), (18, 9, 8), (18, 9, 7)])
 def test_units_in_turn_beside_row_tiles(hq, hkv, n_decode):
     """For 16 CUs: row tiles that take 0.95 to 3.5 of the units' time, so that half as many workgroups as units take two of them each (an
     odd number of units, slices of one head that meet at a barrier, waves without a head), units of several lengths but for those, every row."""
     _say("units in turn hq=%d hkv=%d decode=%d" % (hq, hkv, n_decode))
     lists, fills, nid = [], {}, 0
     for r in range(n_decode + 1):
-        n = 1400 // 64 if r == n_decode else 18 if hkv == 9 else 4 + r % 13
+        n = 1400 // 64 if r == n_decode else 20 if hkv == 9 else 4 + r % 13
         lists.append(list(range(nid, nid + n)))
         nid += n
     fills = {i: 64 for i in range(nid)}
