@@ -118,8 +118,12 @@ def _host(a, dtype) -> np.ndarray:
 
 def _offsets(counts, n: int) -> np.ndarray:
     """0 and the running sums of n counts."""
-    if type(counts) is list and len(counts) == n:
-        return np.array([0, *accumulate(counts)], np.int32)
+    # (plain ints alone: narrow numpy scalars would be added in their own width, one-element lists strung together)
+    if type(counts) is list and len(counts) == n and set(map(type, counts)) <= {int}:
+        try:
+            return np.array([0, *accumulate(counts)], np.int32)
+        except OverflowError:
+            pass
     out = np.zeros(n + 1, np.int32)
     out[1:] = np.cumsum(counts)
     return out

@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import tokenlake_oracle as orc
 from paper_2508_17219_amd import binding as B
@@ -630,6 +631,20 @@ def test_batched_append_validates_every_chain_before_anything_changes():
     B.tl_pool_append_batch(pool, [11, None], [[], []], [0, 0], None, None)   # chains with nothing to add
     assert state() == before
     B.tl_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("counts", [
+    [3, 0, 5], [], [2**31 - 1, 1], [2**32 + 5], [True, False, True], [1.75, 2.5], [[1], [2]], (1, 2), range(3), np.array([7, 9]),
+    [np.int8(100), np.int8(100)], [np.uint8(200), np.int64(100)], np.array([200, 100], np.uint8), [torch.tensor(200, dtype=torch.uint8)] * 2,
+    [np.array([1]), np.array([2])], [np.float32(2**24), np.float32(1)],
+], ids=repr)
+def test_row_counts_of_any_type_become_the_same_offsets(counts):
+    """Counts that a caller took out of an array or a tensor, of whatever width: the offsets are numpy's running sums."""
+    n = len(counts)
+    expect = np.zeros(n + 1, np.int32)
+    expect[1:] = np.cumsum(counts)
+    got = B._offsets(counts, n)
+    assert got.dtype == np.int32 and got.tolist() == expect.tolist()
 
 
 def test_hot_slots_match_the_oracles_prefix_tree():
