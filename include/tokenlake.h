@@ -33,7 +33,8 @@
  *    return TL_EINVAL and enqueue nothing; build a new plan (Section 3.2: plans are made per
  *    iteration).  tl_pool_release and a put of a resident id change no slot and keep plans valid.
  *    A plan may outlive its pool only to be destroyed or read back (info, export, hot slots).
- *  - All tensors are dense, row-major, bf16 = 16-bit brain float bit patterns.
+ *  - All tensors are dense, row-major, bf16 = 16-bit brain float bit patterns.  They may start at any multiple of
+ *    their element's size; row tiles take tensors that do not start on a 16-byte boundary a slower way, to the same bits.
  *  - head_dim must be 128; q_heads must be a multiple of kv_heads, at most 32 times it; seg_len must
  *    be a multiple of 64.  Anything else is TL_EINVAL.
  *  - The normalizer is the natural-log log-sum-exp of the scaled scores.  A row with no

@@ -24,10 +24,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kLdsStride = 136;
 constexpr int kVStrideUnit = 144;
 
-// Tensors that do not start on a 16-byte boundary (a view into the middle of a row): row tiles read queries, masked tiles and prior
-// partials from them by way of registers.
-constexpr int kUnalignedQ = 1, kUnalignedKv = 2, kUnalignedKv2 = 4, kUnalignedPrior = 8;
-
 struct AttnArgs {
   const uint16_t* q;      // [n_tokens, q_heads, 128] bf16
   const uint16_t* k;      // pool K base, or new-token K [n_tokens, kv_heads, 128]
@@ -52,7 +48,7 @@ struct AttnArgs {
   float* lse;             // [rows, q_heads]
   int32_t n_tokens;       // rows of the new tokens' K/V
   int32_t q_heads, kv_heads, group, n_work;   // group = q_heads / kv_heads
-  int32_t off_16;         // kUnaligned*: what does not start on a 16-byte boundary, which direct loads to LDS ask for
+  int32_t off_grid;       // a tensor that row tiles read does not start on a 16-byte boundary (a view into the middle of a row)
   int32_t halve;          // a row tile is two workgroups: its first half_row_tile(group) tokens and the rest
   const Work* units;      // row tiles and split-K units in one launch: the units (work: the row tiles)
   int32_t n_units;

@@ -220,8 +220,9 @@ __global__ __launch_bounds__(256) void single_token_self_kernel(const uint16_t* 
   if (c4 == 0) lse[row] = s * scale;
 }
 
-bool off_16(const void* p) { return ((uintptr_t)p & 15) != 0; }
-int32_t off_16(const void* k, const void* v, int32_t flag) { return off_16(k) || off_16(v) ? flag : 0; }
+// Does one of them not start on a 16-byte boundary?
+template <typename... P>
+bool off_grid(const P*... p) { return ((... | (uintptr_t)p) & 15) != 0; }
 
 void fill_args(AttnArgs& a, const tl_plan* plan, const PlanDev& d, const void* q, float scale, float* out, float* lse) {
   a.q = (const uint16_t*)q;
@@ -233,7 +234,7 @@ void fill_args(AttnArgs& a, const tl_plan* plan, const PlanDev& d, const void* q
   a.part_tile = d.part_tile;
   a.tile_lm = plan->any_repeat ? d.tile_lm : nullptr;   // null: every tile has multiplicity 1
   a.part_lm = plan->any_repeat ? d.part_lm : nullptr;
-  a.off_16 = off_16(q) ? kUnalignedQ : 0;
+  a.off_grid = off_grid(q);
   a.halve = 0;
   a.units = nullptr;
   a.n_units = a.unit_lanes = 0;
@@ -274,7 +275,7 @@ tl_status fused_rows(const tl_pool* pool, const tl_plan* plan, const void* base,
   a.v = (const uint16_t*)pool->v_dev;
   a.k2 = (const uint16_t*)k_new_dev;
   a.v2 = (const uint16_t*)v_new_dev;
-  a.off_16 |= off_16(a.k, a.v, kUnalignedKv) | off_16(a.k2, a.v2, kUnalignedKv2) | (off_16(prior_partial) ? kUnalignedPrior : 0);
+  a.off_grid |= off_grid(a.k, a.v, a.k2, a.v2, prior_partial);
   a.final_out = out_dev;
   a.final_lse = lse_out;
   a.final_is_bf16 = out_is_bf16 ? 1 : 0;
@@ -353,7 +354,7 @@ tl_status tl_segment_attn(const tl_pool* pool, tl_plan* plan, const void* q_dev,
   fill_args(a, plan, d, q_dev, scale, out_partial, lse);
   a.k = (const uint16_t*)pool->k_dev;
   a.v = (const uint16_t*)pool->v_dev;
-  a.off_16 |= off_16(a.k, a.v, kUnalignedKv);
+  a.off_grid |= off_grid(a.k, a.v);
   a.work = d.tiles;
   a.n_work = (int)plan->tiles.size();
   a.halve = plan->halve_tiles;
@@ -362,7 +363,7 @@ tl_status tl_segment_attn(const tl_pool* pool, tl_plan* plan, const void* q_dev,
   a.unit_lanes = plan->unit_lanes;
   // (a launch has less than 2^32 threads: 2^23 blocks of 512, the unit blocks rounded up to a multiple of 8)
   const int64_t blocks = (int64_t)a.n_work * a.kv_heads + a.unit_lanes + 7;
-  if (a.n_work > 0 && a.n_units > 0 && blocks < (1 << 23)) return launch_tiles_and_units(a, st);
+  if (a.n_work > 0 && a.n_units > 0 && !a.off_grid && blocks < (1 << 23)) return launch_tiles_and_units(a, st);
   rc = launch_pool_row_tiles(a, a.n_work, st);
   if (rc != TL_OK) return rc;
   a.work = d.units;
@@ -384,7 +385,7 @@ tl_status tl_causal_block(tl_plan* plan, const void* q_dev, const void* k_new_de
   fill_args(a, plan, d, q_dev, scale, out_partial, lse);
   a.k = (const uint16_t*)k_new_dev;
   a.v = (const uint16_t*)v_new_dev;
-  a.off_16 |= off_16(a.k, a.v, kUnalignedKv);
+  a.off_grid |= off_grid(a.k, a.v);
   a.work = d.ctiles;
   a.n_work = (int)plan->ctiles.size();
   a.halve = plan->halve_ctiles;

@@ -130,6 +130,13 @@ __device__ __forceinline__ float max16(const f32x16& s) {
   return fmaxf(fmaxf(fmaxf(a, b), fmaxf(c, d)), fmaxf(e, s[15]));
 }
 
+// 16 bytes from any address
+__device__ __forceinline__ uint4 load_any(const char* p) {
+  uint4 x;
+  __builtin_memcpy(&x, p, sizeof(x));
+  return x;
+}
+
 __host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) { return ((unsigned)a.unit_lanes + 7u) & ~7u; }
 
 // MODE 0: pool work item (tile lists) -> partial.  MODE 1: causal block of the new tokens ->
@@ -145,7 +152,12 @@ __host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) { return ((un
 // at most.  (Groups of eight blocks of each kind in turn: a unit takes a whole round whatever runs beside it, so the
 // units' second round ends late, a tenth slower.)  The branch is in the kernel itself, not around a function that both
 // kernels call: passed to such a function, the block's number cost the one-pass kernel two spilled registers.
-template <int MODE, int VREAD, bool JOINT = false>
+//
+// READ: how memory is read.  Bit 0: scalar LDS reads of V in place of transposing ones.  Bit 1 (kOffGrid): some tensor does not
+// start on a 16-byte boundary, which direct loads to LDS ask for; what they bring goes through registers instead, to the
+// same places in the same order, so that the results are the same bits.  (A variant of its own: aligned tensors pay nothing.)
+constexpr int kScalarV = 1, kOffGrid = 2;
+template <int MODE, int READ, bool JOINT = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void row_tile_attn_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   if (JOINT && blockIdx.x < unit_blocks(a)) {
@@ -154,7 +166,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     for (int first = 0; first < n; first += lanes) {          // forth and back, as the units come longest first
       const int i = (first / lanes) & 1 ? first + lanes - 1 - lane_no : first + lane_no;
       if (first > 0) __syncthreads();                           // the LDS is free again
-      if (i < n) unit::splitk_unit<VREAD, true>(a, a.units[i % a.n_units], i / a.n_units, lds);
+      if (i < n) unit::splitk_unit<READ & kScalarV, true>(a, a.units[i % a.n_units], i / a.n_units, lds);
     }
     return;
   }
@@ -279,6 +291,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     const char* trow = (const char*)src + (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane(base) * kv_bytes;
     const unsigned dst0 = lds_base_addr + (unsigned)(tile - lds) * 2u + dma_wave_off;
     const unsigned dst1 = dst0 + (unsigned)(kWaves * 4 * kHeadDim) * 2u;
+    if constexpr (READ & kOffGrid) {
+      char* at = (char*)tile + dma_wave_off;
+      ((uint4*)at)[lane] = load_any(trow + off[0]);
+      ((uint4*)(at + kWaves * 4 * kHeadDim * 2))[lane] = load_any(trow + off[1]);
+      return;
+    }
     // address = wave-uniform 64-bit tile base (scalar registers) + this lane's constant 32-bit offset;
     // the LDS destination travels in M0, which the compiler does not accept as a clobber: its value
     // is put back before the statement ends
@@ -292,16 +310,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         : [o0] "v"(off[0]), [o1] "v"(off[1]), [d0] "s"(dst0), [d1] "s"(dst1), [b] "s"(trow)
         : "memory");
   };
-  // the same for the first `rows` rows of a tile; the others' places in LDS keep what they hold.  `plain`: through registers
-  auto dma_rows = [&](const uint16_t* src, int base, int rows, uint16_t* tile, const unsigned (&off)[kDmaPerWave], const bool plain) __attribute__((always_inline)) {
+  // the same for the first `rows` rows of a tile; the others' places in LDS keep what they hold
+  auto dma_rows = [&](const uint16_t* src, int base, int rows, uint16_t* tile, const unsigned (&off)[kDmaPerWave]) __attribute__((always_inline)) {
     const char* trow = (const char*)src + (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane(base) * kv_bytes;
 #pragma unroll
     for (int u = 0; u < kDmaPerWave; ++u) {
       const unsigned dst = lds_base_addr + (unsigned)(tile - lds) * 2u + dma_wave_off + (unsigned)(u * kWaves * 4 * kHeadDim) * 2u;
       unsigned saved_m0;
       if (4 * (wave + kWaves * u) + (lane >> 4) >= rows) continue;
-      if (plain)
-        ((uint4*)((char*)tile + dma_wave_off + u * kWaves * 4 * kHeadDim * 2))[lane] = *(const uint4*)(trow + off[u]);
+      if constexpr (READ & kOffGrid)
+        ((uint4*)((char*)tile + dma_wave_off + u * kWaves * 4 * kHeadDim * 2))[lane] = load_any(trow + off[u]);
       else
         asm volatile("s_mov_b32 %[sv], m0\n\ts_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[o], %[b]\n\ts_mov_b32 m0, %[sv]"
                      : [sv] "=&s"(saved_m0)
@@ -310,8 +328,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
     }
   };
   // wait for all of this wave's direct loads (vmcnt(0); the other counters are left alone so that
-  // LDS operand reads already in flight stay in flight)
-  auto dma_wait = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };
+  // LDS operand reads already in flight stay in flight); for its LDS writes where they take the loads' place
+  auto dma_wait = [&]() __attribute__((always_inline)) {
+    if constexpr (READ & kOffGrid) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
+  };
 
   // ---- queries: a wave's 32 rows by direct loads, 256 bytes of a row by 16 lanes, in the swizzle of a K tile; to
   // registers once the first tiles are on their way too.  (Loaded by the lanes that hold them, 16 bytes of 32 rows an
@@ -326,9 +347,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
       const int r_ = 4 * i + (lane >> 4);
       return (const char*)a.q + (size_t)__shfl(q_row[0], r_) * (2 * kHeadDim) + 16 * ((lane & 15) ^ (r_ & 15));
     };
-    if (a.off_16 & kUnalignedQ) {
+    if constexpr (READ & kOffGrid) {
 #pragma unroll 1
-      for (int i = 0; i < 8; ++i) ((uint4*)((char*)q_lds + i * (4 * kHeadDim * 2)))[lane] = *(const uint4*)q_chunk(i);
+      for (int i = 0; i < 8; ++i) ((uint4*)((char*)q_lds + i * (4 * kHeadDim * 2)))[lane] = load_any(q_chunk(i));
     } else {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -354,7 +375,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   // tokens 16 sp + {4h..4h+3, 8+4h..8+4h+3} -- the order in which the score registers hold them
   auto v_operand = [&](const uint16_t* vt, int hb, int sp, int d) __attribute__((always_inline)) -> bf16x8 {
     const int kvb = 32 * hb + 16 * sp;
-    if (VREAD == 0) {
+    if constexpr (!(READ & kScalarV)) {
       const int blk = lane >> 4, jj = lane & 15;
       // logical chunk 4 d + 2 (blk & 1) + (jj & 3) / 2 of row kvb + 4 (blk >> 1) + jj / 4 (row & 3 = jj / 4)
       const int chunk = (4 * d + 2 * (blk & 1) + ((jj & 3) >> 1)) ^ (4 * (jj >> 2));
@@ -466,7 +487,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   auto careful_tiles = [&](auto SELF, const uint16_t* src_k, const uint16_t* src_v, const int from, const int to, const bool loaded) __attribute__((always_inline)) {
     constexpr bool CAUSAL = decltype(SELF)::value;
     if (from >= to) return;
-    const bool plain = late_args()->off_16 & (CAUSAL && MODE == 2 ? kUnalignedKv2 : kUnalignedKv);
     Tile cur = tile_at(SELF, from);
     int buf = from % kBufs;
     if (loaded) {
@@ -476,8 +496,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
         cur.base -= cur.lo;
       }
     } else {
-      dma_rows(src_k, cur.base, cur.hi, lds_k + buf * kKTile, dma_off_k, plain);
-      dma_rows(src_v, cur.base, cur.hi, lds_v + buf * kVTile, dma_off_v, plain);
+      dma_rows(src_k, cur.base, cur.hi, lds_k + buf * kKTile, dma_off_k);
+      dma_rows(src_v, cur.base, cur.hi, lds_v + buf * kVTile, dma_off_v);
       dma_wait();
       lds_barrier();
     }
@@ -489,8 +509,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
       Tile next = cur;
       if (t + 1 < to) {
         next = tile_at(SELF, t + 1);
-        dma_rows(src_k, next.base, next.hi, lds_k + buf * kKTile, dma_off_k, plain);
-        dma_rows(src_v, next.base, next.hi, lds_v + buf * kVTile, dma_off_v, plain);
+        dma_rows(src_k, next.base, next.hi, lds_k + buf * kKTile, dma_off_k);
+        dma_rows(src_v, next.base, next.hi, lds_v + buf * kVTile, dma_off_v);
       }
       if (cur.hi - cur.lo < kKvTile) {
         // places of V that are not the tile's are zero: 0 * garbage cannot make NaN (their scores are hidden below)
@@ -840,9 +860,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
           const int r_ = 2 * i + (lane >> 5);
           return args->prior_out + (prow0 + __shfl(own, r_)) * kHeadDim + 4 * ((lane & 31) ^ r_);
         };
-        if (args->off_16 & kUnalignedPrior) {
+        if constexpr (READ & kOffGrid) {
 #pragma unroll 1
-          for (int i = 0; i < 16; ++i) ((uint4*)(mine + i * 1024))[lane] = *(const uint4*)prior_chunk(i);
+          for (int i = 0; i < 16; ++i) ((uint4*)(mine + i * 1024))[lane] = load_any((const char*)prior_chunk(i));
         } else {
 #pragma unroll 2
           for (int i = 0; i < 16; ++i) {
@@ -927,10 +947,12 @@ template <int MODE>
 tl_status launch_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) {
   if (n_work == 0) return TL_OK;
   const dim3 grid((unsigned)n_work * a.kv_heads * (a.halve ? 2 : 1)), block(kThreads);
-  static std::atomic<uint64_t> allowed[2];
-  const bool scalar_v = get_option_vread() != 0;
-  auto kern = scalar_v ? row_tile_attn_kernel<MODE, 1> : row_tile_attn_kernel<MODE, 0>;
-  const tl_status rc = allow_lds((const void*)kern, kLds<MODE>, allowed[scalar_v]);
+  static std::atomic<uint64_t> allowed[4];
+  const int read = (get_option_vread() ? kScalarV : 0) | (a.off_grid ? kOffGrid : 0);
+  constexpr decltype(&row_tile_attn_kernel<MODE, 0>) kernels[4] = {row_tile_attn_kernel<MODE, 0>, row_tile_attn_kernel<MODE, 1>,
+                                                                    row_tile_attn_kernel<MODE, 2>, row_tile_attn_kernel<MODE, 3>};
+  auto kern = kernels[read];
+  const tl_status rc = allow_lds((const void*)kern, kLds<MODE>, allowed[read]);
   if (rc != TL_OK) return rc;
   hipLaunchKernelGGL(kern, grid, block, kLds<MODE>, st, a);
   TL_HIP(hipGetLastError());
@@ -943,6 +965,7 @@ tl_status launch_pool_row_tiles(const AttnArgs& a, int n_work, hipStream_t st) {
 tl_status launch_tiles_and_units(const AttnArgs& a, hipStream_t st) {
   if (!unit::can_deal(a))
     TL_FAIL(TL_EINVAL, "launch_tiles_and_units: %d kv heads cannot be dealt %d to a workgroup", a.kv_heads, 1 << a.unit_heads_log2);
+  if (a.off_grid) TL_FAIL(TL_EINVAL, "launch_tiles_and_units: tensors off the 16-byte grid go in two launches");
   const dim3 grid(unit_blocks(a) + (unsigned)a.n_work * a.kv_heads), block(kThreads);
   static std::atomic<uint64_t> allowed[2];
   const bool scalar_v = get_option_vread() != 0;

@@ -1399,6 +1399,52 @@ def test_tensors_off_the_16_byte_grid_give_the_same_bits(flags, out_bf16):
     run.close()
 
 
+def _moved(t, offset, fill=0):
+    """A copy of t that starts `offset` bytes behind a 16-byte boundary (floats: a multiple of four)."""
+    n = max(offset // t.element_size(), 1)
+    flat = torch.full((t.numel() + n,), fill, dtype=t.dtype, device=t.device)
+    view = flat[n:].view(t.shape)
+    view.copy_(t)
+    assert flat.data_ptr() % 16 == 0 and view.data_ptr() % 16 == max(offset, t.element_size())
+    return view
+
+
+@pytest.mark.parametrize("flags", [B.TL_PLAN_SELF_BLOCK, B.TL_PLAN_SELF_BLOCK | B.TL_PLAN_FUSE_ROWS, B.TL_PLAN_SELF_BLOCK | B.TL_PLAN_FUSE_TAILS])
+@pytest.mark.parametrize("which", ["pool", "new", "queries", "all"])
+@pytest.mark.parametrize("offset,vread", [(8, 0), (2, 0), (8, 1)])
+@pytest.mark.parametrize("k_boost", [(), (2, 1 << 30, 32.0)])
+def test_full_tiles_off_the_16_byte_grid_give_the_same_bits(flags, which, offset, vread, k_boost):
+    """Pool and new K/V off the grid where row tiles have full tiles, masked tiles behind full ones, and the careful path: 64, 65, 200 and
+    331 new tokens, private and shared lists with a fill that is no tile, a decoded token beside them (row tiles and units)."""
+    _say("full tiles at %d bytes, %s, flags %d, vread %d, boost %r" % (offset, which, flags, vread, k_boost))
+    lists = [[0, 1, 2, 11], [0, 1, 3, 4], [0, 1], [5, 6, 7, 8, 9], [10, 4]]
+    b = _batch_of_lists("full tiles", 87, 8, 2, 128, lists, {i: {9: 21, 11: 65, 4: 127}.get(i, 128) for i in range(12)}, [64, 65, 200, 331, 1])
+    b.k_boost = k_boost
+    B.tl_set_option("vread", vread)
+    try:
+        run = H.run_gpu(b, flags=flags, compute_units=0)
+        _check_all_requests(run)
+        move = lambda t, name, fill=0: _moved(t, offset, fill) if which in (name, "all") else t
+        pk, pv = (move(t, "pool", float("nan")) for t in (run.pool_k, run.pool_v))
+        kn, vn = (move(t, "new", float("nan")) for t in (run.k_new, run.v_new))
+        q = move(run.q, "queries", float("nan"))
+        outp, lsep, out, lse = (move(torch.full_like(t, float("nan")), "queries") for t in (run.out_partial, run.lse_partial, run.out, run.lse))
+        pool = B.tl_pool_create(b.n_slots, b.seg_len, b.kv_heads, b.head_dim, pk, pv)
+        B.tl_pool_adopt(pool, b.pool_ids, b.pool_slots, b.pool_fills)
+        plan = B.tl_plan_create(pool, b.q_heads, b.req_row_ptr, b.req_seg_ptr, b.seg_ids, flags, 0, 0)
+        B.tl_segment_attn(pool, plan, q, b.scale, outp, lsep)
+        B.tl_causal_block(plan, q, kn, vn, b.scale, outp, lsep)
+        B.tl_merge(plan, outp, lsep, out, False, lse)
+        B.tl_fused_attn(pool, plan, q, kn, vn, b.scale, out, False, lse, prior_partial=outp, prior_lse=lsep)
+        torch.cuda.synchronize()
+        assert torch.equal(out, run.out) and torch.equal(lse, run.lse)
+        B.tl_plan_destroy(plan)
+        B.tl_pool_destroy(pool)
+        run.close()
+    finally:
+        B.tl_set_option("vread", 0)
+
+
 @pytest.mark.parametrize("hq,hkv,n_decode", [(4, 1, 23), (4, 1, 19), (8, 2, 20), (10, 5, 20), (32, 8, 21), (32, 8, 14), (18, 9, 8), (18, 9, 7)])
 def test_units_in_turn_beside_row_tiles(hq, hkv, n_decode):
     """For 16 CUs: row tiles that take 0.95 to 3.5 of the units' time, so that half as many workgroups as units take two of them each (an
