@@ -151,22 +151,27 @@ __host__ __device__ inline unsigned unit_blocks(const AttnArgs& a) { return ((un
 // ones 614 us a step, together 520; over 120 random batches tl_segment_attn takes 0.87 of its time in two launches, 0.99
 // at most.  (Groups of eight blocks of each kind in turn: a unit takes a whole round whatever runs beside it, so the
 // units' second round ends late, a tenth slower.)  The branch is in the kernel itself, not around a function that both
-// kernels call: passed to such a function, the block's number cost the one-pass kernel two spilled registers.
+// kernels call.  IN_TURN: fewer workgroups than units, each takes several (a kernel of its own: units with a workgroup
+// each fetch their tokens 0.2 us faster without, splitk_unit).
 //
 // READ: how memory is read.  Bit 0: scalar LDS reads of V in place of transposing ones.  Bit 1 (kOffGrid): some tensor does not
 // start on a 16-byte boundary, which direct loads to LDS ask for; what they bring goes through registers instead, to the
 // same places in the same order, so that the results are the same bits.  (A variant of its own: aligned tensors pay nothing.)
 constexpr int kScalarV = 1, kOffGrid = 2;
-template <int MODE, int READ, bool JOINT = false>
+template <int MODE, int READ, bool JOINT = false, bool IN_TURN = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void row_tile_attn_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   if (JOINT && blockIdx.x < unit_blocks(a)) {
     const int n = a.n_units * unit_head_blocks(a.kv_heads, a.unit_heads_log2), lanes = a.unit_lanes, lane_no = blockIdx.x;
     if (lane_no >= lanes) return;
-    for (int first = 0; first < n; first += lanes) {          // forth and back, as the units come longest first
-      const int i = (first / lanes) & 1 ? first + lanes - 1 - lane_no : first + lane_no;
-      if (first > 0) __syncthreads();                           // the LDS is free again
-      if (i < n) unit::splitk_unit<READ & kScalarV, true>(a, a.units[i % a.n_units], i / a.n_units, lds);
+    if constexpr (!IN_TURN) {
+      unit::splitk_unit<READ & kScalarV, false>(a, a.units[lane_no % a.n_units], lane_no / a.n_units, lds);
+    } else {
+      for (int first = 0; first < n; first += lanes) {          // forth and back, as the units come longest first
+        const int i = (first / lanes) & 1 ? first + lanes - 1 - lane_no : first + lane_no;
+        if (first > 0) __syncthreads();                           // the LDS is free again
+        if (i < n) unit::splitk_unit<READ & kScalarV, true>(a, a.units[i % a.n_units], i / a.n_units, lds);
+      }
     }
     return;
   }
@@ -967,11 +972,14 @@ tl_status launch_tiles_and_units(const AttnArgs& a, hipStream_t st) {
     TL_FAIL(TL_EINVAL, "launch_tiles_and_units: %d kv heads cannot be dealt %d to a workgroup", a.kv_heads, 1 << a.unit_heads_log2);
   if (a.off_grid) TL_FAIL(TL_EINVAL, "launch_tiles_and_units: tensors off the 16-byte grid go in two launches");
   const dim3 grid(unit_blocks(a) + (unsigned)a.n_work * a.kv_heads), block(kThreads);
-  static std::atomic<uint64_t> allowed[2];
-  const bool scalar_v = get_option_vread() != 0;
-  auto kern = scalar_v ? row_tile_attn_kernel<0, 1, true> : row_tile_attn_kernel<0, 0, true>;
+  static std::atomic<uint64_t> allowed[4];
+  const bool scalar_v = get_option_vread() != 0, in_turn = a.unit_lanes < a.n_units * unit_head_blocks(a.kv_heads, a.unit_heads_log2);
+  constexpr decltype(&row_tile_attn_kernel<0, 0, true>) kernels[4] = {row_tile_attn_kernel<0, 0, true>, row_tile_attn_kernel<0, 1, true>,
+                                                                       row_tile_attn_kernel<0, 0, true, true>, row_tile_attn_kernel<0, 1, true, true>};
+  const int which = 2 * in_turn + scalar_v;
+  auto kern = kernels[which];
   constexpr size_t lds_bytes = kLdsBytes > unit::kLdsBytes ? kLdsBytes : unit::kLdsBytes;
-  const tl_status rc = allow_lds((const void*)kern, lds_bytes, allowed[scalar_v]);
+  const tl_status rc = allow_lds((const void*)kern, lds_bytes, allowed[which]);
   if (rc != TL_OK) return rc;
   hipLaunchKernelGGL(kern, grid, block, lds_bytes, st, a);
   TL_HIP(hipGetLastError());
