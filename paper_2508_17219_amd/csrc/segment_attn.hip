@@ -161,6 +161,13 @@ constexpr int kScalarV = 1, kOffGrid = 2;
 template <int MODE, int READ, bool JOINT = false, bool IN_TURN = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kRG, 2 / kRG))) void row_tile_attn_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  // Arguments for the parts behind the loops, and for each of several units, are read from the kernel's argument block where
+  // they are needed: held in scalar registers from the start they push others of the loop's out.  (The empty asm keeps the loads in their place.)
+  auto late_args = []() __attribute__((always_inline)) {
+    auto p = (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+  };
   if (JOINT && blockIdx.x < unit_blocks(a)) {
     const int n = a.n_units * unit_head_blocks(a.kv_heads, a.unit_heads_log2), lanes = a.unit_lanes, lane_no = blockIdx.x;
     if (lane_no >= lanes) return;
@@ -170,7 +177,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
       for (int first = 0; first < n; first += lanes) {          // forth and back, as the units come longest first
         const int i = (first / lanes) & 1 ? first + lanes - 1 - lane_no : first + lane_no;
         if (first > 0) __syncthreads();                           // the LDS is free again
-        if (i < n) unit::splitk_unit<READ & kScalarV, true>(a, a.units[i % a.n_units], i / a.n_units, lds);
+        if (i >= n) return;
+        const auto args = late_args();
+        const auto* w = unit::scalar_loads((const int32_t*)(args->units + i % args->n_units));     // (a vector load would wait for the last unit's stores)
+        unit::splitk_unit<READ & kScalarV, true>(*args, Work{w[0], w[1], w[2], w[3], w[4]}, i / args->n_units, lds);
       }
     }
     return;
@@ -201,13 +211,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int G = a.group;
   constexpr bool kHasPool = MODE != 1, kHasSelf = MODE != 0;
-  // Arguments for the parts behind the loops are read from the kernel's argument block where they are needed: held in scalar
-  // registers from the start they push others of the loop's out.  (The empty asm keeps the loads in their place.)
-  auto late_args = []() __attribute__((always_inline)) {
-    auto p = (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return p;
-  };
   const int first_token = wk.tok_off;          // causal work: tokens of a tile are consecutive, and the token array starts with
                                                // every token in order (one dependent load less before the queries)
   // K/V of the new tokens: the launch's main K/V for the causal block alone, the second pair when fused
@@ -459,7 +462,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2 / kR
   };
   // Tiles that are masked or walked carefully, by number t in a phase's list: the kv row at the tile's first place, the
   // places [lo, hi) that are the tile's, log2 of the multiplicity.  Pool: the full tiles, then those cut short by a
-  // fill; new tokens: in order.
+  // fill; new tokens: in order.  (The lists' places are held in scalar registers, for which the one-pass kernel puts three others
+  // aside once on the way to its masked pool tiles; read from the argument block tile by tile, nothing is put aside and the tiny
+  // configuration takes 14.4 us, 13.2 so.)
   struct Tile {
     int base, lo, hi;
     float lm;

@@ -49,8 +49,8 @@ inline bool can_deal(const AttnArgs& a) {
 }
 
 // IN_TURN: the workgroup takes several units, one after the other.
-template <int VREAD, bool IN_TURN>
-__device__ __forceinline__ void splitk_unit(const AttnArgs& a, const Work wk, const int head_block, uint16_t* lds) {
+template <int VREAD, bool IN_TURN, typename Args>
+__device__ __forceinline__ void splitk_unit(const Args& a, const Work wk, const int head_block, uint16_t* lds) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, l16 = lane & 15, c4 = lane >> 4;
   const int heads = 1 << a.unit_heads_log2, slices = kWaves >> a.unit_heads_log2;

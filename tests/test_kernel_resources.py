@@ -22,10 +22,11 @@ def _device_compile(source, out, *flags):
 @pytest.mark.parametrize("source,n_kernels", [("segment_attn.hip", 5), ("decode_attn.hip", 1)])
 def test_default_attention_kernels_spill_no_register(source, n_kernels):
     text = _device_compile(source, os.devnull, "-c", "-Rpass-analysis=kernel-resource-usage")
-    spills = re.findall(r"Function Name: (\S+).*?VGPRs Spill: (\d+)", text, re.S)
-    default = {name: int(n) for name, n in spills if re.search(r"row_tile_attn_kernelILi\dELi0E|splitk_unit_attn_kernelILi0E", name)}
+    spills = re.findall(r"Function Name: (\S+).*?SGPRs Spill: (\d+).*?VGPRs Spill: (\d+)", text, re.S)
+    default = {name: (int(scalar), int(vector)) for name, scalar, vector in spills if re.search(r"row_tile_attn_kernelILi\dELi0E|splitk_unit_attn_kernelILi0E", name)}
     assert len(default) == n_kernels, spills
-    assert not any(default.values()), default
+    for name, (scalar, vector) in default.items():       # (the one-pass kernel puts three scalars aside once, outside its loops)
+        assert vector == 0 and scalar <= (3 if "ILi2E" in name else 0), default
 
 
 def test_units_beside_row_tiles_walk_their_lists_through_scalar_loads(tmp_path):
