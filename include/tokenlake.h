@@ -257,6 +257,8 @@ typedef struct tl_plan_info {
                               (the rest belongs to tl_fused_attn's one-pass rows and tails)   */
   int32_t n_prior_rows;    /* partial rows of work items that tl_fused_attn merges in itself
                               (TL_PLAN_FUSE_TAILS), counted per (request, work item)           */
+  int32_t n_unit_workgroups; /* workgroups that take the split-K units; in a launch with row tiles each may
+                              take several in turn                                            */
 } tl_plan_info;
 
 /* req_row_ptr: host [n_req+1], offsets of each request's new tokens in the batch's Q

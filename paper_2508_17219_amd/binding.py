@@ -33,7 +33,7 @@ class tl_plan_info(C.Structure):
         "n_tiles", "n_units", "n_causal_tiles", "n_list_entries", "n_merge_entries")] + [
         (n, C.c_int64) for n in ("prefix_pairs", "self_pairs", "unique_kv_tokens")] + [
         (n, C.c_int32) for n in ("n_fused_tiles", "n_fused_tokens", "n_single_tokens")] + [
-        ("tile_pairs", C.c_int64), ("item_pairs", C.c_int64), ("n_prior_rows", C.c_int32)]
+        ("tile_pairs", C.c_int64), ("item_pairs", C.c_int64), ("n_prior_rows", C.c_int32), ("n_unit_workgroups", C.c_int32)]
 
 
 _lib = None

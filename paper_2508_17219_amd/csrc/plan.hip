@@ -8,6 +8,7 @@
 // query rows are all new tokens of those requests.  Items with few rows per kv head are cut into
 // split-K chunks.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <functional>
 #include <new>
@@ -87,24 +88,101 @@ double joint_tiles(double units, int64_t unit_blocks, double tiles, int64_t n_cu
   return units + tiles - std::min(shorter, std::min(idle, 0.5 * tiles) + 0.25 * shorter);
 }
 
+// When a launch of split-K units and row tiles ends (us) whose units are taken by `lanes` workgroups in turn: a walk from end
+// to end of a workgroup over the launch, as it is dealt.  An XCD takes every eighth workgroup, in order, as its CUs fall free;
+// walked are the first, which stands for those with a unit workgroup more, and the last (all eight: 45 of the batches below
+// more than 1.02 for 54, and a plan of 196 units and 656 row tiles takes 330 us for 223).  A unit's workgroup streams
+// kUnitRate at most, all of them share what row tiles leave of HBM; a row tile's takes its KV tiles from HBM, with the others
+// of its list from L2, and is slower the more of HBM is asked for and the more of the chip multiplies (power).  Fitted to
+// tl_segment_attn of 12774 random batches of 1 to 8 prefill chunks beside 4 to 200 decoded tokens, each timed with all units
+// at once and with two in turn: the ratio of the two ends is off by 6.5 % in the root mean square.
+constexpr int64_t kXcds = 8;
+constexpr double kHbmRate = 5.9e6, kUnitRate = 47e3, kRowTileRate = 42e3;      // bytes per us: of HBM, of a unit's workgroup, of a row tile's by itself
+constexpr double kUnitStart = 4.0;                                              // us: a unit's start and end
+constexpr double kRowTileUs = 1.1, kRowTileHbmUs = 0.5, kRowTilePowerUs = 0.4;  // us of a KV tile, and what HBM load and a full chip add
+double joint_end(const std::vector<double>& unit_bytes, int64_t head_blocks, int64_t lanes, const std::vector<Work>& tiles,
+                 const std::vector<double>& tile_rate, int32_t kv_heads, int64_t n_cu) {
+  struct End {
+    double at, rate;       // in bytes that each unit's, in KV tiles that each row tile's workgroup has seen go by since the start
+    int xcd;
+    bool operator<(const End& o) const { return at > o.at; }
+  };
+  const int64_t n_units = (int64_t)unit_bytes.size(), n = n_units * head_blocks, row0 = (lanes + kXcds - 1) / kXcds * kXcds;
+  const int64_t total = row0 + (int64_t)tiles.size() * kv_heads, cus = std::max<int64_t>(1, n_cu / kXcds);
+  const double hbm = kHbmRate * (double)(cus * kXcds) / kComputeUnits;
+  std::priority_queue<End> units, rows;
+  const int64_t more = lanes % kXcds ? lanes % kXcds : kXcds / 2;
+  const double weight[2] = {(double)more, (double)(kXcds - more)};
+  double t = 0, bytes = 0, kv = 0, row_rate = 0, n_at_units = 0, n_at_rows = 0;
+  int64_t next[2] = {0, kXcds - 1}, idle[2] = {cus, cus};
+  auto deal = [&](int x) {
+    for (; idle[x] > 0 && next[x] < total; next[x] += kXcds) {
+      const int64_t wg = next[x];
+      if (wg >= lanes && wg < row0) continue;
+      --idle[x];
+      if (wg < lanes) {
+        double chain = 0;
+        for (int64_t first = 0; first < n; first += lanes) {
+          const int64_t i = (first / lanes) & 1 ? first + lanes - 1 - wg : first + wg;
+          if (i < n) chain += unit_bytes[i % n_units] + kUnitStart * kUnitRate;
+        }
+        units.push(End{bytes + chain, 0, x});
+        n_at_units += weight[x];
+      } else {
+        const int64_t tile = (wg - row0) / kv_heads;
+        rows.push(End{kv + (double)(tiles[tile].n_full + tiles[tile].n_part + kTileStart), tile_rate[tile], x});
+        row_rate += weight[x] * tile_rate[tile];
+        n_at_rows += weight[x];
+      }
+    }
+  };
+  deal(0);
+  deal(1);
+  while (!units.empty() || !rows.empty()) {
+    const double left = std::max(hbm - row_rate, 0.2 * hbm), asked = kUnitRate * n_at_units, busy = n_at_rows / (double)(cus * kXcds);
+    const double per_unit = asked > left ? kUnitRate * left / asked : kUnitRate;
+    const double per_row = 1 / (kRowTileUs + kRowTileHbmUs * std::min(1.0, asked / left) + kRowTilePowerUs * busy * busy * busy);
+    const double unit_end = units.empty() ? HUGE_VAL : (units.top().at - bytes) / per_unit, row_end = rows.empty() ? HUGE_VAL : (rows.top().at - kv) / per_row;
+    const double dt = std::min(unit_end, row_end);
+    t += dt;
+    bytes = unit_end <= row_end ? units.top().at : bytes + dt * per_unit;
+    kv = row_end <= unit_end ? rows.top().at : kv + dt * per_row;
+    for (; !units.empty() && units.top().at <= bytes; units.pop()) {
+      ++idle[units.top().xcd];
+      n_at_units -= weight[units.top().xcd];
+    }
+    for (; !rows.empty() && rows.top().at <= kv; rows.pop()) {
+      ++idle[rows.top().xcd];
+      n_at_rows -= weight[rows.top().xcd];
+      row_rate -= weight[rows.top().xcd] * rows.top().rate;
+    }
+    deal(0);
+    deal(1);
+  }
+  return t;
+}
+
 // Workgroups that take the split-K units beside row tiles.  All units at once keep HBM busy and leave row tiles the few CUs that are
-// over; with half as many workgroups that take two units each in turn, row tiles and units run side by side for longer.  That pays
-// where the two take about as long, units by their bytes and row tiles by their KV tiles, and row tiles share the CUs beside the
-// units evenly: tl_segment_attn of 878 random batches of 1 to 8 chunks beside 4 to 91 decoded tokens, row tiles of 0.95 to 3.5 of
-// the units' time, half a round to one and a half of unit workgroups, against all units at once:
-//   row tiles in 1.1 to 2.25 rounds of the other CUs: 0.97 (0.80 to 1.14), every fourth more than 1.02, as the second round then
-//     starts where all units at once would be over; otherwise 0.94;
-//   fewer than five eighths of a round of unit workgroups (half of the CUs are free without) 0.99, more than 5/4 rounds 0.98;
-//   in what is left, 511 batches, 0.93 (0.75 to 1.14), 17 of them more than 1.02 and 4 more than 1.05 (mixed batch of perf/cases.py 451 -> 441 us).
-// Units longer than the row tiles want the CUs (20 row tiles beside 116 decoded tokens 1.42, twelve batches of 0.5 to 0.95 0.67
-// to 1.28); row tiles longer than 3.5 make no difference (0.95 to 1.08).  Three in turn: 1.01 in the mean.
-constexpr double kUnitBytesPerUs = 6.0e6, kRowTileUs = 1.5;
-int64_t plan_unit_lanes(int64_t unit_blocks, double unit_bytes, int64_t row_blocks, double row_us, int64_t n_cu) {
-  const double units = unit_bytes / kUnitBytesPerUs, rows = n_cu > 0 ? row_us / (double)n_cu : 0;
-  const int64_t lanes = (unit_blocks + 1) / 2;
-  if (8 * unit_blocks < 5 * n_cu || 4 * unit_blocks > 5 * n_cu || rows < 0.95 * units || rows > 3.5 * units) return unit_blocks;
-  const double rounds = (double)row_blocks / (double)(n_cu - lanes);
-  return rounds <= 1.1 || rounds > 2.25 ? lanes : unit_blocks;
+// over; with half as many workgroups that take two units each in turn, row tiles and units may run side by side for longer,
+// or the units may be what ends last: whichever the walk says ends earlier, two in turn by a margin of 3 % and 3 us.  Of the 12774
+// batches 3030 are taken in turn: 0.88 of the time of all at once in the mean, 54 of them more than 1.02 and 12 more than 1.05;
+// of 14546 others, which nothing was fitted to, 2515: 0.90, 39 and 8, 1.12 at most.  Over the 12774 0.971 of all at once, and
+// the better of the two each time would be 0.959.  (Lines on the ratio of units to row tiles and on rounds of either take 1678,
+// 71 of them more than 1.02 and 38 more than 1.05, up to 1.29: over all 0.988.  The walk passes by 440 that gained 2 % or more there.)
+// Not where several workgroups share a unit with eight heads each (16 kv heads): at once they read the parts of a token's row
+// together, in turn one after the other (180 batches where the walk says 0.92 or less 0.99, 35 of them more than 1.02).
+// Three in turn: 1.01 in the mean.
+int64_t plan_unit_lanes(const std::vector<double>& unit_bytes, int32_t heads_log2, const std::vector<Work>& tiles, int32_t kv_heads, int64_t n_cu) {
+  const int64_t head_blocks = unit_head_blocks(kv_heads, heads_log2), all = (int64_t)unit_bytes.size() * head_blocks, half = (all + 1) / 2;
+  // (row tiles in more than 16 rounds of the CUs leave no gaps that a walk would find)
+  if (unit_bytes.empty() || tiles.empty() || n_cu <= 0 || (head_blocks > 1 && heads_log2 == 3) || (int64_t)tiles.size() * kv_heads > 16 * n_cu) return all;
+  std::vector<double> tile_rate(tiles.size());
+  for (size_t first = 0, end; first < tiles.size(); first = end) {       // the row tiles of an item, up to eight of them at a time
+    for (end = first; end < tiles.size() && tiles[end].kv_off == tiles[first].kv_off;) ++end;
+    for (size_t i = first; i < end; ++i) tile_rate[i] = kRowTileRate / (double)std::min<size_t>(end - first, 8);
+  }
+  const double at_once = joint_end(unit_bytes, head_blocks, all, tiles, tile_rate, kv_heads, n_cu);
+  return joint_end(unit_bytes, head_blocks, half, tiles, tile_rate, kv_heads, n_cu) < 0.97 * at_once - 3 ? half : all;
 }
 
 struct RowWork {
@@ -779,13 +857,6 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       unit_load.longest = std::max(unit_load.longest, tokens);
     }
     p->unit_heads_log2 = plan_unit_heads_log2(pool->kv_heads, unit_load, n_cu > 0 ? n_cu : kComputeUnits);
-    {
-      double row_us = 0;
-      for (const Work& w : p->tiles) row_us += kRowTileUs * (double)((w.n_full + w.n_part + kTileStart) * pool->kv_heads);
-      p->unit_lanes = (int32_t)plan_unit_lanes(unit_load.units * unit_head_blocks(pool->kv_heads, p->unit_heads_log2),
-                                               (double)unit_load.tokens * pool->kv_heads * (4 * kHeadDim),
-                                               (int64_t)p->tiles.size() * pool->kv_heads, row_us, n_cu);
-    }
     p->tok.resize(own_toks);
     std::iota(p->tok.begin(), p->tok.end(), 0);
     p->tok.insert(p->tok.end(), p->item_tokens.begin(), p->item_tokens.end());
@@ -859,6 +930,17 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       for (const auto& s : spans)
         for (int32_t i = s.second - 1; i >= s.first; --i) sorted.push_back(p->ftiles[i]);
       p->ftiles.swap(sorted);
+    }
+
+    {
+      std::vector<double> unit_bytes;      // of a workgroup: the kv heads that it takes of its unit's tokens
+      unit_bytes.reserve(p->units.size());
+      for (const Work& w : p->units) {
+        int64_t tokens = 0;
+        for (int32_t i = w.kv_off; i < w.kv_off + w.kv_len; ++i) tokens += p->unit_slots[2 * (size_t)i + 1];
+        unit_bytes.push_back((double)tokens * std::min(1 << p->unit_heads_log2, pool->kv_heads) * (4 * kHeadDim));
+      }
+      p->unit_lanes = (int32_t)plan_unit_lanes(unit_bytes, p->unit_heads_log2, p->tiles, pool->kv_heads, n_cu);
     }
 
     // Row tiles as two workgroups of half the rows each where that stays one round of the CUs: the four waves of a half have a
@@ -957,6 +1039,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     inf.tile_pairs = tile_pairs;
     inf.item_pairs = item_pairs;
     inf.n_prior_rows = (int32_t)p->prior_rows.size();
+    inf.n_unit_workgroups = p->unit_lanes;
 
     // ---- one block with everything the kernels read ---------------------------------------------
     {

@@ -339,6 +339,31 @@ def test_a_launch_that_leaves_cus_idle_is_cut_into_short_pieces(n_req, new, lo, 
     B.tl_pool_destroy(plan_pool[0])
 
 
+@pytest.mark.parametrize("hq,hkv,n_decode,segs,chunks,chunk,chunk_segs,cus,workgroups", [
+    (32, 8, 115, 8, 2, 256, 32, 256, 115),     # 230 workgroups of four heads: units of 512 tokens hold up 64 long row tiles (82 us, in turn 49)
+    (8, 1, 254, 32, 2, 900, 32, 256, 127),     # a whole round of 2048 tokens of one head (85 us, in turn 52)
+    (32, 8, 196, 24, 10, 500, 64, 256, 98),    # both as long as each other (538 us, in turn 448)
+    (16, 4, 188, 3, 3, 256, 4, 256, 188),      # short lists: the second unit of a workgroup ends last (16.8 us, in turn 22.7)
+    (16, 16, 104, 4, 5, 1700, 8, 256, 208),    # two workgroups read a token's row together (88 us, in turn 92)
+    (32, 8, 115, 8, 2, 256, 32, 0, 230),       # no number of CUs
+    (32, 8, 230, 8, 0, 0, 0, 256, 230),        # units alone
+])
+def test_units_are_taken_in_turn_where_the_launch_ends_earlier(hq, hkv, n_decode, segs, chunks, chunk, chunk_segs, cus, workgroups):
+    """Decoded tokens of one unit each beside prefill chunks: how many workgroups take the units.  The times are
+    tl_segment_attn's of the batch, with all units at once and with two to a workgroup."""
+    pool = B.tl_pool_create(16384, 64, hkv, 128, FAKE_K, FAKE_V)
+    lens = [segs] * n_decode + [chunk_segs] * chunks
+    ids = np.arange(sum(lens), dtype=np.uint64)
+    B.tl_pool_adopt(pool, ids, np.arange(len(ids)), np.full(len(ids), 64))
+    plan = B.tl_plan_create(pool, hq, np.concatenate([[0], np.cumsum([1] * n_decode + [chunk] * chunks)]), np.concatenate([[0], np.cumsum(lens)]), ids,
+                            B.TL_PLAN_SELF_BLOCK, 32, cus)
+    info = B.tl_plan_get_info(plan)
+    assert info.n_units == n_decode and (info.n_tiles > 0) == (chunks > 0)
+    assert info.n_unit_workgroups == workgroups
+    B.tl_plan_destroy(plan)
+    B.tl_pool_destroy(pool)
+
+
 @pytest.mark.parametrize("heads", [(32, 8, 5), (8, 1, 16)])
 def test_uneven_chunks_beside_decode_leave_the_one_pass_kernel(heads):
     """Prefill chunks on prefixes of very different lengths beside decoded tokens: the longest list would
