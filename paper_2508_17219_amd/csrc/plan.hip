@@ -224,6 +224,7 @@ struct Walk {
 struct RowItem {       // a work item of row tiles
   Walk walk;
   int64_t row_tiles, halves;      // workgroups per kv head and piece, whole and where each takes half the rows
+  int64_t rows;                   // per kv head
 };
 
 // How the lists of a launch's row-tile items are cut along the KV: into `chunks` pieces of min_slots or more, or
@@ -267,31 +268,51 @@ int64_t cut_workgroups(const std::vector<RowItem>& items, const RowCut& cut, int
   return wgs;
 }
 
+// Row tiles as two workgroups of half the rows each where that stays one round of the CUs: the four waves of a half have a
+// SIMD each, and a tile takes 0.76 us instead of 1.12.  (3 chunks of 256 tokens with 8 kv heads, 96 workgroups: pool
+// launch 15.5 -> 13.4 us, causal launch 13.4 -> 11.4; one of 322 to 645 as one-pass rows 25.8 -> 20.9.)  A second half
+// without rows ends at once but holds a CU until then: where they do not all fit beside the others an eighth of the round is left for
+// them (17 row tiles of 8 kv heads of which 15 have two halves, 256 of 272 workgroups: 41.6 us whole, 47.7 halved), and
+// no more than two in five of the row tiles have two halves (18 of 8 kv heads, every other one narrow, 216 of 288 workgroups:
+// some second halves wait for a whole chain, 63.7 us; up to 1.4 workgroups a row tile nothing waits, from 1.5 on 4 us in the mean).
+// `wgs`: with two for a tile of more than half its rows.
+bool halves_fit(int64_t row_tiles, int64_t wgs, int32_t kv_heads, int64_t n_cu) {
+  return wgs > row_tiles && (2 * row_tiles * kv_heads <= n_cu || (8 * wgs * kv_heads <= 7 * n_cu && 5 * wgs <= 7 * row_tiles));
+}
+
+// What the three steps of a launch of one round take (us), but for what is the same however its lists are cut: the longest
+// chain of tiles, workgroups that start, partials written and read.  Fitted to 4508 random batches, each timed in five
+// cuts: differences between the cuts of a batch are off by 1.9 us in the root mean square.
+double one_round_us(const std::vector<RowItem>& items, const RowCut& cut, int64_t n_cu, int32_t kv_heads, bool wide) {
+  int64_t row_tiles = 0, wgs = 0, rows = 0, chain = 0;
+  for (const RowItem& it : items) {
+    if (it.walk.slots == 0) continue;
+    const int64_t step = std::min(cut.step(it.walk), it.walk.slots), n = (it.walk.slots + step - 1) / step;
+    row_tiles += n * it.row_tiles;
+    wgs += n * it.halves;
+    rows += n * it.rows;
+    chain = std::max(chain, (it.walk.kv_tiles * step + it.walk.slots - 1) / it.walk.slots);
+  }
+  const double tile = wide && !halves_fit(row_tiles, wgs, kv_heads, n_cu) ? 1.0 : 0.68;
+  return tile * (double)chain + 7.4 * (double)(row_tiles * kv_heads) / (double)n_cu + 0.2e-6 * (double)(rows * kv_heads) * (4 * kHeadDim);
+}
+
 // A launch that leaves CUs idle where its lists are cut into pieces of 2048 tokens (half of the CUs, or where row tiles have half
 // their rows or less, which are bound by their chain of tiles alone, any) waits for the longest chain of
-// tiles: pieces as short as they may be (512 tokens) without becoming more than one round of the CUs, of whole row tiles or
-// of halves, which take kHalfTile of the time a tile.
-// Measured, three steps, with pieces of 2048 tokens and whole row tiles against this: 6 chunks of 16 to 32 tokens on 4k to 17k
-// of one kv head 57 -> 33 us, 39 of 3 to 7 on 3k to 11k 57 -> 36, one of 120 to 240 on 1.2k to 5k of two 59 -> 33.
-constexpr double kHalfTile = 0.68;
+// tiles: pieces down to 512 tokens, no more than one round of whole row tiles, as one_round_us has it.
+// Of 3118 other batches, three steps, against pieces of 2048 tokens: 0.80 of the time in the mean, 72 more than 1.02 (the shortest
+// pieces that are one round, partials not counted: 0.81, 179 of them).
 RowCut one_round_cut(const std::vector<RowItem>& items, int64_t n_cu, int32_t kv_heads, const RowCut& otherwise) {
-  int64_t longest_list = 0;
   bool wide = false;
-  for (const RowItem& it : items) {
-    longest_list = std::max(longest_list, it.walk.kv_tiles);
-    wide = wide || it.halves > it.row_tiles;
-  }
+  for (const RowItem& it : items) wide = wide || it.halves > it.row_tiles;
   RowCut best = otherwise;
-  double best_cost = 0;
-  for (const bool halves : {false, true}) {
-    if (halves && !wide) continue;
-    RowCut c;
-    c.longest = kShortPieceTiles;
-    while (c.longest < kMinPieceTiles && cut_workgroups(items, c, kv_heads, halves) > n_cu) c.longest += kShortPieceTiles / 4;
-    if (c.longest >= kMinPieceTiles) continue;
-    const double cost = (halves ? kHalfTile : 1.0) * (double)(std::min(longest_list, c.longest) + kTileStart);
-    if (best_cost == 0 || cost < best_cost) {
-      best_cost = cost;
+  double best_us = one_round_us(items, otherwise, n_cu, kv_heads, wide);
+  RowCut c;
+  for (c.longest = kShortPieceTiles; c.longest < kMinPieceTiles; c.longest += kShortPieceTiles / 4) {
+    if (cut_workgroups(items, c, kv_heads, false) > n_cu) continue;
+    const double us = one_round_us(items, c, n_cu, kv_heads, wide);
+    if (us < best_us) {
+      best_us = us;
       best = c;
     }
   }
@@ -437,7 +458,7 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
     const int tok_tile = kRowTile / G, half_tile = half_row_tile(G);
     auto row_item = [&](const Walk& w, int64_t n_tok) {
       const int64_t whole = n_tok / tok_tile, rest = n_tok % tok_tile;
-      return RowItem{w, whole + (rest > 0), whole * (tok_tile > half_tile ? 2 : 1) + (rest > half_tile ? 2 : rest > 0)};
+      return RowItem{w, whole + (rest > 0), whole * (tok_tile > half_tile ? 2 : 1) + (rest > half_tile ? 2 : rest > 0), n_tok * G};
     };
     const int64_t n_cu = compute_units < 0 ? kComputeUnits : compute_units;
     const int32_t min_chunk_slots = std::max(1, kMinPieceTiles * kKvTile / pool->seg_len);
@@ -943,16 +964,10 @@ tl_status tl_plan_create(tl_plan** out, const tl_pool* pool, int32_t q_heads, in
       p->unit_lanes = (int32_t)plan_unit_lanes(unit_bytes, p->unit_heads_log2, p->tiles, pool->kv_heads, n_cu);
     }
 
-    // Row tiles as two workgroups of half the rows each where that stays one round of the CUs: the four waves of a half have a
-    // SIMD each, and a tile takes 0.76 us instead of 1.12.  (3 chunks of 256 tokens with 8 kv heads, 96 workgroups: pool
-    // launch 15.5 -> 13.4 us, causal launch 13.4 -> 11.4; one of 322 to 645 as one-pass rows 25.8 -> 20.9.)  A second half
-    // without rows ends at once but holds a CU until then: an eighth of the round is left for them (17 row tiles of 8 kv heads of
-    // which 15 have two halves, 256 of 272 workgroups: 41.6 us whole, 47.7 halved).
     auto halve = [&](const std::vector<Work>& tiles) {
-      const int64_t n = (int64_t)tiles.size();
-      int64_t wgs = n;
+      int64_t wgs = (int64_t)tiles.size();
       for (const Work& w : tiles) wgs += w.n_tok > half_tile;
-      return wgs > n && (2 * n * pool->kv_heads <= n_cu || 8 * wgs * pool->kv_heads <= 7 * n_cu);
+      return halves_fit((int64_t)tiles.size(), wgs, pool->kv_heads, n_cu);
     };
     p->halve_tiles = halve(p->tiles) && p->units.empty();
     p->halve_ctiles = halve(p->ctiles);

@@ -339,6 +339,23 @@ def test_a_launch_that_leaves_cus_idle_is_cut_into_short_pieces(n_req, new, lo, 
     B.tl_pool_destroy(plan_pool[0])
 
 
+@pytest.mark.parametrize("new_tokens,pieces", [
+    ([64, 64, 20, 20], 4),     # 16 row tiles are halved and 20 would not be, as only two of four lists have rows for two halves
+    ([20], 8),                 # narrow: 512 tokens a piece
+    ([500], 2),                # 16 row tiles halved: four pieces of whole ones write and read twice the partials
+])
+def test_short_pieces_are_weighed_as_they_are_launched(new_tokens, pieces):
+    """Lists of 64 KV tiles: how many pieces, with partials counted, row tiles halved where the launch halves them."""
+    n = len(new_tokens)
+    pool = B.tl_pool_create(64 * n, 64, 8, 128, FAKE_K, FAKE_V)
+    ids = np.arange(64 * n, dtype=np.uint64)
+    B.tl_pool_adopt(pool, ids, np.arange(64 * n), np.full(64 * n, 64))
+    plan = B.tl_plan_create(pool, 32, np.concatenate([[0], np.cumsum(new_tokens)]), 64 * np.arange(n + 1), ids)
+    assert B.tl_plan_get_info(plan).n_items == pieces * n
+    B.tl_plan_destroy(plan)
+    B.tl_pool_destroy(pool)
+
+
 @pytest.mark.parametrize("hq,hkv,n_decode,segs,chunks,chunk,chunk_segs,cus,workgroups", [
     (32, 8, 115, 8, 2, 256, 32, 256, 115),     # 230 workgroups of four heads: units of 512 tokens hold up 64 long row tiles (82 us, in turn 49)
     (8, 1, 254, 32, 2, 900, 32, 256, 127),     # a whole round of 2048 tokens of one head (85 us, in turn 52)
