@@ -4,6 +4,7 @@
 // (tl_segment_attn, tl_causal_block, tl_fused_attn, tl_merge).
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "attn_common.h"
 
@@ -93,7 +94,6 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict_
 // accumulates with the same weights w_j = exp(LSE_j - M) as the kernel above, and slice 0 adds
 // the slices up in a fixed order.
 constexpr int kMergeSlices = 8;
-constexpr int kMergeHeld = 8;
 constexpr int64_t kMidMergePairs = 8192;    // (token, head) pairs beyond which lists of 8 to 15 partials are worth a launch
 template <bool OUT_BF16>
 __global__ __launch_bounds__(32 * kMergeSlices) void lse_merge_sliced_kernel(
@@ -106,69 +106,76 @@ __global__ __launch_bounds__(32 * kMergeSlices) void lse_merge_sliced_kernel(
   const int t = mtok[blockIdx.x], hd = blockIdx.y;
   const int b = mptr[t], e = mptr[t + 1];
   const int sl = threadIdx.x >> 5, c4 = threadIdx.x & 31;
-  // A slice's first kMergeHeld partials are fetched at once, rows and LSEs, and stay in registers until the maximum is known: lists
-  // of up to 64 partials are read in one go.  (Bound by the chain of loads in front of it, and by HBM with many tokens: a walk for
-  // the maximum and another for the sum, each behind its row numbers, took one decoded token with 33 partials of 64 heads 22.7 us
-  // a step, now 21.4; 8 tokens with 25 each 336 and 332; 256 tokens' merge 11.1 and 10.4.)
-  float held_l[kMergeHeld];
-  float4 held_v[kMergeHeld];
-  float m = -INFINITY;
-  int32_t held_row[kMergeHeld];        // (places behind the list's end take its last entry: a branch would put the loads in a chain)
-#pragma unroll
-  for (int u = 0; u < kMergeHeld; ++u) held_row[u] = mrows[min(b + sl + u * kMergeSlices, e - 1)];
-#pragma unroll
-  for (int u = 0; u < kMergeHeld; ++u) {
-    const size_t row = (size_t)held_row[u] * q_heads + hd;
-    held_l[u] = lse[row];
-    held_v[u] = ((const float4*)part)[row * 32 + c4];
-  }
-#pragma unroll
-  for (int u = 0; u < kMergeHeld; ++u) m = fmaxf(m, held_l[u]);
-  // (both walks of the rest take four entries at a time so that their loads are in flight together)
-  constexpr int kStep = 4 * kMergeSlices;
-  int j0 = b + sl + kMergeHeld * kMergeSlices;
-  for (; j0 + 3 * kMergeSlices < e; j0 += kStep) {
-    const float l0 = lse[(size_t)mrows[j0] * q_heads + hd], l1 = lse[(size_t)mrows[j0 + kMergeSlices] * q_heads + hd];
-    const float l2 = lse[(size_t)mrows[j0 + 2 * kMergeSlices] * q_heads + hd], l3 = lse[(size_t)mrows[j0 + 3 * kMergeSlices] * q_heads + hd];
-    m = fmaxf(fmaxf(m, fmaxf(l0, l1)), fmaxf(l2, l3));
-  }
-  for (; j0 < e; j0 += kMergeSlices) m = fmaxf(m, lse[(size_t)mrows[j0] * q_heads + hd]);
-  if (c4 == 0) sh_m[sl] = m;
-  __syncthreads();
-  float M = sh_m[0];
-#pragma unroll
-  for (int i = 1; i < kMergeSlices; ++i) M = fmaxf(M, sh_m[i]);
+  // A slice's first partials are fetched at once, rows and LSEs, and stay in registers until the maximum is known: lists of up
+  // to 64 partials are read in one go, by two, four or eight places a slice (eight whatever the list: 64 rows are fetched
+  // for 8, 128 tokens of 64 heads with 8, 12 and 17 partials each 15.0, 15.6 and 17.8 us, now 10.3, 11.2 and 16.1).  (Bound by the chain of loads in front of it, and by HBM with many
+  // tokens: a walk for the maximum and another for the sum, each behind its row numbers, took one decoded token with 33
+  // partials of 64 heads 22.7 us a step, now 21.4; 8 tokens with 25 each 336 and 332; 256 tokens' merge 11.1 and 10.4.)
+  float M = -INFINITY, wsum = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  float wsum = 0.f;
-  if (M > -INFINITY) {
-    auto add = [&](float l, const float4& v) {
-      const float w = expf(l - M);
-      acc.x += w * v.x; acc.y += w * v.y; acc.z += w * v.z; acc.w += w * v.w;
-      wsum += w;
-    };
+  auto merge = [&](auto HELD) __attribute__((always_inline)) {
+    constexpr int kHeld = decltype(HELD)::value;
+    float held_l[kHeld];
+    float4 held_v[kHeld];
+    float m = -INFINITY;
+    int32_t held_row[kHeld];        // (places behind the list's end take its last entry: a branch would put the loads in a chain)
 #pragma unroll
-    for (int u = 0; u < kMergeHeld; ++u)
-      if (b + sl + u * kMergeSlices < e) add(held_l[u], held_v[u]);
-    int jj = b + sl + kMergeHeld * kMergeSlices;
-    for (; jj + 3 * kMergeSlices < e; jj += kStep) {
-      size_t row[4];
-      float l[4];
-      float4 v[4];
+    for (int u = 0; u < kHeld; ++u) held_row[u] = mrows[min(b + sl + u * kMergeSlices, e - 1)];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) row[u] = (size_t)mrows[jj + u * kMergeSlices] * q_heads + hd;
+    for (int u = 0; u < kHeld; ++u) {
+      const size_t row = (size_t)held_row[u] * q_heads + hd;
+      held_l[u] = lse[row];
+      held_v[u] = ((const float4*)part)[row * 32 + c4];
+    }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        l[u] = lse[row[u]];
-        v[u] = ((const float4*)part)[row[u] * 32 + c4];
+    for (int u = 0; u < kHeld; ++u) m = fmaxf(m, held_l[u]);
+    // (both walks of the rest take four entries at a time so that their loads are in flight together)
+    constexpr int kStep = 4 * kMergeSlices;
+    int j0 = b + sl + kHeld * kMergeSlices;
+    for (; j0 + 3 * kMergeSlices < e; j0 += kStep) {
+      const float l0 = lse[(size_t)mrows[j0] * q_heads + hd], l1 = lse[(size_t)mrows[j0 + kMergeSlices] * q_heads + hd];
+      const float l2 = lse[(size_t)mrows[j0 + 2 * kMergeSlices] * q_heads + hd], l3 = lse[(size_t)mrows[j0 + 3 * kMergeSlices] * q_heads + hd];
+      m = fmaxf(fmaxf(m, fmaxf(l0, l1)), fmaxf(l2, l3));
+    }
+    for (; j0 < e; j0 += kMergeSlices) m = fmaxf(m, lse[(size_t)mrows[j0] * q_heads + hd]);
+    if (c4 == 0) sh_m[sl] = m;
+    __syncthreads();
+    M = sh_m[0];
+#pragma unroll
+    for (int i = 1; i < kMergeSlices; ++i) M = fmaxf(M, sh_m[i]);
+    if (M > -INFINITY) {
+      auto add = [&](float l, const float4& v) {
+        const float w = expf(l - M);
+        acc.x += w * v.x; acc.y += w * v.y; acc.z += w * v.z; acc.w += w * v.w;
+        wsum += w;
+      };
+#pragma unroll
+      for (int u = 0; u < kHeld; ++u)
+        if (b + sl + u * kMergeSlices < e) add(held_l[u], held_v[u]);
+      int jj = b + sl + kHeld * kMergeSlices;
+      for (; jj + 3 * kMergeSlices < e; jj += kStep) {
+        size_t row[4];
+        float l[4];
+        float4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) row[u] = (size_t)mrows[jj + u * kMergeSlices] * q_heads + hd;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          l[u] = lse[row[u]];
+          v[u] = ((const float4*)part)[row[u] * 32 + c4];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) add(l[u], v[u]);       // same order as one by one
       }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) add(l[u], v[u]);       // same order as one by one
+      for (; jj < e; jj += kMergeSlices) {
+        const size_t row = (size_t)mrows[jj] * q_heads + hd;
+        add(lse[row], ((const float4*)part)[row * 32 + c4]);
+      }
     }
-    for (; jj < e; jj += kMergeSlices) {
-      const size_t row = (size_t)mrows[jj] * q_heads + hd;
-      add(lse[row], ((const float4*)part)[row * 32 + c4]);
-    }
-  }
+  };
+  if (e - b <= 2 * kMergeSlices) merge(std::integral_constant<int, 2>{});
+  else if (e - b <= 4 * kMergeSlices) merge(std::integral_constant<int, 4>{});
+  else merge(std::integral_constant<int, 8>{});
   sh_acc[sl][c4] = acc;
   if (c4 == 0) sh_w[sl] = wsum;
   __syncthreads();
@@ -427,10 +434,10 @@ tl_status tl_merge(tl_plan* plan, const float* out_partial, const float* lse, vo
   if (plan->merge_tok.empty()) return TL_OK;
   const PlanDev d = plan_dev(plan, plan->blob_dev);
   // Lists of 8 to 15 partials (a prompt's list cut into pieces) take a launch of the plain kernel: 9 partials for
-  // each of 512 tokens x 32 heads, 75 MB, 15 us there against 27 us from the slices.  A few such tokens beside long
-  // lists (a decode batch) go with those, up to 8192 (token, head) pairs: with 12 partials each beside 4 long lists,
-  // 4096 pairs 7.6 to 8.3 us in one launch, 8.9 to 9.1 in two; 8192 15.4 and 15.5; 16384 27.2 and 23.4.  Without long
-  // lists either is one launch, and the plain kernel as fast or faster (6 us up to 2048 pairs; 4096 5.9 and 7.9).
+  // each of 512 tokens x 32 heads, 75 MB, 15 us.  A few such tokens beside long lists (a decode batch) go with those, up to
+  // 8192 (token, head) pairs, where lists of 8 are even: beside 4 long lists, in one launch and in two, with 8 partials each
+  // 4096 pairs 5.5 and 7.6 us, 8192 10.2 and 10.0, 16384 18.3 and 16.0; with 12 each 6.4 and 7.8, 11.2 and 13.8, 19.8 and
+  // 21.1.  Without long lists either is one launch, and the plain kernel as fast or faster (6 us up to 2048 pairs; 4096 5.9 and 7.9).
   const int n_short = plan->n_merge_short;
   int n_mid = plan->n_merge_mid, n_long = (int)plan->merge_tok.size() - n_short - n_mid;
   if (n_long > 0 && (int64_t)n_mid * plan->q_heads <= kMidMergePairs) {

@@ -1524,6 +1524,12 @@ def test_merge_lists_around_what_a_slice_holds(out_bf16):
     test_merge_lists_at_the_edges_of_their_kernels([15, 22, 23, 62, 63, 64, 70, 94, 95, 96, 130], 8, out_bf16)
 
 
+@pytest.mark.parametrize("out_bf16", [False, True])
+def test_merge_lists_around_the_places_that_a_slice_fetches(out_bf16):
+    """Lists of 8 to 34 partials: two, four and eight places a slice, one partial less and more, those of 8 to 15 beside longer ones."""
+    test_merge_lists_at_the_edges_of_their_kernels([7, 8, 11, 14, 15, 16, 17, 24, 30, 31, 32, 33], 8, out_bf16)
+
+
 # ---- the step as a HIP graph ----------------------------------------------------------------------
 @pytest.mark.parametrize("fuse", [False, True])
 def test_step_replays_from_a_hip_graph(fuse):
