@@ -119,7 +119,7 @@ def _host(a, dtype) -> np.ndarray:
 def _offsets(counts, n: int) -> np.ndarray:
     """0 and the running sums of n counts."""
     # (plain ints alone: narrow numpy scalars would be added in their own width, one-element lists strung together)
-    if type(counts) is list and len(counts) == n and set(map(type, counts)) <= {int}:
+    if type(counts) is list and len(counts) == n and [*map(type, counts)].count(int) == n:
         try:
             return np.array([0, *accumulate(counts)], np.int32)
         except OverflowError:
