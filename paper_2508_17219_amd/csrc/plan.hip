@@ -341,7 +341,10 @@ RowCut plan_row_cut(const std::vector<RowItem>& items, int64_t n_cu, int32_t kv_
     if (beside_units) return c;
     if (cut_workgroups(items, c, kv_heads, true) <= n_cu) return one_round_cut(items, n_cu, kv_heads, c);
     // more than half a round whole: as many pieces as end the launch earliest, their partials counted (26 row tiles of 8 kv
-    // heads on one list of 6k tokens: whole 285 us, in the three pieces that two workgroups per CU would take 324)
+    // heads on one list of 6k tokens: whole 285 us, in the three pieces that two workgroups per CU would take 324).  The line is not
+    // a measured one: below it the estimate would often be right too (512 tokens on 32k, 8 kv heads: four pieces 246 us, the eight
+    // that are two workgroups per CU 263), but how many pieces such a prompt gets is part of the plan's stated behaviour, which
+    // its tests count.
     if (2 * wgs > n_cu) {
       RowCut tried = c;
       double best_cost = 0;
