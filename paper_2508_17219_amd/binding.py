@@ -118,11 +118,14 @@ def _host(a, dtype) -> np.ndarray:
 
 def _offsets(counts, n: int) -> np.ndarray:
     """0 and the running sums of n counts."""
-    # (plain ints alone: narrow numpy scalars would be added in their own width, one-element lists strung together)
-    if type(counts) is list and len(counts) == n and [*map(type, counts)].count(int) == n:
+    # (plain ints alone: narrow numpy scalars would be added in their own width, one-element lists strung together.  Anything else
+    # in the list leaves its type in the last sum: looking at every entry's type takes 16 counts 1.03 us, this 0.82)
+    if type(counts) is list and n and len(counts) == n and type(counts[0]) is int:
         try:
-            return np.array([0, *accumulate(counts)], np.int32)
-        except OverflowError:
+            sums = [0, *accumulate(counts)]
+            if type(sums[-1]) is int:
+                return np.array(sums, np.int32)
+        except Exception:       # numpy's to take or refuse
             pass
     out = np.zeros(n + 1, np.int32)
     out[1:] = np.cumsum(counts)

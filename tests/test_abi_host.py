@@ -678,7 +678,8 @@ def test_batched_append_validates_every_chain_before_anything_changes():
 @pytest.mark.parametrize("counts", [
     [3, 0, 5], [], [2**31 - 1, 1], [2**32 + 5], [True, False, True], [1.75, 2.5], [[1], [2]], (1, 2), range(3), np.array([7, 9]),
     [np.int8(100), np.int8(100)], [np.uint8(200), np.int64(100)], np.array([200, 100], np.uint8), [torch.tensor(200, dtype=torch.uint8)] * 2,
-    [np.array([1]), np.array([2])], [np.float32(2**24), np.float32(1)],
+    [np.array([1]), np.array([2])], [np.float32(2**24), np.float32(1)], [5, np.int8(100), np.int8(100)], [2**24, np.float32(1), 1],
+    [1, torch.tensor(255, dtype=torch.uint8), 1], [3, np.True_, 4], [1, 1.75, 1.75], [2, True, True],
 ], ids=repr)
 def test_row_counts_of_any_type_become_the_same_offsets(counts):
     """Counts that a caller took out of an array or a tensor, of whatever width: the offsets are numpy's running sums."""
